@@ -6,7 +6,7 @@
 
 namespace lsrvt {
 
-constexpr int kLayTile = 4096;  // consecutive linear indices walked by one wave
+constexpr int kLayTile = 4096;  // consecutive linear indices sorted by one workgroup
 
 // Device buffers of one layout build.  Cells are numbered by rank: the
 // position of their site when sites are sorted stably by component.
@@ -25,10 +25,10 @@ struct LayoutWork {
   uint32_t *cell_off;       // [S + 1] start of every cell, by rank
   uint32_t *tile_nd;        // [T] distinct cells per tile
   uint32_t *pair_off;       // [T + 1] first (tile, cell) pair of every tile
-  uint8_t *tile_big;        // [T] 0: small table, 1: medium table, 2: whole-tile table
+  uint32_t *tile_nv;        // [T] placed voxels per tile
+  uint16_t *tile_order;     // [T][kLayTile] places of a tile's voxels ordered by cell
   uint32_t *big_list;       // [T] tiles deferred by the small table
-  uint32_t *huge_list;      // [T] tiles deferred by the medium table
-  uint32_t *big_cnt;        // [4] [0] big_list length, [1] huge_list length
+  uint32_t *big_cnt;        // [1] their number
   uint32_t *pair_cell;      // [Pcap] cell of every pair, then reused
   uint32_t *pair_cnt;       // [Pcap] voxels of every pair, then segment starts
   uint32_t *val_a, *val_b;  // [Pcap + 1] pair sort ping-pong / scan output
@@ -67,10 +67,10 @@ void layout_take(A &a, const Geom &g, uint32_t S, uint32_t C, LayoutWork *W) {
   auto cell_off = a.template take<uint32_t>(s1 + 1);
   auto tile_nd = a.template take<uint32_t>(T);
   auto pair_off = a.template take<uint32_t>(T + 1);
-  auto tile_big = a.template take<uint8_t>(T);
+  auto tile_nv = a.template take<uint32_t>(T);
+  auto tile_order = a.template take<uint16_t>((size_t)T * kLayTile);
   auto big_list = a.template take<uint32_t>(T);
-  auto huge_list = a.template take<uint32_t>(T);
-  auto big_cnt = a.template take<uint32_t>(4);
+  auto big_cnt = a.template take<uint32_t>(1);
   auto pair_cell = a.template take<uint32_t>(P);
   auto pair_cnt = a.template take<uint32_t>(P);
   auto val_a = a.template take<uint32_t>(P + 1);
@@ -90,9 +90,9 @@ void layout_take(A &a, const Geom &g, uint32_t S, uint32_t C, LayoutWork *W) {
     W->cell_off = cell_off;
     W->tile_nd = tile_nd;
     W->pair_off = pair_off;
-    W->tile_big = tile_big;
+    W->tile_nv = tile_nv;
+    W->tile_order = tile_order;
     W->big_list = big_list;
-    W->huge_list = huge_list;
     W->big_cnt = big_cnt;
     W->pair_cell = pair_cell;
     W->pair_cnt = pair_cnt;

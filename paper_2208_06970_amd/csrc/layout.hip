@@ -8,40 +8,31 @@
 // Components are numbered band-major, so this order is also band-major.
 //
 // Voxels are placed by a deterministic counting sort.  The volume is cut
-// into tiles of 4096 consecutive linear indices.  One wave walks a tile in
-// index order, 64 voxels at a time: ballots split each group into runs of
-// equal cell, and an LDS hash table numbers the distinct cells of the tile
-// in order of first appearance.  Every (tile, cell) pair becomes one segment
-// of the output.  The pairs are sorted stably by cell rank, so the segments
-// of a cell follow each other in tile order, and an exclusive scan of their
-// sizes gives every segment's start.  A last walk writes each voxel to its
-// segment start plus the number of earlier voxels of its cell in the tile.
-// Tiles with more distinct cells than the common kernel's table holds are
-// listed and walked with a medium table, and those that overflow it by a
-// kernel whose table covers a whole tile.
+// into tiles of 4096 consecutive linear indices.  One workgroup per tile sorts
+// its voxels stably by cell in LDS (k_lay_sort) and keeps the order as one
+// 16-bit word per voxel.  Every (tile, cell) pair becomes one segment of the
+// output.  The pairs are sorted stably by cell rank, so the segments of a cell
+// follow each other in tile order, and an exclusive scan of their sizes gives
+// every segment's start.  A last pass over the tiles' orders writes each voxel
+// to its segment (k_lay_runs).
 #include "layout.h"
 
 namespace lsrvt {
 
 namespace {
 
-// Three table sizes: tiles with at most 256 distinct cells (almost all) are
-// walked with a small table, so many waves fit a CU; a tile with more is
-// deferred to a medium table (640), and from there to one that covers a
-// whole tile.
-constexpr int kSmallCap = 512, kSmallMax = 256;
-constexpr int kMidCap = 1024, kMidMax = 640;
-constexpr int kBigCap = kLayTile, kBigMax = kLayTile;
-constexpr int kLayAhead = 4;  // 64-voxel groups whose cells are loaded ahead of the walk
-
-enum { kPassCount = 0, kPassPairs = 1, kPassPlace = 2 };
-
-template <int Cap, int MaxD>
-struct TileTab {
-  uint32_t key[Cap];    // cell id, kNone = empty
-  uint32_t slot[Cap];   // order of first appearance in the tile
-  uint32_t val[MaxD];   // per slot: running voxel count or next output index
-};
+constexpr int kLayThreads = 256;
+constexpr int kLayWaves = kLayThreads / kWave;
+constexpr int kLayGroups = kLayTile / kLayThreads;  // 64-voxel groups of a wave, consecutive
+// Hash tables of a tile's distinct cells: a small one for almost all tiles, so
+// that eight workgroups fit a CU, and one that holds a whole tile (a tile
+// that overflows the small table is listed for it).  A thread adds one cell
+// between two looks at the count, so at most kLayThreads more than MaxD are
+// added and the tables keep free slots.
+constexpr int kSmallCap = 1024, kSmallMax = 640;
+constexpr int kBigCap = 2 * kLayTile, kBigMax = kLayTile;
+static_assert(kSmallMax + kLayThreads < kSmallCap, "free slots in the small table");
+constexpr uint32_t kLayHead = 0x8000u;  // first voxel of its cell in the tile's order
 
 struct LayArgs {
   const uint32_t *cell;
@@ -49,160 +40,268 @@ struct LayArgs {
   uint32_t S;
   int64_t n_tiles;
   unsigned long long *cnt;
-  uint32_t *tile_nd;
-  uint8_t *tile_big;    // 0: small table, 1: medium, 2: whole-tile table
+  uint32_t *tile_nd;    // distinct cells of every tile
+  uint32_t *tile_nv;    // placed voxels of every tile
+  uint16_t *order;      // [tiles][4096] the placed voxels' places in the tile, by cell, kLayHead at each cell's first
   uint32_t *big_list;   // tiles deferred by the small table
-  uint32_t *huge_list;  // tiles deferred by the medium table
-  uint32_t *big_cnt;    // [0] big_list length, [1] huge_list length
+  uint32_t *big_cnt;    // their number
   const uint32_t *pair_off;
   uint32_t *pair_cell, *pair_cnt;
   const uint32_t *seg_off;
   uint32_t *perm;
 };
 
-// One wave walks one tile, 64 voxels at a time, with the cells of the next
-// kLayAhead groups loaded while the current ones are walked.  Returns false
-// (and has no side effects in the count and pair passes) when the tile has
-// more than MaxD distinct cells.
-template <int Cap, int MaxD, int Pass>
-__device__ bool lay_walk(const LayArgs &A, int64_t tile, TileTab<Cap, MaxD> &T, uint32_t &nd_out) {
-  const int lane = threadIdx.x;
-  for (int i = lane; i < Cap; i += kWave) T.key[i] = kNone;
-  const int64_t v0 = tile * kLayTile;
-  if (Pass == kPassPlace) {
-    // segment starts of the tile's pairs, in the same first-appearance order
-    const uint32_t p0 = A.pair_off[tile], np = A.pair_off[tile + 1] - p0;
-    for (uint32_t i = lane; i < np && i < (uint32_t)MaxD; i += kWave) T.val[i] = A.seg_off[p0 + i];
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t u = __shfl_up(v, o, kWave);
+    if (lane >= o) v += u;
   }
-  __syncthreads();
-  auto load = [&](int g) {
-    const int64_t v = v0 + g + lane;
-    const uint32_t c = v < A.n ? A.cell[v] : kNone;
-    return c < A.S ? c : kNone;
-  };
-  uint32_t cur[kLayAhead], nxt[kLayAhead];
+  return v;
+}
+
+// A tile's voxels sorted stably by cell.  Wave w holds the tile's groups
+// [16 w, 16 w + 16) of 64 voxels, one voxel a lane.  The first voxel of every
+// run of equal cells in a group looks its cell up in a hash table of the tile
+// (LDS, atomicCAS), the occupied slots are numbered in slot order (the order
+// of the cells inside a tile is of no consequence, as the pairs are sorted by
+// cell rank), and the voxels are sorted by that number, six bits a pass and
+// so one pass for up to 63 cells: ballots rank a lane among the equal digits
+// of its group, counters in LDS carry the ranks over a wave's groups, and one
+// scan of the counters gives the places.  Unplaced voxels (no cell) take the
+// last number and are left out.
+//
+// Bound by the ballots and the LDS round trips of a pass; four waves a tile
+// and no serial walk over runs of equal cells, so the time depends little on
+// how fragmented the cells are.  The three walks of a wave per tile that this
+// and k_lay_runs replace took 1.8 ms on 512 x 256 x 256 voxels in 9155 cells
+// (now 0.35 + 0.08 + 0.05 ms), 2.5 ms on 333 x 255 x 201 in 322209 (now 0.37)
+// and 5.0 ms on 131 x 121 x 77 in 123464 (now 0.1): there a tile's ~1000 runs
+// were taken one after another.  Four waves a SIMD: five and six spill more
+// and are 3 % and 5 % slower on the whole call.
+template <int Cap, int MaxD, bool small>
+__global__ __launch_bounds__(kLayThreads, small ? 4 : 3) void k_lay_sort(LayArgs A) {
+  __shared__ uint32_t key[Cap];         // cell id (kNone: free), then its number
+  __shared__ uint32_t item[kLayTile];   // number << 12 | place in the tile
+  __shared__ uint32_t cnt[kLayWaves][kWave];
+  __shared__ uint32_t part[kLayWaves];
+  __shared__ uint32_t found, placed;
+  const int t = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const uint32_t n_list = small ? (uint32_t)A.n_tiles : *A.big_cnt;
+  for (uint32_t b = blockIdx.x; b < n_list; b += gridDim.x) {
+    const uint32_t tile = small ? b : A.big_list[b];
+    const int64_t v0 = (int64_t)tile * kLayTile;
+    uint32_t c[kLayGroups];
 #pragma unroll
-  for (int j = 0; j < kLayAhead; ++j) cur[j] = load(j * kWave);
-  uint32_t nd = 0, last_c = kNone, last_s = 0;
-  for (int g0 = 0; g0 < kLayTile; g0 += kLayAhead * kWave) {
-    if (g0 + kLayAhead * kWave < kLayTile) {
-#pragma unroll
-      for (int j = 0; j < kLayAhead; ++j) nxt[j] = load(g0 + (kLayAhead + j) * kWave);
+    for (int g = 0; g < kLayGroups; ++g) {
+      const int64_t v = v0 + (w * kLayGroups + g) * kWave + lane;
+      c[g] = v < A.n ? A.cell[v] : kNone;
+      if (c[g] >= A.S) c[g] = kNone;
     }
+    for (int i = t; i < Cap; i += kLayThreads) key[i] = kNone;
+    if (t == 0) found = placed = 0u;
+    __syncthreads();
+    // slots of the table
+    bool over = false;
+    uint32_t n_placed = 0;
 #pragma unroll
-    for (int j = 0; j < kLayAhead; ++j) {
-      const int g = g0 + j * kWave;
-      const uint32_t c = cur[j];
-      uint64_t rem = __ballot(c != kNone);
-      while (rem) {
-        const int leader = __ffsll((unsigned long long)rem) - 1;
-        const uint32_t cl = __builtin_amdgcn_readlane(c, leader);
-        const uint64_t mask = __ballot(c == cl);
-        rem &= ~mask;
-        uint32_t sl = last_s;
-        if (cl != last_c) {
-          uint32_t h = (cl * 2654435761u) & (Cap - 1);
-          for (int probe = 0;; ++probe) {
-            if (probe == Cap) return false;  // unreachable: the table always keeps a free slot for a new cell
-            const uint32_t k = T.key[h];
-            if (k == cl) {
-              sl = T.slot[h];
+    for (int g = 0; g < kLayGroups; ++g) {
+      const uint32_t cl = c[g], left = __shfl_up(cl, 1, kWave);
+      const bool first = lane == 0 || cl != left;
+      const uint64_t firsts = __ballot(first);
+      n_placed += (uint32_t)__popcll(__ballot(cl != kNone));
+      uint32_t h = 0;
+      if (first && cl != kNone && !over) {
+        h = (cl * 2654435761u) & (Cap - 1);
+        for (int probe = 0; probe < Cap; ++probe) {
+          const uint32_t k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (k == cl) break;
+          if (k == kNone) {
+            const uint32_t old = atomicCAS(&key[h], kNone, cl);
+            if (old == kNone) {
+              over = atomicAdd(&found, 1u) >= (uint32_t)MaxD;
               break;
             }
-            if (k == kNone) {
-              if (nd >= (uint32_t)MaxD) return false;
-              // every lane stores the same values, so each lane reads back its own stores
-              T.key[h] = cl;
-              T.slot[h] = nd;
-              sl = nd;
-              if (Pass != kPassPlace) T.val[sl] = 0u;
-              ++nd;
-              break;
-            }
-            h = (h + 1) & (Cap - 1);
+            if (old == cl) break;
           }
-          last_c = cl;
-          last_s = sl;
+          h = (h + 1) & (Cap - 1);
         }
-        const uint32_t base = T.val[sl];
-        if (Pass == kPassPlace && ((mask >> lane) & 1ull))
-          A.perm[base + (uint32_t)__popcll(mask & lanemask_lt())] = (uint32_t)(v0 + g + lane);
-        T.val[sl] = base + (uint32_t)__popcll(mask);
+        if (small)
+          over = over || __hip_atomic_load(&found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > (uint32_t)MaxD;
       }
+      // the run's slot from its first voxel
+      const int leader = kWave - 1 - __clzll((long long)(firsts & (lanemask_lt() | (1ull << lane))));
+      h = __shfl(h, leader, kWave);
+      c[g] = cl == kNone ? kNone : h;
+    }
+    if (lane == 0) atomicAdd(&placed, n_placed);
+    __syncthreads();
+    const uint32_t nd = found;
+    if (small && nd > (uint32_t)MaxD) {
+      if (t == 0) A.big_list[atomicAdd(A.big_cnt, 1u)] = tile;
+      __syncthreads();
+      continue;
+    }
+    if (nd == 1 && placed == (uint32_t)kLayTile) {  // a tile inside one cell is in order
+#pragma unroll
+      for (int g = 0; g < kLayGroups; ++g) {
+        const uint32_t q = (uint32_t)((w * kLayGroups + g) * kWave + lane);
+        A.order[v0 + q] = (uint16_t)(q | (q == 0 ? kLayHead : 0u));
+      }
+      if (t == 0) {
+        A.tile_nd[tile] = 1;
+        A.tile_nv[tile] = kLayTile;
+      }
+      __syncthreads();
+      continue;
+    }
+    // numbers of the occupied slots, in slot order
+    constexpr int kOwn = Cap / kLayThreads;
+    uint32_t own = 0;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) own += key[t * kOwn + i] != kNone ? 1u : 0u;
+    const uint32_t inc = wave_scan_add(own);
+    if (lane == kWave - 1) part[w] = inc;
+    __syncthreads();
+    uint32_t num = inc - own;
+    for (int i = 0; i < w; ++i) num += part[i];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+      if (key[t * kOwn + i] != kNone) key[t * kOwn + i] = num++;
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kLayGroups; ++g)
+      c[g] = (c[g] == kNone ? nd : key[c[g]]) << 12 | (uint32_t)((w * kLayGroups + g) * kWave + lane);
+    // stable passes of six bits
+    for (uint32_t bits = 0; nd >> bits; bits += 6) {
+      const int shift = 12 + (int)bits;
+      uint32_t r[kLayGroups];
+      cnt[w][lane] = 0u;
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int g = 0; g < kLayGroups; ++g) {
+        const uint32_t dg = c[g] >> shift & 63u;
+        uint64_t same = ~0ull;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+          const uint64_t bal = __ballot(dg >> k & 1u);
+          same &= dg >> k & 1u ? bal : ~bal;
+        }
+        // LDS operations of a wave complete in order
+        const uint32_t base = __hip_atomic_load(&cnt[w][dg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        r[g] = base + (uint32_t)__popcll(same & lanemask_lt());
+        __builtin_amdgcn_wave_barrier();
+        if (same >> lane == 1ull)
+          __hip_atomic_store(&cnt[w][dg], base + (uint32_t)__popcll(same), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_wave_barrier();
+      }
+      __syncthreads();
+      if (w == 0) {
+        uint32_t of[kLayWaves], all = 0;
+#pragma unroll
+        for (int i = 0; i < kLayWaves; ++i) {
+          of[i] = all;
+          all += cnt[i][lane];
+        }
+        const uint32_t start = wave_scan_add(all) - all;
+#pragma unroll
+        for (int i = 0; i < kLayWaves; ++i) cnt[i][lane] = start + of[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < kLayGroups; ++g) item[cnt[w][c[g] >> shift & 63u] + r[g]] = c[g];
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < kLayGroups; ++g) c[g] = item[(w * kLayGroups + g) * kWave + lane];
+      __syncthreads();
+    }
+    // (with nd = 0 nothing is placed)
+    const uint32_t nv = placed;
+#pragma unroll
+    for (int g = 0; g < kLayGroups; ++g) {
+      const uint32_t q = (uint32_t)((w * kLayGroups + g) * kWave + lane);
+      if (q < nv) {
+        const bool head = q == 0 || item[q - 1] >> 12 != c[g] >> 12;
+        A.order[v0 + q] = (uint16_t)((c[g] & 0xFFFu) | (head ? kLayHead : 0u));
+      }
+    }
+    if (t == 0) {
+      A.tile_nd[tile] = nd;
+      A.tile_nv[tile] = nv;
+    }
+    __syncthreads();
+  }
+}
+
+// The runs of equal cells in every tile's order.  place = false: the (tile,
+// cell) pairs with their voxel counts, also added to the cells' totals; place
+// = true: every voxel to its pair's segment start plus its place in the run.
+// One streaming read of the order (2 B per voxel); the runs are numbered by
+// ballots, a wave's total carried to the next waves through LDS.
+template <bool place>
+__global__ __launch_bounds__(kLayThreads) void k_lay_runs(LayArgs A) {
+  __shared__ uint32_t at[kLayTile + 1];  // per run: its first place in the order, or its segment start less that
+  __shared__ uint32_t part[kLayWaves];
+  const int t = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  for (uint32_t tile = blockIdx.x; tile < (uint32_t)A.n_tiles; tile += gridDim.x) {
+    const uint32_t nv = A.tile_nv[tile];
+    if (nv == 0) continue;  // uniform
+    const uint32_t p0 = A.pair_off[tile];
+    const int64_t v0 = (int64_t)tile * kLayTile;
+    uint32_t e[kLayGroups];
+    uint64_t heads[kLayGroups];
+    uint32_t total = 0;
+#pragma unroll
+    for (int g = 0; g < kLayGroups; ++g) {
+      const uint32_t q = (uint32_t)((w * kLayGroups + g) * kWave + lane);
+      e[g] = q < nv ? A.order[v0 + q] : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < kLayAhead; ++j) cur[j] = nxt[j];
-  }
-  nd_out = nd;
-  return true;
-}
-
-// Level 0 (small table) defers a tile to big_list, level 1 (medium) to
-// huge_list; level 2 cannot fail.  Only the count pass defers; the later
-// passes skip deferred tiles up front.
-template <int Cap, int MaxD, int Pass, int Level>
-__device__ void lay_tile(const LayArgs &A, int64_t tile, TileTab<Cap, MaxD> &T) {
-  uint32_t nd = 0;
-  const bool ok = lay_walk<Cap, MaxD, Pass>(A, tile, T, nd);
-  __syncthreads();
-  if (!ok) {
-    if (Pass == kPassCount && Level < 2 && threadIdx.x == 0) {
-      A.tile_big[tile] = (uint8_t)(Level + 1);
-      A.tile_nd[tile] = 0;
-      if (Level == 0) A.big_list[atomicAdd(&A.big_cnt[0], 1u)] = (uint32_t)tile;
-      else A.huge_list[atomicAdd(&A.big_cnt[1], 1u)] = (uint32_t)tile;
+    for (int g = 0; g < kLayGroups; ++g) {
+      heads[g] = __ballot(e[g] & kLayHead);
+      total += (uint32_t)__popcll(heads[g]);
     }
-    return;
-  }
-  if (Pass == kPassCount) {
-    for (int i = threadIdx.x; i < Cap; i += kWave) {
-      const uint32_t k = T.key[i];
-      if (k != kNone) atomicAdd(&A.cnt[k], (unsigned long long)T.val[T.slot[i]]);
+    if (lane == 0) part[w] = total;
+    __syncthreads();
+    uint32_t before = 0, nd = 0;
+    for (int i = 0; i < kLayWaves; ++i) {
+      if (i < w) before += part[i];
+      nd += part[i];
     }
-    if (threadIdx.x == 0) {
-      A.tile_nd[tile] = nd;
-      A.tile_big[tile] = (uint8_t)Level;
+    uint32_t run = before;
+#pragma unroll
+    for (int g = 0; g < kLayGroups; ++g) {
+      const uint32_t q = (uint32_t)((w * kLayGroups + g) * kWave + lane);
+      if (e[g] & kLayHead) {
+        const uint32_t k = run + (uint32_t)__popcll(heads[g] & lanemask_lt());
+        at[k] = place ? A.seg_off[p0 + k] - q : q;
+        if (!place) A.pair_cell[p0 + k] = A.cell[v0 + (e[g] & 0xFFFu)];
+      }
+      run += (uint32_t)__popcll(heads[g]);
     }
-  } else if (Pass == kPassPairs) {
-    const uint32_t p0 = A.pair_off[tile];
-    for (int i = threadIdx.x; i < Cap; i += kWave) {
-      const uint32_t k = T.key[i];
-      if (k != kNone) {
-        A.pair_cell[p0 + T.slot[i]] = k;
-        A.pair_cnt[p0 + T.slot[i]] = T.val[T.slot[i]];
+    if (!place && t == 0) at[nd] = nv;
+    __syncthreads();
+    if (place) {
+      run = before;
+#pragma unroll
+      for (int g = 0; g < kLayGroups; ++g) {
+        const uint32_t q = (uint32_t)((w * kLayGroups + g) * kWave + lane);
+        const uint32_t k = run + (uint32_t)__popcll(heads[g] & (lanemask_lt() | (1ull << lane)));  // runs begun up to q
+        if (q < nv) A.perm[at[k - 1] + q] = (uint32_t)(v0 + (e[g] & 0xFFFu));
+        run += (uint32_t)__popcll(heads[g]);
+      }
+    } else {
+      for (uint32_t k = t; k < nd; k += kLayThreads) {
+        const uint32_t len = at[k + 1] - at[k];
+        A.pair_cnt[p0 + k] = len;
+        atomicAdd(&A.cnt[A.pair_cell[p0 + k]], (unsigned long long)len);
       }
     }
-  }
-}
-
-template <int Pass>
-__global__ __launch_bounds__(kWave) void k_lay_small(LayArgs A) {
-  __shared__ TileTab<kSmallCap, kSmallMax> T;
-  for (int64_t tile = blockIdx.x; tile < A.n_tiles; tile += gridDim.x) {
-    if (Pass != kPassCount && A.tile_big[tile]) continue;
-    lay_tile<kSmallCap, kSmallMax, Pass, 0>(A, tile, T);
-    __syncthreads();
-  }
-}
-
-template <int Pass>
-__global__ __launch_bounds__(kWave) void k_lay_mid(LayArgs A) {
-  __shared__ TileTab<kMidCap, kMidMax> T;
-  const uint32_t nb = A.big_cnt[0];
-  for (uint32_t i = blockIdx.x; i < nb; i += gridDim.x) {
-    const uint32_t tile = A.big_list[i];
-    if (Pass != kPassCount && A.tile_big[tile] != 1) continue;
-    lay_tile<kMidCap, kMidMax, Pass, 1>(A, tile, T);
-    __syncthreads();
-  }
-}
-
-template <int Pass>
-__global__ __launch_bounds__(kWave) void k_lay_big(LayArgs A) {
-  __shared__ TileTab<kBigCap, kBigMax> T;
-  const uint32_t nb = A.big_cnt[1];
-  for (uint32_t i = blockIdx.x; i < nb; i += gridDim.x) {
-    lay_tile<kBigCap, kBigMax, Pass, 2>(A, A.huge_list[i], T);
     __syncthreads();
   }
 }
@@ -299,7 +398,7 @@ int32_t layout_sites(const uint32_t *site_comp, uint32_t S, uint32_t C, LayoutWo
 int32_t layout_voxels(const uint32_t *cell, const Geom &g, uint32_t S, LayoutWork &W, uint32_t *perm, hipStream_t s) {
   int32_t rc;
   if ((rc = fill<unsigned long long>(W.cnt, S ? S : 1, 0ull, s))) return rc;
-  if ((rc = fill<uint32_t>(W.big_cnt, 2, 0u, s))) return rc;
+  if ((rc = fill<uint32_t>(W.big_cnt, 1, 0u, s))) return rc;
   if (S == 0) return fill<uint32_t>(W.cell_off, 1, 0u, s);
   const int64_t T = W.n_tiles;
   LayArgs A;
@@ -309,9 +408,9 @@ int32_t layout_voxels(const uint32_t *cell, const Geom &g, uint32_t S, LayoutWor
   A.n_tiles = T;
   A.cnt = W.cnt;
   A.tile_nd = W.tile_nd;
-  A.tile_big = W.tile_big;
+  A.tile_nv = W.tile_nv;
+  A.order = W.tile_order;
   A.big_list = W.big_list;
-  A.huge_list = W.huge_list;
   A.big_cnt = W.big_cnt;
   A.pair_off = W.pair_off;
   A.pair_cell = W.pair_cell;
@@ -319,11 +418,10 @@ int32_t layout_voxels(const uint32_t *cell, const Geom &g, uint32_t S, LayoutWor
   A.seg_off = W.pair_cnt;  // segment starts replace the counts before the place pass
   A.perm = perm;
   const unsigned grid = (unsigned)(T < 65535 ? T : 65535);
-  const unsigned grid_mid = 2048, grid_big = 256;
-  // 1. distinct cells per tile and voxels per site
-  hipLaunchKernelGGL(k_lay_small<kPassCount>, dim3(grid), dim3(kWave), 0, s, A);
-  hipLaunchKernelGGL(k_lay_mid<kPassCount>, dim3(grid_mid), dim3(kWave), 0, s, A);
-  hipLaunchKernelGGL(k_lay_big<kPassCount>, dim3(grid_big), dim3(kWave), 0, s, A);
+  // 1. every tile's order and distinct cells
+  hipLaunchKernelGGL((k_lay_sort<kSmallCap, kSmallMax, true>), dim3(grid), dim3(kLayThreads), 0, s, A);
+  hipLaunchKernelGGL((k_lay_sort<kBigCap, kBigMax, false>), dim3((unsigned)(T < 768 ? T : 768)), dim3(kLayThreads), 0,
+                     s, A);
   LSRVT_LAUNCHED();
   if ((rc = ScanU32::run(W.tile_nd, T, W.pair_off, W.scratch, W.scratch_bytes, s))) return rc;
   uint32_t P = 0;
@@ -332,10 +430,8 @@ int32_t layout_voxels(const uint32_t *cell, const Geom &g, uint32_t S, LayoutWor
     if (rc_) return rc_;
   }
   if ((int64_t)P > W.pair_cap) return LSRVT_EDEVICE;  // cannot happen: the capacity is an upper bound
-  // 2. the pairs, in tile order
-  hipLaunchKernelGGL(k_lay_small<kPassPairs>, dim3(grid), dim3(kWave), 0, s, A);
-  hipLaunchKernelGGL(k_lay_mid<kPassPairs>, dim3(grid_mid), dim3(kWave), 0, s, A);
-  hipLaunchKernelGGL(k_lay_big<kPassPairs>, dim3(grid_big), dim3(kWave), 0, s, A);
+  // 2. the pairs, in tile order, and the voxels per site
+  hipLaunchKernelGGL(k_lay_runs<false>, dim3(grid), dim3(kLayThreads), 0, s, A);
   LSRVT_LAUNCHED();
   // 3. stable sort of the pairs by cell rank
   if (P) {
@@ -361,9 +457,7 @@ int32_t layout_voxels(const uint32_t *cell, const Geom &g, uint32_t S, LayoutWor
     hipLaunchKernelGGL(k_scatter32, dim3(blocks_for(P)), dim3(256), 0, s, other, cur, (int64_t)P, W.pair_cnt);
     LSRVT_LAUNCHED();
     // 5. place every voxel
-    hipLaunchKernelGGL(k_lay_small<kPassPlace>, dim3(grid), dim3(kWave), 0, s, A);
-    hipLaunchKernelGGL(k_lay_mid<kPassPlace>, dim3(grid_mid), dim3(kWave), 0, s, A);
-    hipLaunchKernelGGL(k_lay_big<kPassPlace>, dim3(grid_big), dim3(kWave), 0, s, A);
+    hipLaunchKernelGGL(k_lay_runs<true>, dim3(grid), dim3(kLayThreads), 0, s, A);
     LSRVT_LAUNCHED();
   }
   // cell offsets by rank
