@@ -267,7 +267,7 @@ def bench_flame(args):
         "lloyd_gvox_per_iter_s": round(n * wl.iters / (ph["lloyd"] / 1e3) / 1e9, 4) if ph["lloyd"] else None,
         "stats_gvox_s": round(n / (ph["aggregate"] / 1e3) / 1e9, 4) if ph["aggregate"] else None,
         "end_to_end_gvox_s": round(n / (ms / 1e3) / 1e9, 4),
-        "stats_dtype": "f32 compensated per cell, f64 merges",
+        "stats_dtype": "f64 sums and merges, f32 cell outputs",
         "tuning": {"vt_schedule": "bricks" if timing[4] == 2 else "levels" if timing[4] == 1 else "both",
                    "br_grid": grid, "stats_tile": tile},
         "roofline": roofline(timing, "flame"),

@@ -6,19 +6,17 @@
 //     one contiguous range, cells in (component, site id) order and voxels
 //     in index order;
 //  2. every cell's range is cut into work items of at most kItemVoxels;
-//  3. one workgroup per item gathers the item's values into LDS, shifted by
-//     the value at the cell's site, and accumulates per "unit" float32 sums
-//     with an error-free two-sum compensation (hi + lo): units are sum d_j
-//     and sum d_j d_k (the product error of d_j d_k is folded into lo with
-//     an FMA).  Lanes own units, so the order of every sum is fixed.
-//     Histograms and extrema are integer / compare operations and go through
-//     LDS and then global atomics;
-//  4. per cell, the item partials are combined in item order; the
-//     compensated float32 pair of every unit is exact in float64, where the
-//     cell's mean, M2 and co-moments are formed once (a constant amount of
-//     work per cell, and the inputs the float64 merges need); the float32
-//     cell outputs are those values rounded once.  Every sum over voxels is
-//     float32;
+//  3. one workgroup per item (one wave for a small cell) gathers the item's
+//     values and sums, per "unit", d_j and d_j d_k in float64, d being the
+//     float32 difference from the value at the cell's site: exact products,
+//     so the only rounding besides is that of the sums (2^-53 of their size).  With the
+//     covariance the sums are a matrix product of the staged values with
+//     themselves on the matrix cores; without, lanes own voxels.  The order
+//     of every sum is fixed.  Histograms and extrema are integer / compare
+//     operations and go through LDS and registers;
+//  4. per cell, the item partials are combined in item order and the cell's
+//     mean, M2 and co-moments formed in float64; the float32 cell outputs are
+//     those values rounded once;
 //  5. Chan et al.'s pairwise merge in float64: cells of a component in site
 //     id order, then components of a band in component id order.  Counts,
 //     extrema and histograms merge exactly with atomics.
@@ -31,7 +29,8 @@ namespace lsrvt {
 namespace {
 
 constexpr int kAggThreads = 256;
-constexpr int kAggMaxThreads = 512;  // k_agg_cell with two lane groups of up to 256 units
+constexpr int kAggWaves = kAggThreads / kWave;
+constexpr int kFold = 32;  // item partials of a large cell added together before the finalize
 constexpr int kMaxVars = 32;
 constexpr int kMaxPairs = kMaxVars * (kMaxVars + 1) / 2;
 constexpr int64_t kItemVoxels = 4096;
@@ -47,19 +46,7 @@ struct BBox {
   uint32_t *x0, *x1, *y0, *y1, *z0, *z1;
 };
 
-__device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
-  s = a + b;
-  float bb = s - a;
-  e = (a - (s - bb)) + (b - bb);
-}
-
-// Compensated accumulate of x (with an exact extra error term ex) into (hi, lo).
-__device__ __forceinline__ void acc(float &hi, float &lo, float x, float ex) {
-  float s, e;
-  two_sum(hi, x, s, e);
-  hi = s;
-  lo += e + ex;
-}
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // 1-2. the voxels of every cell are a contiguous range of the structured
@@ -115,18 +102,17 @@ struct CellArgs {
   const float *vars;  // [m][N]
   const float *edges; // [m][B+1] or null
   int64_t n;
-  int m, B, U, G, P, tile;  // tile: voxels staged in LDS per round (1, 2 or 4 times the block size)
+  int m, B, U, tile;          // tile: voxels staged in LDS per round, a multiple of 256
+  uint32_t stage;             // bytes of the stage
   Pairs pairs;
   const uint32_t *item_off;   // [S + 1] by rank
   const uint32_t *item_rank;  // [n_items]
   const uint32_t *list;       // items of this launch
   const uint32_t *list_cnt;   // their number (device)
-  float *part_hi, *part_lo;  // [n_items][U]
+  double *part;               // [n_items][U]
   uint32_t *hist;            // cell histograms [S][m][B] (zeroed) or null
   uint32_t *kmin, *kmax;     // ordered keys [S][m]
 };
-
-constexpr int kMaxVPT = 4;  // voxels per thread and round
 
 // Wave-wide min / max by DPP lane moves (quad permutes, row mirrors, row
 // broadcasts; every lane of the wave active): the result is read from the
@@ -152,6 +138,11 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
 }
 #undef LSRVT_DPP_STEP
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
 
 // Histogram bin of x: #{interior edges e_1..e_{B-1} <= x} for ascending
 // edges e_0..e_B (sc = B / (e_B - e_0)).  A guess from the mean edge spacing
@@ -172,35 +163,162 @@ __device__ __forceinline__ int hist_bin(float x, const float *e, int B, float e0
   return a - 1;
 }
 
-// R = unit slots per lane: with R == 1 the U units are replicated over G
-// lane groups that split each staging round's voxels into G contiguous
-// ranges (multiples of four voxels, in order; the workgroup has at least
-// G * U threads); with R > 1 (more units than lanes) lane t owns units t,
-// t + NT, ... and G = 1.  VPT = voxels staged per thread and round (the
-// round holds VPT * NT voxels).
-template <int R, int VPT>
-__global__ __launch_bounds__(kAggMaxThreads) void k_agg_cell(CellArgs A) {
-  extern __shared__ uint8_t smem[];
-  const int m = A.m, B = A.B, U = A.U, G = A.G, TL = A.tile, ld = A.tile + 4;
-  const int NT = blockDim.x;
-  float *dv = reinterpret_cast<float *>(smem);                       // [m][TL + 4] values minus the site value
-  float *ones = dv + m * ld;                                         // [TL + 4] 1.0: the second factor of Σd
-  uint32_t *hist_l = reinterpret_cast<uint32_t *>(ones + ld);        // [m*B]
-  uint32_t *kmin_l = hist_l + m * B;                                 // [m]
-  uint32_t *kmax_l = kmin_l + m;                                     // [m]
-  float *K = reinterpret_cast<float *>(kmax_l + m);                  // [m]
-  float *ph = K + m;                                                 // [G*U]
-  float *pl = ph + G * U;                                            // [G*U]
-  float *edg = pl + G * U;                                           // [m][B+1]
-  float *scl = edg + m * (B + 1);                                    // [m] B / (e_B - e_0)
-  const int t = threadIdx.x;
-  const int lane = lane_id();
-  const int grp = R == 1 ? t / U : 0;
-  if (B > 0) {
-    for (int i = t; i < m * (B + 1); i += NT) edg[i] = A.edges[i];
-    for (int j = t; j < m; j += NT) scl[j] = (float)B / (A.edges[j * (B + 1) + B] - A.edges[j * (B + 1)]);
+// Count x of variable j in the histogram h (LDS) for the active lanes.  The
+// values of a cell lie close together, so most lanes of a wave often meet in
+// one bin, which the LDS would take one after another: the first lane's bin
+// gets one addition for all of its lanes (2.97 ms for the statistics of
+// 512 x 256 x 256 voxels with 18 variables; 3.11 ms without, 3.01 and 3.34 ms
+// with two and four such bins).
+__device__ __forceinline__ void hist_count(uint32_t *h, int bin, int lane) {
+  const int lead = __builtin_amdgcn_readfirstlane(bin);
+  const uint64_t same = __ballot(bin == lead);
+  if (bin != lead)
+    atomicAdd(&h[bin], 1u);
+  else if (lane == __ffsll((unsigned long long)same) - 1)
+    atomicAdd(&h[bin], (uint32_t)__popcll(same));
+}
+
+// How the products are taken.  kDiag: squares only, lanes own voxels.  Else on
+// the matrix cores, whose 16 x 16 x 4 instruction multiplies 16 values of four
+// voxels with each other: k16 for up to 16 variables (with up to 8, or 4, the
+// 16 rows hold the variables of two, or four, groups of voxels, and the
+// diagonal blocks are added); k20 for 17 to 20, the last of them as the
+// columns of 4 x 4 x 4 instructions; k32 for 21 to 32, three 16 x 16 tiles.
+enum { kDiag = 0, k16 = 1, k20 = 2, k32 = 3 };
+
+// Rows held by the variables of one voxel group (a power of two), and their groups.
+__host__ __device__ inline int group_rows(int mode, int m) { return mode != k16 || m > 8 ? 16 : m > 4 ? 8 : 4; }
+
+// The accumulators of one wave.  A lane's operand is variable `row` of voxel
+// group g (k16) at one of four voxels; `extra` is its variable among the ones
+// after the first 16.
+template <int MODE>
+struct CellSums {
+  d4 t00, t01, t11;      // 16 x 16 tiles
+  double e0, ee;         // 4 x 4 x 4 blocks: tile 0 with the extras, the extras with themselves
+  double s0, s1;         // sums of the lane's operands
+  __device__ __forceinline__ void zero() {
+    t00 = t01 = t11 = d4{0.0, 0.0, 0.0, 0.0};
+    e0 = ee = s0 = s1 = 0.0;
   }
-  for (int i = t; i < ld; i += NT) ones[i] = 1.0f;
+  __device__ __forceinline__ void add(double x, double y) {
+    t00 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, t00, 0, 0, 0);
+    s0 += x;
+    if constexpr (MODE == k20) {
+      e0 = __builtin_amdgcn_mfma_f64_4x4x4f64(x, y, e0, 0, 0, 0);
+      ee = __builtin_amdgcn_mfma_f64_4x4x4f64(y, y, ee, 0, 0, 0);
+      s1 += y;
+    }
+    if constexpr (MODE == k32) {
+      t01 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, t01, 0, 0, 0);
+      t11 = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, t11, 0, 0, 0);
+      s1 += y;
+    }
+  }
+};
+
+// The sums of `nw` waves to a row of unit sums: each accumulator in turn goes
+// through `red` (256 doubles), wave by wave, and the units it holds are picked
+// from there.  An accumulator register i of lane l is entry (4 i + l / 16,
+// l % 16) of its 16 x 16 tile, or entry (l / 16, l % 4) of the 4 x 4 block of
+// rows l / 4 % 4.  `sync` orders the LDS accesses of the cooperating threads.
+template <int MODE, class Sync>
+__device__ __forceinline__ void put_sums(const CellSums<MODE> &C, const CellArgs &A, double *red, int t, int nt, int w,
+                                         int nw, double *row, Sync sync) {
+  const int lane = lane_id(), m = A.m, P = A.U - m;
+  const int gr = group_rows(MODE, m), G = 16 / gr;
+  auto tile = [&](const d4 &v, int bj, int bk) {  // products of variables bj .. bj + 15 with bk .. bk + 15
+    for (int i = 0; i < nw; ++i) {
+      if (w == i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int at = (4 * q + lane / 16) * 16 + lane % 16;
+          red[at] = i ? red[at] + v[q] : v[q];
+        }
+      sync();
+    }
+    for (int p = t; p < P; p += nt) {
+      const int j = A.pairs.j[p] - bj, k = A.pairs.k[p] - bk;
+      if (j < 0 || k < 0 || j > 15 || k > 15) continue;
+      double x = red[j * 16 + k];
+      for (int g = 1; g < G; ++g) x += red[(g * gr + j) * 16 + g * gr + k];
+      row[m + p] = x;
+    }
+    sync();
+  };
+  // sums of the lanes' own operands: lane l holds variable b + l % gr
+  auto lanes = [&](double v, int b, int gr, int G) {
+    for (int i = 0; i < nw; ++i) {
+      if (w == i) red[lane] = i ? red[lane] + v : v;
+      sync();
+    }
+    for (int u = b + t; u < min(m, b + gr); u += nt) {
+      double x = 0.0;
+      for (int k = 0; k < 4; ++k)
+        for (int g = 0; g < G; ++g) x += red[k * 16 + g * gr + u - b];
+      row[u] = x;
+    }
+    sync();
+  };
+  tile(C.t00, 0, 0);
+  lanes(C.s0, 0, gr, G);
+  if constexpr (MODE == k32) {
+    tile(C.t01, 0, 16);
+    tile(C.t11, 16, 16);
+    lanes(C.s1, 16, 16, 1);
+  }
+  if constexpr (MODE == k20) {
+    auto block = [&](double v, bool first) {
+      for (int i = 0; i < nw; ++i) {
+        if (w == i) red[lane] = i ? red[lane] + v : v;
+        sync();
+      }
+      for (int p = t; p < P; p += nt) {
+        const int j = A.pairs.j[p], k = A.pairs.k[p] - 16;
+        if (k < 0 || (j < 16) != first) continue;
+        row[m + p] = first ? red[(j & 3) * 16 + (j >> 2) * 4 + k] : red[(j - 16) * 16 + k];
+      }
+      sync();
+    };
+    block(C.e0, true);
+    block(C.ee, false);
+    lanes(C.s1, 16, 4, 1);  // every block of four lanes holds the same extras: the first is taken
+  }
+}
+
+// Items of large cells, one workgroup each.  A round's voxels are staged in
+// LDS as [variable][voxel]: wave w gathers variables w, w + 4, ... (64 voxels
+// of one variable per load, NS variables a wave), keeping their extrema in
+// registers and counting their histograms on the way.  Each wave then takes
+// every fourth chunk of 16 voxels (per voxel group): one 16-byte LDS read per
+// lane feeds four matrix steps, and only the conversion to float64 and the
+// subtraction of the site's value are left to the vector units.  Rows are
+// tile + 4 floats apart, so the lanes' reads fall on all banks.
+//
+// Bound by the gathers and the histograms' LDS atomics, not by the products:
+// 512 x 256 x 256 voxels, 18 variables, 32 bins and the covariance take 1.8 ms
+// (1.0 TB/s of values), 0.9 ms of it the histograms and 0.15 ms the products;
+// float32 sums with error terms on the vector units, 11 operations per voxel
+// and unit, took 4.1 ms.
+template <int MODE, int NS>
+__global__ __launch_bounds__(kAggThreads) void k_agg_cell(CellArgs A) {
+  extern __shared__ uint8_t smem[];
+  const int m = A.m, B = A.B, TL = A.tile, ld = A.tile + 4;
+  double *red = reinterpret_cast<double *>(smem);                     // [256], after the rounds
+  float *dv = reinterpret_cast<float *>(smem);                        // [m][tile + 4]
+  uint32_t *hist_l = reinterpret_cast<uint32_t *>(smem + A.stage);    // [m*B]
+  float *edg = reinterpret_cast<float *>(hist_l + m * B);             // [m][B+1]
+  float *scl = edg + m * (B + 1);                                     // [m] B / (e_B - e_0)
+  float *K = scl + m;                                                 // [m]
+  const int t = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int gr = group_rows(MODE, m), G = 16 / gr;
+  const int row0 = min(lane % gr, m - 1);
+  const int row1 = min(16 + (MODE == k20 ? lane % 4 : lane % 16), m - 1);
+  if (B > 0) {
+    for (int i = t; i < m * (B + 1); i += kAggThreads) edg[i] = A.edges[i];
+    for (int j = t; j < m; j += kAggThreads) scl[j] = (float)B / (A.edges[j * (B + 1) + B] - A.edges[j * (B + 1)]);
+  }
 
   const uint32_t n_list = *A.list_cnt;
   for (uint32_t k = blockIdx.x; k < n_list; k += gridDim.x) {
@@ -210,280 +328,274 @@ __global__ __launch_bounds__(kAggMaxThreads) void k_agg_cell(CellArgs A) {
     const uint32_t part = item - A.item_off[r];
     const uint32_t start = A.cell_off[r] + part * (uint32_t)kItemVoxels;
     const uint32_t stop = min(A.cell_off[r + 1], start + (uint32_t)kItemVoxels);
-
-    for (int i = t; i < m * B; i += NT) hist_l[i] = 0;
-    if (t < m) {
-      kmin_l[t] = 0xFFFFFFFFu;
-      kmax_l[t] = 0u;
-      K[t] = A.vars[(int64_t)t * A.n + A.sites[s]];
-    }
-    float hi[R], lo[R];
+    for (int i = t; i < m * B; i += kAggThreads) hist_l[i] = 0;
+    if (t < m) K[t] = A.vars[(int64_t)t * A.n + A.sites[s]];
+    uint32_t kmn[NS], kmx[NS];
+    double d1[MODE == kDiag ? NS : 1], d2[MODE == kDiag ? NS : 1];
+    CellSums<MODE> C;
+    C.zero();
 #pragma unroll
-    for (int q = 0; q < R; ++q) hi[q] = lo[q] = 0.0f;
+    for (int q = 0; q < NS; ++q) {
+      kmn[q] = 0xFFFFFFFFu;
+      kmx[q] = 0u;
+      if constexpr (MODE == kDiag) d1[q] = d2[q] = 0.0;
+    }
     __syncthreads();
+    const float K0 = K[row0], K1 = K[row1];
 
     for (uint32_t base = start; base < stop; base += (uint32_t)TL) {
       const int nt = (int)min((uint32_t)TL, stop - base);
-      // stage: thread t owns voxels t, t + NT, ... of the round
-      uint32_t vv[VPT];
-      bool ok[VPT];
+      for (int sub = 0; sub < nt; sub += 4 * kWave) {
+        uint32_t vv[4];
+        bool ok[4];
 #pragma unroll
-      for (int i = 0; i < VPT; ++i) {
-        const int q = t + i * NT;
-        ok[i] = q < nt;
-        vv[i] = ok[i] ? A.perm[base + q] : 0u;
-      }
-#pragma unroll 2
-      for (int j = 0; j < m; ++j) {
-        const float kj = K[j];
-        const float *col = A.vars + (int64_t)j * A.n;
-        float x[VPT];
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) x[i] = ok[i] ? col[vv[i]] : 0.0f;
-        uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          if (!ok[i]) continue;
-          dv[j * ld + t + i * NT] = x[i] - kj;
-          const uint32_t kk = f2key(x[i]);
-          kmn = min(kmn, kk);
-          kmx = max(kmx, kk);
+        for (int i = 0; i < 4; ++i) {
+          ok[i] = sub + i * kWave + lane < nt;
+          vv[i] = ok[i] ? A.perm[base + sub + i * kWave + lane] : 0u;
         }
-        kmn = wave_min_u32(kmn);
-        kmx = wave_max_u32(kmx);
-        if (lane == 0) {
-          if (kmn != 0xFFFFFFFFu) atomicMin(&kmin_l[j], kmn);
-          if (kmx != 0u) atomicMax(&kmax_l[j], kmx);
-        }
-        if (B > 0) {
-          const float *e = edg + j * (B + 1);
-          const float e0 = e[0], sc = scl[j];
+        float xs[NS][4];  // all of the wave's gathers in flight at once
 #pragma unroll
-          for (int i = 0; i < VPT; ++i)
-            // one LDS atomic per lane; the LDS serialises lanes that hit one bin
-            if (ok[i]) atomicAdd(&hist_l[j * B + hist_bin(x[i], e, B, e0, sc)], 1u);
-        }
-      }
-      __syncthreads();
-      // this group's voxels of the round: [v0, v1), four at a time
-      const int cs = R == 1 ? ((nt + G - 1) / G + 3) & ~3 : nt;
-      const int v0 = min(nt, grp * cs), v1 = min(nt, v0 + cs);
+        for (int q = 0; q < NS; ++q) {
+          const int j = min(w + q * kAggWaves, m - 1);
+          const float *col = A.vars + (int64_t)j * A.n;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const int u = R == 1 ? t % U : t + q * NT;
-        const bool worker = R == 1 ? t < G * U : u < U;
-        if (!worker) continue;
-        // every unit sums products: Σd_j d_k, and Σd_j as d_j times a row of
-        // ones (d·1 is d exactly and its product error 0, so the sum is the
-        // one of d itself; only a d of ±inf, |x - x_site| beyond the float
-        // range, would give NaN instead of ±inf), so the lanes of a wave
-        // take one path
-        const float *dj, *dk;
-        if (u < m) {
-          dj = dv + u * ld;
-          dk = ones;
-        } else {
-          const int p = u - m;
-          dj = dv + A.pairs.j[p] * ld;
-          dk = dv + A.pairs.k[p] * ld;
+          for (int i = 0; i < 4; ++i) xs[q][i] = col[vv[i]];
         }
-        int v = v0;
-        for (; v + 4 <= v1; v += 4) {
-          const float4 a = *reinterpret_cast<const float4 *>(dj + v);
-          const float4 b = *reinterpret_cast<const float4 *>(dk + v);
-          const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+          const int j = w + q * kAggWaves;
+          if (j >= m) continue;  // uniform over the wave
+          const float kj = K[j];
+          float x[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = ok[i] ? xs[q][i] : kj;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float pr = av[i] * bv[i];
-            const float pe = __builtin_fmaf(av[i], bv[i], -pr);  // exact error of the product
-            acc(hi[q], lo[q], pr, pe);
+            if constexpr (MODE != kDiag) dv[j * ld + sub + i * kWave + lane] = x[i];
+            if constexpr (MODE == kDiag) {  // a lane without a voxel adds zeros
+              const double d = (double)(x[i] - kj);
+              d1[q] += d;
+              d2[q] = __builtin_fma(d, d, d2[q]);
+            }
+            if (ok[i]) {
+              const uint32_t kk = f2key(x[i]);
+              kmn[q] = min(kmn[q], kk);
+              kmx[q] = max(kmx[q], kk);
+            }
+          }
+          if (B > 0) {
+            const float *e = edg + j * (B + 1);
+            const float e0 = e[0], sc = scl[j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (ok[i]) hist_count(hist_l + j * B, hist_bin(x[i], e, B, e0, sc), lane);
           }
         }
-        for (; v < v1; ++v) {
-          const float a0 = dj[v], b0 = dk[v];
-          const float pr = a0 * b0;
-          const float pe = __builtin_fmaf(a0, b0, -pr);
-          acc(hi[q], lo[q], pr, pe);
+      }
+      if constexpr (MODE != kDiag) {
+        __syncthreads();
+        // the stage holds whole multiples of 256 voxels, the site's value past nt
+        for (int c = w * 16 * G; c < nt; c += kAggWaves * 16 * G) {
+          const int at = c + (lane % 16) / gr * 16 + lane / 16 * 4;
+          const float4 a = *reinterpret_cast<const float4 *>(dv + row0 * ld + at);
+          float4 b = a;
+          if constexpr (MODE != k16) b = *reinterpret_cast<const float4 *>(dv + row1 * ld + at);
+          C.add((double)(a.x - K0), (double)(b.x - K1));
+          C.add((double)(a.y - K0), (double)(b.y - K1));
+          C.add((double)(a.z - K0), (double)(b.z - K1));
+          C.add((double)(a.w - K0), (double)(b.w - K1));
         }
-      }
-      __syncthreads();
-    }
-    // combine the lane groups in group order
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int u = R == 1 ? t % U : t + q * NT;
-      const bool worker = R == 1 ? t < G * U : u < U;
-      if (worker) {
-        ph[grp * U + u] = hi[q];
-        pl[grp * U + u] = lo[q];
+        __syncthreads();
       }
     }
+    double *out = A.part + (int64_t)item * A.U;
+    if constexpr (MODE != kDiag)
+      put_sums<MODE>(C, A, red, t, kAggThreads, w, kAggWaves, out, [] { __syncthreads(); });
     __syncthreads();
-    for (int u = t; u < U; u += NT) {
-      float H = 0.0f, Lo = 0.0f;
-      for (int gg = 0; gg < G; ++gg) {
-        acc(H, Lo, ph[gg * U + u], 0.0f);
-        Lo += pl[gg * U + u];
-      }
-      A.part_hi[(int64_t)item * U + u] = H;
-      A.part_lo[(int64_t)item * U + u] = Lo;
-    }
     // flush exact integer/compare statistics
     if (A.hist) {
       uint32_t *dst = A.hist + (int64_t)s * m * B;
-      for (int i = t; i < m * B; i += NT)
+      for (int i = t; i < m * B; i += kAggThreads)
         if (hist_l[i]) atomicAdd(&dst[i], hist_l[i]);
     }
-    if (t < m) {
-      if (kmin_l[t] != 0xFFFFFFFFu) atomicMin(&A.kmin[(int64_t)s * m + t], kmin_l[t]);
-      if (kmax_l[t] != 0u) atomicMax(&A.kmax[(int64_t)s * m + t], kmax_l[t]);
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      const int j = w + q * kAggWaves;
+      if (j >= m) continue;
+      const uint32_t mn = wave_min_u32(kmn[q]), mx = wave_max_u32(kmx[q]);
+      if constexpr (MODE == kDiag) {
+        d1[q] = wave_sum(d1[q]);
+        d2[q] = wave_sum(d2[q]);
+      }
+      if (lane == 0) {
+        atomicMin(&A.kmin[(int64_t)s * m + j], mn);
+        atomicMax(&A.kmax[(int64_t)s * m + j], mx);
+        if constexpr (MODE == kDiag) {
+          out[j] = d1[q];
+          out[m + j] = d2[q];
+        }
+      }
     }
     __syncthreads();
   }
 }
 
 // The same sums for cells of at most kSmallCell voxels, one wave per cell:
-// each wave has its own LDS region and synchronises only with itself.
+// each wave has its own LDS region and synchronises only with itself.  A cell
+// of at most 16 (32) voxels takes four (two) variables at a time, its voxels
+// over 16 (32) lanes.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-__host__ __device__ inline size_t wave_region_words(int m, int B, int U, int G) {
-  return (size_t)m * (kSmallCell + 1) + (size_t)m * B + 3 * (size_t)m + 2 * (size_t)G * U;
+constexpr int kWaveLd = kWave + 4;  // floats between the rows of a wave's stage
+
+// Bytes of a wave's stage ([m][kWaveLd] floats, then 256 doubles of put_sums; none for squares alone) and of its region.
+__host__ __device__ inline size_t wave_stage_bytes(int mode, int m) {
+  const size_t v = sizeof(float) * (size_t)m * kWaveLd;
+  return mode == kDiag ? 0 : v > 2048 ? v : 2048;
+}
+__host__ __device__ inline size_t wave_region_bytes(int mode, int m, int B) {
+  // stage, m sums and squares, histogram, extrema, site values
+  return (wave_stage_bytes(mode, m) + sizeof(double) * 2 * m + sizeof(uint32_t) * ((size_t)m * B + 3 * (size_t)m) + 15) & ~size_t(15);
 }
 
-template <int R>
+template <int MODE>
 __global__ __launch_bounds__(kAggThreads) void k_agg_cell_wave(CellArgs A) {
   extern __shared__ uint8_t smem[];
-  constexpr int kWaves = kAggThreads / kWave;
-  constexpr int VPT = kSmallCell / kWave;
-  const int m = A.m, B = A.B, U = A.U, G = A.G, ld = kSmallCell + 1;
-  const int wid = threadIdx.x / kWave, lane = lane_id();
+  const int m = A.m, B = A.B;
+  const int lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   float *edg = reinterpret_cast<float *>(smem);  // [m][B+1], shared by the waves
-  float *ones = edg + m * (B + 1);               // [kSmallCell + 1] 1.0, shared: the second factor of Σd
-  float *dv = ones + (kSmallCell + 1) + (size_t)wid * wave_region_words(m, B, U, G);
-  uint32_t *hist_l = reinterpret_cast<uint32_t *>(dv + m * ld);  // [m*B]
+  const size_t head = (sizeof(float) * m * (B + 1) + 15) & ~size_t(15);
+  uint8_t *own = smem + head + w * wave_region_bytes(MODE, m, B);
+  float *dv = reinterpret_cast<float *>(own);
+  double *red = reinterpret_cast<double *>(own);
+  double *sum = reinterpret_cast<double *>(own + wave_stage_bytes(MODE, m));  // [2m] (kDiag)
+  uint32_t *hist_l = reinterpret_cast<uint32_t *>(sum + 2 * m);               // [m*B]
   uint32_t *kmin_l = hist_l + m * B;
   uint32_t *kmax_l = kmin_l + m;
   float *K = reinterpret_cast<float *>(kmax_l + m);
-  float *ph = K + m;
-  float *pl = ph + G * U;
-  const int grp = R == 1 ? lane / U : 0;
+  const int gr = group_rows(MODE, m), G = 16 / gr;
+  const int row0 = min(lane % gr, m - 1);
+  const int row1 = min(16 + (MODE == k20 ? lane % 4 : lane % 16), m - 1);
   if (B > 0)
     for (int i = threadIdx.x; i < m * (B + 1); i += kAggThreads) edg[i] = A.edges[i];
-  for (int i = threadIdx.x; i < kSmallCell + 1; i += kAggThreads) ones[i] = 1.0f;
   __syncthreads();
   const uint32_t n_list = *A.list_cnt;
-  for (uint32_t k = blockIdx.x * kWaves + wid; k < n_list; k += gridDim.x * kWaves) {
+  for (uint32_t k = blockIdx.x * kAggWaves + w; k < n_list; k += gridDim.x * kAggWaves) {
     const uint32_t item = A.list[k];
     const uint32_t r = A.item_rank[item];
     const uint32_t s = A.order[r];
     const uint32_t start = A.cell_off[r];
     const int nt = (int)(A.cell_off[r + 1] - start);
+    const int L = nt <= 16 ? 16 : nt <= 32 ? 32 : kWave;  // lanes of a variable
     for (int i = lane; i < m * B; i += kWave) hist_l[i] = 0;
-    for (int j = lane; j < m; j += kWave) K[j] = A.vars[(int64_t)j * A.n + A.sites[s]];
-    wave_sync();
-    uint32_t vv[VPT];
-    bool ok[VPT];
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      const int q = lane + i * kWave;
-      ok[i] = q < nt;
-      vv[i] = ok[i] ? A.perm[start + q] : 0u;
+    for (int j = lane; j < m; j += kWave) {
+      K[j] = A.vars[(int64_t)j * A.n + A.sites[s]];
+      kmin_l[j] = 0xFFFFFFFFu;
+      kmax_l[j] = 0u;
+      if constexpr (MODE == kDiag) sum[j] = sum[m + j] = 0.0;
     }
-#pragma unroll 2
-    for (int j = 0; j < m; ++j) {
-      const float kj = K[j];
-      const float *col = A.vars + (int64_t)j * A.n;
-      float x[VPT];
-#pragma unroll
-      for (int i = 0; i < VPT; ++i) x[i] = ok[i] ? col[vv[i]] : 0.0f;
-      uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
-#pragma unroll
-      for (int i = 0; i < VPT; ++i) {
-        if (!ok[i]) continue;
-        dv[j * ld + lane + i * kWave] = x[i] - kj;
-        const uint32_t kk = f2key(x[i]);
-        kmn = min(kmn, kk);
-        kmx = max(kmx, kk);
-      }
-      kmn = wave_min_u32(kmn);
-      kmx = wave_max_u32(kmx);
-      if (lane == 0) {
-        kmin_l[j] = kmn;
-        kmax_l[j] = kmx;
-      }
-      if (B > 0) {
-        const float *e = edg + j * (B + 1);
-        const float e0 = e[0], sc = (float)B / (e[B] - e0);
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          if (i * kWave >= nt) break;
-          if (ok[i]) atomicAdd(&hist_l[j * B + hist_bin(x[i], e, B, e0, sc)], 1u);
+    wave_sync();
+    const float K0 = K[row0], K1 = K[row1];
+    CellSums<MODE> C;
+    C.zero();
+    for (int base = 0; base < nt; base += L) {
+      const int v = lane & (L - 1);
+      const bool in = base + v < nt;
+      const uint32_t vv = in ? A.perm[start + base + v] : 0u;
+      for (int j0 = 0; j0 < m; j0 += kWave / L) {
+        const int j = j0 + lane / L;
+        const bool ok = in && j < m;
+        const float kj = K[min(j, m - 1)];
+        const float x = ok ? A.vars[(int64_t)j * A.n + vv] : kj;
+        const uint32_t kk = f2key(x);
+        uint32_t mn = ok ? kk : 0xFFFFFFFFu, mx = ok ? kk : 0u;
+        double a = 0.0, b = 0.0;
+        if constexpr (MODE == kDiag) {
+          a = (double)(x - kj);
+          b = a * a;
+        }
+        for (int o = 1; o < L; o <<= 1) {
+          mn = min(mn, (uint32_t)__shfl_xor(mn, o, kWave));
+          mx = max(mx, (uint32_t)__shfl_xor(mx, o, kWave));
+          if constexpr (MODE == kDiag) {
+            a += __shfl_xor(a, o, kWave);
+            b += __shfl_xor(b, o, kWave);
+          }
+        }
+        if (v == 0 && j < m) {
+          kmin_l[j] = min(kmin_l[j], mn);
+          kmax_l[j] = max(kmax_l[j], mx);
+          if constexpr (MODE == kDiag) {
+            sum[j] += a;
+            sum[m + j] += b;
+          }
+        }
+        if constexpr (MODE != kDiag)
+          if (j < m) dv[j * kWaveLd + v] = x;
+        if (B > 0 && ok) {
+          const float *e = edg + j * (B + 1);
+          atomicAdd(&hist_l[j * B + hist_bin(x, e, B, e[0], (float)B / (e[B] - e[0]))], 1u);
         }
       }
-    }
-    wave_sync();
-    float hi[R], lo[R];
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      hi[q] = lo[q] = 0.0f;
-      const int u = R == 1 ? lane % U : lane + q * kWave;
-      const bool worker = R == 1 ? lane < G * U : u < U;
-      if (!worker) continue;
-      // Σd_j as d_j times ones through the product path (see k_agg_cell)
-      const float *dj, *dk;
-      if (u < m) {
-        dj = dv + u * ld;
-        dk = ones;
-      } else {
-        const int p = u - m;
-        dj = dv + A.pairs.j[p] * ld;
-        dk = dv + A.pairs.k[p] * ld;
-      }
-      for (int v = grp; v < nt; v += G) {
-        const float a = dj[v], b = dk[v];
-        const float pr = a * b;
-        const float pe = __builtin_fmaf(a, b, -pr);
-        acc(hi[q], lo[q], pr, pe);
+      wave_sync();
+      if constexpr (MODE != kDiag) {
+        const int left = min(L, nt - base);
+        for (int c = 0; c < left; c += 4 * G) {
+          const int at = c + (lane % 16) / gr * 4 + lane / 16;
+          const float a = dv[row0 * kWaveLd + at];
+          float b = a;
+          if constexpr (MODE != k16) b = dv[row1 * kWaveLd + at];
+          C.add((double)(a - K0), (double)(b - K1));
+        }
+        wave_sync();
       }
     }
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int u = R == 1 ? lane % U : lane + q * kWave;
-      const bool worker = R == 1 ? lane < G * U : u < U;
-      if (worker) {
-        ph[grp * U + u] = hi[q];
-        pl[grp * U + u] = lo[q];
-      }
-    }
-    wave_sync();
-    for (int u = lane; u < U; u += kWave) {
-      float H = 0.0f, Lo = 0.0f;
-      for (int gg = 0; gg < G; ++gg) {
-        acc(H, Lo, ph[gg * U + u], 0.0f);
-        Lo += pl[gg * U + u];
-      }
-      A.part_hi[(int64_t)item * U + u] = H;
-      A.part_lo[(int64_t)item * U + u] = Lo;
-    }
+    double *out = A.part + (int64_t)item * A.U;
+    if constexpr (MODE != kDiag)
+      put_sums<MODE>(C, A, red, lane, kWave, 0, 1, out, [] { wave_sync(); });
+    else
+      for (int u = lane; u < 2 * m; u += kWave) out[u] = sum[u];
+    // the cell's only item: plain stores
     if (A.hist) {
       uint32_t *dst = A.hist + (int64_t)s * m * B;
       for (int i = lane; i < m * B; i += kWave)
-        if (hist_l[i]) atomicAdd(&dst[i], hist_l[i]);
+        if (hist_l[i]) dst[i] = hist_l[i];
     }
     for (int j = lane; j < m; j += kWave) {
-      if (kmin_l[j] != 0xFFFFFFFFu) atomicMin(&A.kmin[(int64_t)s * m + j], kmin_l[j]);
-      if (kmax_l[j] != 0u) atomicMax(&A.kmax[(int64_t)s * m + j], kmax_l[j]);
+      A.kmin[(int64_t)s * m + j] = kmin_l[j];
+      A.kmax[(int64_t)s * m + j] = kmax_l[j];
     }
     wave_sync();
   }
 }
 
-// 4. per-cell finalize: combine item partials (item order), form the float32
-// statistics and the float64 merge inputs.
+// Runs of kFold item partials of a cell with more than kFold items, added into
+// the run's first row: a cell of most of the volume has thousands.
+__global__ __launch_bounds__(kAggThreads) void k_agg_fold(CellArgs A) {
+  const uint32_t n_list = *A.list_cnt;
+  for (uint32_t k = blockIdx.x; k < n_list; k += gridDim.x) {
+    const uint32_t item = A.list[k];
+    const uint32_t r = A.item_rank[item];
+    const uint32_t i0 = A.item_off[r], i1 = A.item_off[r + 1];
+    if (i1 - i0 <= (uint32_t)kFold || (item - i0) % kFold) continue;
+    const uint32_t hi = min(i1, item + kFold);
+    for (int u = threadIdx.x; u < A.U; u += kAggThreads) {
+      double v = A.part[(int64_t)item * A.U + u];
+#pragma unroll 8
+      for (uint32_t i = item + 1; i < hi; ++i) v += A.part[(int64_t)i * A.U + u];
+      A.part[(int64_t)item * A.U + u] = v;
+    }
+  }
+}
+
+// 4. per-cell finalize, one wave per cell: combine the item partials in item
+// order, form the float32 statistics and the float64 merge inputs, and add
+// the exact ones to the cell's component.
 struct FinArgs {
   uint32_t S;
   int m, U, P;  // P = number of pair units (all pairs, or the diagonal only)
@@ -494,7 +606,7 @@ struct FinArgs {
   const unsigned long long *cnt;
   const uint32_t *rank;      // site -> cell rank
   const uint32_t *item_off;  // by rank
-  const float *part_hi, *part_lo;
+  const double *part;
   const uint32_t *kmin, *kmax;
   // outputs
   uint64_t *out_n;
@@ -513,47 +625,41 @@ struct FinArgs {
 
 __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
   extern __shared__ uint8_t smem[];
-  float *th = reinterpret_cast<float *>(smem);  // [U]
-  float *tl = th + A.U;                         // [U]
-  float *K = tl + A.U;                          // [m]
-  const int t = threadIdx.x;
-  const int m = A.m;
-  for (uint32_t s = blockIdx.x; s < A.S; s += gridDim.x) {
+  const int m = A.m, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  double *th = reinterpret_cast<double *>(smem) + (size_t)w * A.U;  // [U] of this wave's cell
+  for (uint32_t s = blockIdx.x * kAggWaves + w; s < A.S; s += gridDim.x * kAggWaves) {
     const uint64_t n = A.cnt[s];
     const uint32_t i0 = A.item_off[A.rank[s]], i1 = A.item_off[A.rank[s] + 1];
-    for (int u = t; u < A.U; u += kAggThreads) {
-      float H = 0.0f, Lo = 0.0f;
-      for (uint32_t it = i0; it < i1; ++it) {
-        acc(H, Lo, A.part_hi[(int64_t)it * A.U + u], 0.0f);
-        Lo += A.part_lo[(int64_t)it * A.U + u];
-      }
-      th[u] = H;
-      tl[u] = Lo;
+    const uint32_t step = i1 - i0 > (uint32_t)kFold ? kFold : 1;
+    for (int u = lane; u < A.U; u += kWave) {
+      double v = 0.0;
+#pragma unroll 8
+      for (uint32_t it = i0; it < i1; it += step) v += A.part[(int64_t)it * A.U + u];
+      // an infinite value among the cell's leaves no mean
+      th[u] = v + (v - v);
     }
-    if (t < m) K[t] = n ? A.vars[(int64_t)t * A.n + A.sites[s]] : 0.0f;
-    __syncthreads();
-    if (t == 0) A.out_n[s] = n;
+    wave_sync();
+    if (lane == 0) A.out_n[s] = n;
     const uint32_t c = A.site_comp[s];
     if (n && c < A.n_comp) {
-      if (t == 0) atomicAdd(&A.cnt_c[c], (unsigned long long)n);
-      for (int j = t; j < m; j += kAggThreads) {
+      if (lane == 0) atomicAdd(&A.cnt_c[c], (unsigned long long)n);
+      for (int j = lane; j < m; j += kWave) {
         atomicMin(&A.kmin_c[(int64_t)c * m + j], A.kmin[(int64_t)s * m + j]);
         atomicMax(&A.kmax_c[(int64_t)c * m + j], A.kmax[(int64_t)s * m + j]);
       }
       if (A.hist)
-        for (int i = t; i < m * A.B; i += kAggThreads) {
+        for (int i = lane; i < m * A.B; i += kWave) {
           uint32_t h = A.hist[(int64_t)s * m * A.B + i];
           if (h) atomicAdd(&A.hist_c[(int64_t)c * m * A.B + i], h);
         }
     }
     const double dn = (double)n;
-    for (int j = t; j < m; j += kAggThreads) {
+    for (int j = lane; j < m; j += kWave) {
       float mean = 0.0f;
       double mean64 = 0.0;
       if (n) {
-        // the compensated pair (th, tl) is exact in float64; the float32
-        // output is the float64 result rounded once
-        mean64 = (double)K[j] + ((double)th[j] + (double)tl[j]) / dn;
+        mean64 = (double)A.vars[(int64_t)j * A.n + A.sites[s]] + th[j] / dn;
         mean = (float)mean64;
       }
       A.mean32[(int64_t)s * m + j] = mean;
@@ -561,17 +667,14 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
       A.vmin[(int64_t)s * m + j] = n ? key2f(A.kmin[(int64_t)s * m + j]) : __builtin_inff();
       A.vmax[(int64_t)s * m + j] = n ? key2f(A.kmax[(int64_t)s * m + j]) : -__builtin_inff();
     }
-    for (int p = t; p < A.P; p += kAggThreads) {
+    for (int p = lane; p < A.P; p += kWave) {
       const int j = A.pairs.j[p], k = A.pairs.k[p];
       float c32 = 0.0f;
       double c64 = 0.0;
       if (n) {
         // C = S_jk - S_j S_k / n cancels when the site's value is far from the
-        // cell mean, so it is formed in float64 from the exact pairs and the
-        // float32 output is that result rounded once
-        const int uq = m + p;
-        double dj = (double)th[j] + (double)tl[j], dk = (double)th[k] + (double)tl[k];
-        c64 = ((double)th[uq] + (double)tl[uq]) - dj * dk / dn;
+        // cell mean, so it is formed in float64 and rounded once
+        c64 = th[m + p] - th[j] * th[k] / dn;
         if (j == k && c64 < 0.0) c64 = 0.0;
         c32 = (float)c64;
       }
@@ -579,15 +682,17 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
       if (j == k) A.m2_32[(int64_t)s * m + j] = c32;
       if (A.with_cov) A.cov32[(int64_t)s * A.P + p] = c32;
     }
-    __syncthreads();
+    wave_sync();
   }
 }
 
-// 5a. exact band statistics from the components: one workgroup per run of 256
-// components in band order; each lane owns columns (count, minima, maxima,
-// histogram bins) and flushes one atomic per column whenever the band changes.
+// 5a. exact band statistics from the components: one workgroup per run of at
+// most 256 components in band order; each lane owns columns (count, minima,
+// maxima, histogram bins) and flushes one atomic per column whenever the band
+// changes.  Runs are short enough for about 2048 workgroups: a lane walks its
+// run one load after another, which is what the time goes to.
 struct BandIntArgs {
-  uint32_t n_comp;
+  uint32_t n_comp, run;
   int m, B;
   const uint32_t *order;  // components sorted by band
   const uint8_t *comp_band;
@@ -600,8 +705,8 @@ struct BandIntArgs {
 __global__ __launch_bounds__(256) void k_band_int(BandIntArgs A) {
   const int m = A.m, B = A.B;
   const int64_t cols = 1 + 2 * (int64_t)m + (int64_t)m * B;
-  const uint32_t q0 = blockIdx.x * 256u;
-  const uint32_t q1 = q0 + 256u < A.n_comp ? q0 + 256u : A.n_comp;
+  const uint32_t q0 = blockIdx.x * A.run;
+  const uint32_t q1 = q0 + A.run < A.n_comp ? q0 + A.run : A.n_comp;
   const int nq = (int)(q1 - q0);
   // the run's components and their bands, staged once (the order -> band
   // chain of loads would otherwise repeat for every column)
@@ -809,7 +914,7 @@ struct AggWork {
   uint32_t *perm;  // [N]
   unsigned long long *cnt_c, *cnt_b;
   uint32_t *items, *item_off;
-  float *part_hi, *part_lo;
+  double *part;
   uint32_t *kmin, *kmax, *kmin_c, *kmax_c, *kmin_b, *kmax_b;
   double *mean64, *c64, *mean64_c, *c64_c, *m2tmp_c, *mean64_b, *c64_b, *m2tmp_b;
   uint32_t *key_b, *val_b, *pos, *corder, *bucket;
@@ -832,8 +937,7 @@ void agg_layout(A &a, const Geom &g, uint32_t S, uint32_t n_comp, int32_t n_band
   auto cnt_b = a.template take<unsigned long long>(b1);
   auto items = a.template take<uint32_t>(s1);
   auto ioff = a.template take<uint32_t>(s1 + 1);
-  auto ph = a.template take<float>(ic * U);
-  auto pl = a.template take<float>(ic * U);
+  auto part = a.template take<double>(ic * U);
   auto kmin = a.template take<uint32_t>(s1 * m);
   auto kmax = a.template take<uint32_t>(s1 * m);
   auto kminc = a.template take<uint32_t>(c1 * m);
@@ -864,8 +968,7 @@ void agg_layout(A &a, const Geom &g, uint32_t S, uint32_t n_comp, int32_t n_band
     W->cnt_b = cnt_b;
     W->items = items;
     W->item_off = ioff;
-    W->part_hi = ph;
-    W->part_lo = pl;
+    W->part = part;
     W->kmin = kmin;
     W->kmax = kmax;
     W->kmin_c = kminc;
@@ -901,6 +1004,17 @@ struct SizerT : Sizer {
     return nullptr;
   }
 };
+
+// Variables and bins that the call takes: those whose histograms, edges and
+// stage of one value per unit group fit in 64 KiB.
+bool hist_fits(int m, int B, int U) {
+  int G = 1, NT = kAggThreads;
+  if (U <= kAggThreads) {
+    G = 2 * U <= kAggThreads ? kAggThreads / U : 2;
+    NT = std::max(kAggThreads, (G * U + kWave - 1) / kWave * kWave);
+  }
+  return sizeof(float) * (2 * (size_t)m * B + 5 * (size_t)m + 2 * (size_t)G * U + (size_t)(m + 1) * (NT + 4)) <= 65536;
+}
 
 void units_for(int m, bool cov, int &P, int &U, Pairs &pairs) {
   P = 0;
@@ -1021,6 +1135,7 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
 
   // 3. per-item sums: cells of at most kSmallCell voxels one wave each, larger cells one workgroup per item
   if (n_items) {
+    if (!hist_fits(m, B, U)) return LSRVT_EINVAL;
     CellArgs A;
     A.perm = W.perm;
     A.cell_off = W.lay.cell_off;
@@ -1032,21 +1147,19 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     A.m = m;
     A.B = B;
     A.U = U;
-    A.P = P;
     A.pairs = pairs;
     A.item_off = W.item_off;
     A.item_rank = W.item_rank;
-    A.part_hi = W.part_hi;
-    A.part_lo = W.part_lo;
+    A.part = W.part;
     A.hist = want_hist ? cs.hist : nullptr;
     A.kmin = W.kmin;
     A.kmax = W.kmax;
-    // wave path: U units over 64 lanes, LDS for four waves
-    const int Rw = (U + kWave - 1) / kWave;
-    const int Gw = Rw == 1 ? kWave / U : 1;
-    const size_t lds_w =
-        sizeof(float) * ((size_t)m * (B + 1) + kSmallCell + 1 + (kAggThreads / kWave) * wave_region_words(m, B, U, Gw));
-    const bool small_ok = Rw <= 3 && lds_w <= 65536;
+    A.stage = 0;
+    A.tile = 0;
+    const int mode = !want_cov ? kDiag : m <= 16 ? k16 : m <= 20 ? k20 : k32;
+    // wave path, while four waves' regions fit in LDS
+    const size_t lds_w = ((sizeof(float) * m * (B + 1) + 15) & ~size_t(15)) + kAggWaves * wave_region_bytes(mode, m, B);
+    const bool small_ok = lds_w <= 65536;
     if ((rc = fill<uint32_t>(W.big_cnt + 1, 2, 0u, s))) return rc;
     uint32_t *counts = W.big_cnt + 1;
     hipLaunchKernelGGL(k_item_cells, dim3((S + 255) / 256), dim3(256), 0, s, W.item_off, W.lay.cnt_rank, S,
@@ -1055,59 +1168,43 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     if (small_ok) {
       A.list = W.small_list;
       A.list_cnt = counts;
-      A.G = Gw;
-      A.tile = kSmallCell;
       const unsigned grid = (unsigned)std::min<uint64_t>(65535, (n_items + 3) / 4);
-      if (Rw == 1)
-        hipLaunchKernelGGL(k_agg_cell_wave<1>, dim3(grid), dim3(kAggThreads), lds_w, s, A);
-      else if (Rw == 2)
-        hipLaunchKernelGGL(k_agg_cell_wave<2>, dim3(grid), dim3(kAggThreads), lds_w, s, A);
-      else
-        hipLaunchKernelGGL(k_agg_cell_wave<3>, dim3(grid), dim3(kAggThreads), lds_w, s, A);
+      auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(kAggThreads), lds_w, s, A); };
+      mode == kDiag ? launch(k_agg_cell_wave<kDiag>)
+      : mode == k16 ? launch(k_agg_cell_wave<k16>)
+      : mode == k20 ? launch(k_agg_cell_wave<k20>)
+                    : launch(k_agg_cell_wave<k32>);
       LSRVT_LAUNCHED();
     }
     A.list = W.big_list;
     A.list_cnt = counts + 1;
-    const int R = (U + kAggThreads - 1) / kAggThreads;
-    // lane groups: 256 / U of them in 256 threads while units fill at most
-    // half the workgroup, else two groups in up to 512 threads (all lanes but
-    // the rounding to whole waves work)
-    int NT = kAggThreads;
-    if (R == 1) {
-      A.G = 2 * U <= kAggThreads ? kAggThreads / U : 2;
-      NT = std::max(kAggThreads, (A.G * U + kWave - 1) / kWave * kWave);
-    } else {
-      A.G = 1;
-    }
-    // the largest staging round (NT, 2 NT or 4 NT voxels) that keeps the
-    // workgroup within 40 KiB of LDS, so four workgroups share a CU
-    const size_t fixed = sizeof(float) * ((size_t)m * B + 3 * m + 2 * (size_t)A.G * U + (size_t)m * (B + 1) + m);
-    size_t lds = 0;
-    int vpt = kMaxVPT;
-    for (; vpt >= 1; vpt /= 2) {
-      A.tile = vpt * NT;
-      lds = fixed + sizeof(float) * (size_t)(m + 1) * (A.tile + 4);
-      if (lds <= 40960 || vpt == 1) break;
-    }
-    const int32_t tv = tuning(LSRVT_TUNE_STATS_TILE);  // a tuned round size, if it fits in 64 KiB
-    if (tv) {
-      const size_t l2 = fixed + sizeof(float) * (size_t)(m + 1) * ((size_t)tv * NT + 4);
-      if (l2 <= 65536) {
-        vpt = tv;
-        A.tile = vpt * NT;
-        lds = l2;
-      }
-    }
-    if (lds > 65536 || R > 3 || NT > kAggMaxThreads) return LSRVT_EINVAL;
+    // a staging round of 256 voxels, or the tuned multiple of it if that fits in 64 KiB
+    const size_t fixed = sizeof(float) * ((size_t)m * B + (size_t)m * (B + 1) + 2 * m);
+    auto stage = [&](int tile) {
+      return mode == kDiag ? (size_t)0 : std::max<size_t>(2048, sizeof(float) * (size_t)m * (tile + 4));
+    };
+    A.tile = kAggThreads;
+    const int32_t tv = tuning(LSRVT_TUNE_STATS_TILE);
+    if (tv && fixed + stage(tv * kAggThreads) <= 65536) A.tile = tv * kAggThreads;
+    A.stage = (uint32_t)stage(A.tile);
+    const size_t lds = fixed + A.stage;  // within 64 KiB: less than hist_fits asks for
     const unsigned grid = n_items < 16384 ? n_items : 16384;
-    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, s, A); };
-    if (R == 1)
-      vpt == 4 ? launch(k_agg_cell<1, 4>) : vpt == 2 ? launch(k_agg_cell<1, 2>) : launch(k_agg_cell<1, 1>);
-    else if (R == 2)
-      vpt == 4 ? launch(k_agg_cell<2, 4>) : vpt == 2 ? launch(k_agg_cell<2, 2>) : launch(k_agg_cell<2, 1>);
+    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(kAggThreads), lds, s, A); };
+    const int ns = (m + kAggWaves - 1) / kAggWaves;  // variables of a wave
+    if (mode == kDiag)
+      ns == 1 ? launch(k_agg_cell<kDiag, 1>) : ns == 2 ? launch(k_agg_cell<kDiag, 2>)
+      : ns <= 5 ? launch(k_agg_cell<kDiag, 5>) : launch(k_agg_cell<kDiag, 8>);
+    else if (mode == k16)
+      ns == 1 ? launch(k_agg_cell<k16, 1>) : ns == 2 ? launch(k_agg_cell<k16, 2>) : launch(k_agg_cell<k16, 4>);
+    else if (mode == k20)
+      launch(k_agg_cell<k20, 5>);
     else
-      vpt == 4 ? launch(k_agg_cell<3, 4>) : vpt == 2 ? launch(k_agg_cell<3, 2>) : launch(k_agg_cell<3, 1>);
+      launch(k_agg_cell<k32, 8>);
     LSRVT_LAUNCHED();
+    if (n_items > (uint32_t)kFold) {
+      hipLaunchKernelGGL(k_agg_fold, dim3(std::min<uint32_t>(grid, 4096)), dim3(kAggThreads), 0, s, A);
+      LSRVT_LAUNCHED();
+    }
   }
 
   // 4. per-cell finalize, plus exact merges of counts, extrema and histograms into components
@@ -1124,8 +1221,7 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     F.cnt = W.lay.cnt;
     F.rank = W.lay.rank;
     F.item_off = W.item_off;
-    F.part_hi = W.part_hi;
-    F.part_lo = W.part_lo;
+    F.part = W.part;
     F.kmin = W.kmin;
     F.kmax = W.kmax;
     F.out_n = cs.n;
@@ -1145,8 +1241,9 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     F.kmin_c = W.kmin_c;
     F.kmax_c = W.kmax_c;
     F.hist_c = want_hist ? comp->hist : nullptr;
-    size_t lds = sizeof(float) * (2 * (size_t)U + m);
-    hipLaunchKernelGGL(k_agg_finalize, dim3(S < 16384 ? S : 16384), dim3(kAggThreads), lds, s, F);
+    const size_t lds = sizeof(double) * (size_t)U * kAggWaves;
+    const unsigned grid = std::min<uint32_t>((S + kAggWaves - 1) / kAggWaves, 16384);
+    hipLaunchKernelGGL(k_agg_finalize, dim3(grid), dim3(kAggThreads), lds, s, F);
     LSRVT_LAUNCHED();
   }
 
@@ -1160,6 +1257,7 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     LSRVT_LAUNCHED();
     BandIntArgs BI;
     BI.n_comp = C;
+    BI.run = std::min<uint32_t>(256, std::max<uint32_t>(8, C / 2048));
     BI.m = m;
     BI.B = B;
     BI.order = W.val_b;
@@ -1172,7 +1270,7 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     BI.kmin_b = W.kmin_b;
     BI.kmax_b = W.kmax_b;
     BI.hist_b = want_hist ? band->hist : nullptr;
-    hipLaunchKernelGGL(k_band_int, dim3((C + 255) / 256), dim3(256), 0, s, BI);
+    hipLaunchKernelGGL(k_band_int, dim3((C + BI.run - 1) / BI.run), dim3(256), 0, s, BI);
     LSRVT_LAUNCHED();
     hipLaunchKernelGGL(k_decode_minmax, dim3(grid_for((int64_t)C * m, 256, 1 << 30)), dim3(256), 0, s, W.kmin_c,
                        W.kmax_c, W.cnt_c, (int64_t)C, m, comp->vmin, comp->vmax, comp->n);
