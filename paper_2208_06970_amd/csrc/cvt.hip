@@ -107,7 +107,7 @@ __device__ __forceinline__ void mark_brick(const BFSArgs &A, int bx, int by, int
 // too); voxels outside the volume have no edges.  One voxel per lane, so a
 // wave covers four rows of a brick and the band reads are coalesced.  Bands
 // do not change during a Lloyd loop, so this runs once per call.
-__device__ __forceinline__ void d_vt_eq(const uint8_t *__restrict__ band, Geom g, VTGrid bg,
+__global__ __launch_bounds__(kVTThreads) void k_vt_eq(const uint8_t *__restrict__ band, Geom g, VTGrid bg,
                                                       uint32_t *__restrict__ eq) {
   const int64_t slots = bg.nbricks * kRows * BX;
   const int lane = lane_id();
@@ -144,9 +144,55 @@ __device__ __forceinline__ void d_vt_eq(const uint8_t *__restrict__ band, Geom g
     }
   }
 }
-__global__ __launch_bounds__(kVTThreads) void k_vt_eq(const uint8_t *__restrict__ band, Geom g, VTGrid bg,
-                                                      uint32_t *__restrict__ eq) { d_vt_eq(band, g, bg, eq); }
-
+// The same edges for the brick relaxation, one word per line of a brick:
+// words [0, 256) the x lines by row (ly, lz), [256, 512) the y lines (lx, lz),
+// [512, 768) the z lines (lx, ly), the first coordinate fastest.  Bit i, 1 to
+// 15: edge between the line's voxels i - 1 and i; bit 0: edge of voxel 0 across
+// the brick's face; bit 16: that of voxel 15.  One workgroup per brick: thread
+// (lx, ly) reads its z line (16 voxels of x a run), the other two axes are
+// compared from LDS, so each band is read once and the lines a thread sweeps
+// need no transposition in the rounds.
+__device__ __forceinline__ void d_br_masks(const uint8_t *__restrict__ band, Geom g, VTGrid bg,
+                                           uint32_t *__restrict__ eq) {
+  constexpr uint32_t kOut = 256u;  // no band: outside the volume
+  __shared__ uint16_t B[kRows * (BX + 2)];  // by row, padded against bank conflicts
+  const int t = threadIdx.x, lo = t & 15, hi = t >> 4;
+  for (int64_t b = blockIdx.x; b < bg.nbricks; b += gridDim.x) {
+    const int x0 = (int)(b % bg.nbx) * BX, y0 = (int)((b / bg.nbx) % bg.nby) * BY,
+              z0 = (int)(b / ((int64_t)bg.nbx * bg.nby)) * BZ;
+    auto at = [&](int x, int y, int z) -> uint32_t {
+      const bool in = x >= 0 && y >= 0 && z >= 0 && x < g.nx && y < g.ny && z < g.nz;
+      return in ? (uint32_t)band[x + (int64_t)g.nx * (y + (int64_t)g.ny * z)] : kOut;
+    };
+    // the word of the line with voxels v(-1) .. v(16)
+    auto word = [&](auto v) {
+      uint32_t m = 0, last = v(-1);
+#pragma unroll
+      for (int i = 0; i <= BX; ++i) {
+        const uint32_t c = v(i);
+        m |= (uint32_t)(c == last && c != kOut) << i;
+        last = c;
+      }
+      return m;
+    };
+    uint32_t v[BZ + 2];
+#pragma unroll
+    for (int i = 0; i < BZ + 2; ++i) v[i] = at(x0 + lo, y0 + hi, z0 + i - 1);
+    const uint32_t xm = at(x0 - 1, y0 + lo, z0 + hi), xp = at(x0 + BX, y0 + lo, z0 + hi);
+    const uint32_t ym = at(x0 + lo, y0 - 1, z0 + hi), yp = at(x0 + lo, y0 + BY, z0 + hi);
+#pragma unroll
+    for (int i = 0; i < BZ; ++i) B[(hi + BY * i) * (BX + 2) + lo] = (uint16_t)v[i + 1];
+    __syncthreads();
+    uint32_t *dst = eq + (size_t)b * kRows * 3;
+    dst[t] = word([&](int i) -> uint32_t { return i < 0 ? xm : i == BX ? xp : B[t * (BX + 2) + i]; });
+    dst[kRows + t] =
+        word([&](int i) -> uint32_t { return i < 0 ? ym : i == BY ? yp : B[(i + BY * hi) * (BX + 2) + lo]; });
+    dst[2 * kRows + t] = word([&](int i) -> uint32_t { return v[i + 1]; });
+    __syncthreads();
+  }
+}
+__global__ __launch_bounds__(kVTThreads) void k_br_masks(const uint8_t *__restrict__ band, Geom g, VTGrid bg,
+                                                         uint32_t *__restrict__ eq) { d_br_masks(band, g, bg, eq); }
 
 struct BrickPos {
   uint32_t b, row, lx;
@@ -802,7 +848,7 @@ constexpr int kGraphRounds = 8;  // relaxation rounds per captured graph
 struct BRArgs {
   Geom g;
   VTGrid bg;
-  const uint32_t *eq;              // [nbricks][256][3] same-band edge masks (as the level search)
+  const uint32_t *eq;              // [nbricks][3][256] same-band edge words of the bricks' lines (d_br_masks)
   void *key;                       // [nbricks][4096] brick-major keys (narrow or wide), all ones = unreached
   void *xface;                     // [nbricks][2][256] keys of the x = 0 and x = 15 voxels of every row
   uint32_t hop32;                  // narrow keys: one hop (1 << b)
@@ -831,12 +877,19 @@ struct BRKey<unsigned long long> {
   __device__ static unsigned long long add(unsigned long long k, unsigned long long h) {
     return k == inf ? inf : k + h;
   }
+  // the hop over an edge (cut = 0) or none (cut = all ones), and the offer over it
+  __device__ static unsigned long long edge(unsigned long long, unsigned long long cut) { return cut; }
+  __device__ static unsigned long long over(unsigned long long k, unsigned long long h, unsigned long long e) {
+    return add(k, h) | e;
+  }
 };
 template <>
 struct BRKey<uint32_t> {
   static constexpr uint32_t inf = ~0u;
   __device__ static uint32_t hop(const BRArgs &A) { return A.hop32; }
   __device__ static uint32_t add(uint32_t k, uint32_t h) { return __builtin_elementwise_add_sat(k, h); }
+  __device__ static uint32_t edge(uint32_t h, uint32_t cut) { return h | cut; }
+  __device__ static uint32_t over(uint32_t k, uint32_t, uint32_t e) { return __builtin_elementwise_add_sat(k, e); }
 };
 
 // A key of the previous pass as the fused reset sees it at voxel v:
@@ -1030,43 +1083,38 @@ __global__ __launch_bounds__(256) void k_br_list(BRArgs A, int32_t i) {
 __device__ __forceinline__ int br_at(int lx, int row) { return row * kBRRow + lx; }
 
 // One line of 16 voxels at K[base + i * st] relaxed forward and backward
-// along its same-band edges (mask bit i: edge from voxel i to i - 1, bit
-// 16 + i: edge to i + 1).  Returns the bits of the voxels whose key dropped;
-// the line is written back only then.  The calling thread owns the line for
-// the whole stage.  Branch-free: a missing edge turns the offer into all
-// ones (never smaller).  The mask passes through an empty asm statement so
-// that the per-voxel edge tests are made here, from one register, rather
-// than hoisted out of the caller's sweep loop as lane masks (two scalar
-// registers each, 90 for a thread's three lines).
+// along its same-band edges (mask bit i: edge between voxels i - 1 and i).
+// Returns the bits of the voxels whose key dropped; the line is written back
+// only then.  The calling thread owns the line for the whole stage.
+// Branch-free, and one word serves both directions: a missing edge is a hop of
+// all ones, which a narrow key's saturating addition turns into "unreached"
+// (a wide key's offer is set to it), so a step is an addition and a minimum
+// and what dropped is found by comparing once at the end.  The mask passes
+// through an empty asm statement so that the per-voxel edge tests are made
+// here, from one register, rather than hoisted out of the caller's sweep loop.
 template <class KT>
 __device__ __forceinline__ uint32_t br_sweep(KT *K, int base, int st, uint32_t mask, KT hop) {
   using KO = BRKey<KT>;
   uint32_t nm = ~mask;
   asm volatile("" : "+v"(nm));
-  // all ones when bit j of the mask is clear, else zero
-  auto cut = [&](int j) { return (KT)(int64_t)((int32_t)(nm << (31 - j)) >> 31); };
-  KT k[16];
+  KT k[16], old[16], h[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) k[i] = K[base + i * st];
-  // the changed bits are shifted in one at a time (no per-bit constants):
-  // forward voxel i lands at bit 15 - i (reversed below), backward voxel i
-  // at bit i
-  uint32_t cf = 0, cb = 0;
+  for (int i = 0; i < 16; ++i) old[i] = k[i] = K[base + i * st];
+#pragma unroll
+  for (int i = 1; i < 16; ++i) h[i] = KO::edge(hop, (KT)(int64_t)((int32_t)(nm << (31 - i)) >> 31));
 #pragma unroll
   for (int i = 1; i < 16; ++i) {
-    const KT o = KO::add(k[i - 1], hop) | cut(i);
-    const bool lt = o < k[i];
-    k[i] = lt ? o : k[i];
-    cf = cf + cf + (uint32_t)lt;
+    const KT o = KO::over(k[i - 1], hop, h[i]);
+    k[i] = o < k[i] ? o : k[i];
   }
 #pragma unroll
   for (int i = 14; i >= 0; --i) {
-    const KT o = KO::add(k[i + 1], hop) | cut(16 + i);
-    const bool lt = o < k[i];
-    k[i] = lt ? o : k[i];
-    cb = cb + cb + (uint32_t)lt;
+    const KT o = KO::over(k[i + 1], hop, h[i + 1]);
+    k[i] = o < k[i] ? o : k[i];
   }
-  const uint32_t c = (__builtin_bitreverse32(cf) >> 16) | cb;
+  uint32_t c = 0;
+#pragma unroll
+  for (int i = 15; i >= 0; --i) c = c + c + (uint32_t)(k[i] != old[i]);
   if (c) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) K[base + i * st] = k[i];
@@ -1074,25 +1122,62 @@ __device__ __forceinline__ uint32_t br_sweep(KT *K, int base, int st, uint32_t m
   return c;
 }
 
-// One round over the listed bricks.  Thread t owns three lines of the
-// brick for the whole processing: row t along x (ly, lz) = (t & 15, t >> 4),
-// the y line (lx, lz) = (t & 15, t >> 4) and the z line (lx, ly) =
-// (t & 15, t >> 4); their edge masks stay in registers.  LDS holds the
-// keys (rows padded against bank conflicts), a changed bit per voxel and a
-// dirty flag per line.
 // LDS of one brick processing: the keys (rows padded against bank
-// conflicts), the y and z edge masks by row (transposed into line masks),
-// a changed bit per voxel, a dirty flag per line, the face flags.
+// conflicts), by row the voxels whose key changed in this processing and
+// those among them that changed since the row's last x sweep, and the y and z
+// lines to sweep: bit lx of yl[lz] and of zl[ly].
 template <class KT>
 struct BRLds {
   KT K[kRows * kBRRow];
-  uint32_t raw[2][kRows];
-  uint32_t chg[kRows];                      // bit lx of row: the voxel's key changed in this processing
-  uint8_t dx[kRows], dy[kRows], dz[kRows];  // lines to sweep along x (by row), y (lx, lz), z (lx, ly)
-  uint32_t flags[8];
+  uint32_t chg[kRows];
+  uint32_t pend[kRows];
+  uint32_t yl[BZ], zl[BY];
+  uint32_t more;
 };
 
+// The changed voxels of a wave's 64 lines along y (or z), bits c by place on
+// the line; lane l holds line (lx, q) = (l & 15, l >> 4) of the wave's four.
+// Ballot i holds the rows at place i, 16 bits for each q, and lane i takes
+// it: no lane loops over its voxels.  row(i, q) is the row's index, lines[i]
+// the summary of the other axis.
+template <class Row>
+__device__ __forceinline__ void br_spread(uint32_t c, uint32_t *pend, uint32_t *lines, uint32_t *more, uint32_t it,
+                                          Row row) {
+  if (__ballot(c != 0u) == 0ull) return;
+  const int lane = lane_id();
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint64_t bal = __ballot(c >> i & 1u);
+    lo = lane == i ? (uint32_t)bal : lo;
+    hi = lane == i ? (uint32_t)(bal >> 32) : hi;
+  }
+  if (lane < 16) {
+    const uint32_t part[4] = {lo & 0xFFFFu, lo >> 16, hi & 0xFFFFu, hi >> 16};
+    // the rows of this wave's lines are no other wave's in this stage
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (part[q]) pend[row(lane, q)] |= part[q];
+    const uint32_t any = part[0] | part[1] | part[2] | part[3];
+    if (any) atomicOr(&lines[lane], any);
+    if (lane == 0) *more = it;
+  }
+}
+
 // One processing of brick b in round r (all threads of the workgroup).
+// Thread t owns three lines of the brick for the whole processing: row t along
+// x (ly, lz) = (t & 15, t >> 4), the y line (lx, lz) and the z line (lx, ly),
+// the first coordinate t & 15 and the second t >> 4; their edge words stay in
+// registers.
+//
+// Bound by the sweeps' vector operations and, in the rounds of few bricks, by
+// the chain of LDS accesses and barriers between the axes.  Flame loop
+// (1024 x 512 x 512, 30 updates): 110 ms, the rounds 2.6 ms a pass.  142 ms and
+// 3.3 ms with a changed-voxel loop per lane, edge masks transposed from rows
+// per processing, changes counted at every step of a sweep and 2048
+// workgroups a round.  Six waves a SIMD: 48.9 ms for 10 updates, 49.7 with
+// five, 52.2 with seven and 59.7 with eight (spills); 8192 workgroups (48.9)
+// because the bricks' work is uneven: 53.3 with 2048.
 template <class KT>
 __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t r, BRLds<KT> &L) {
   using KO = BRKey<KT>;
@@ -1100,10 +1185,7 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
   const KT hop = KO::hop(A);
   KT *key = static_cast<KT *>(A.key), *xface = static_cast<KT *>(A.xface);
   KT *K = L.K;
-  uint32_t(*raw)[kRows] = L.raw;
   uint32_t *chg = L.chg;
-  uint8_t *dx = L.dx, *dy = L.dy, *dz = L.dz;
-  uint32_t *flags = L.flags;
   // the thread index passes through an empty asm statement so that what is
   // derived from it (LDS and global offsets) is recomputed per processing
   // instead of being kept live across a round's processings
@@ -1118,13 +1200,13 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
     const bool hxm = bx > 0, hxp = bx < A.bg.nbx - 1, hym = by > 0, hyp = by < A.bg.nby - 1, hzm = bz > 0,
                hzp = bz < A.bg.nbz - 1;
     // every global read of the processing, issued together: the brick's keys
-    // (16 per thread, coalesced), its edge masks and the six faces of the
+    // (16 per thread, coalesced), its edge words and the six faces of the
     // neighbours (a missing neighbour reads the brick itself, unused)
     KT kv[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) kv[i] = key[(size_t)b * kB + i * kBRThreads + t];
-    const uint32_t *eq = A.eq + ((size_t)b * kRows + t) * 3;
-    const uint32_t mx = eq[0], e1 = eq[1], e2 = eq[2];
+    const uint32_t *eq = A.eq + (size_t)b * kRows * 3 + t;
+    const uint32_t mx = eq[0], my = eq[kRows], mz = eq[2 * kRows];
     KT fxm = xface[(size_t)(hxm ? b - 1 : b) * 512 + 256 + t];
     KT fxp = xface[(size_t)(hxp ? b + 1 : b) * 512 + t];
     KT fym = key[(size_t)(hym ? b - bsy : b) * kB + lo4 + 16 * 15 + 256 * hi4];
@@ -1153,109 +1235,102 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
       const int loc = i * kBRThreads + t;
       K[br_at(loc & 15, loc >> 4)] = kv[i];
     }
-    raw[0][t] = e1;
-    raw[1][t] = e2;
     chg[t] = 0u;
-    // In round 1 every line starts dirty (sites were set, keys reset or the
-    // pass starts from nothing).  Later a brick's keys are a fixed point of
-    // its own relaxation (its last processing ended at one, or the previous
-    // pass's result is one), so only the lines through voxels that a
-    // neighbour's offer lowered can change.
-    dx[t] = dy[t] = dz[t] = r == 1 ? 1 : 0;
-    if (t < 8) flags[t] = 0u;
+    L.pend[t] = 0u;
+    if (t < BZ) L.yl[t] = 0u;
+    if (t < BY) L.zl[t] = 0u;
+    if (t == 0) L.more = 0u;
     __syncthreads();
-    // line masks of this thread's y line (lx, lz) and z line (lx, ly), in
-    // the x rows' format (bit i: edge to i - 1, bit 16 + i: edge to i + 1)
-    uint32_t my = 0, mz = 0;
-#pragma unroll 2
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t wy = raw[0][i + 16 * hi4], wz = raw[1][hi4 + 16 * i];
-      my |= ((wy >> lo4) & 1u) << i | ((wy >> (16 + lo4)) & 1u) << (16 + i);
-      mz |= ((wz >> lo4) & 1u) << i | ((wz >> (16 + lo4)) & 1u) << (16 + i);
-    }
     // offers of the six face neighbours: their keys plus one hop
     {
       auto offer = [&](bool has, bool edge, KT h, int lx, int row) {
         const KT o = KO::add(h, hop);
         if (has && edge && h != kInf && atomicMin(&K[br_at(lx, row)], o) > o) {
-          atomicOr(&chg[row], 1u << lx);
-          dx[row] = 1;
-          dy[lx + 16 * (row >> 4)] = 1;
-          dz[lx + 16 * (row & 15)] = 1;
+          atomicOr(&L.pend[row], 1u << lx);
+          atomicOr(&L.yl[row >> 4], 1u << lx);
+          atomicOr(&L.zl[row & 15], 1u << lx);
         }
       };
       offer(hxm, mx & 1u, fxm, 0, t);
-      offer(hxp, (mx >> 31) & 1u, fxp, 15, t);
+      offer(hxp, (mx >> 16) & 1u, fxp, 15, t);
       offer(hym, my & 1u, fym, lo4, 16 * hi4);
-      offer(hyp, (my >> 31) & 1u, fyp, lo4, 15 + 16 * hi4);
+      offer(hyp, (my >> 16) & 1u, fyp, lo4, 15 + 16 * hi4);
       offer(hzm, mz & 1u, fzm, lo4, hi4);
-      offer(hzp, (mz >> 31) & 1u, fzp, lo4, hi4 + 16 * 15);
+      offer(hzp, (mz >> 16) & 1u, fzp, lo4, hi4 + 16 * 15);
     }
     __syncthreads();
-    // the brick's own fixed point: line sweeps along x, y and z.  A line is
-    // swept (again) along its axis only after a voxel on it changed; the
-    // loop ends when no line is dirty.
-    uint32_t sweeps = 0;
-    for (;;) {
-      ++sweeps;
-      if (dx[t]) {  // row t = (ly, lz)
-        dx[t] = 0;
-        uint32_t c = br_sweep<KT>(K, t * kBRRow, 1, mx, hop);
-        chg[t] |= c;  // only this thread touches row t's word in this stage
-        while (c) {
-          const int x = __builtin_ctz(c);
-          c &= c - 1;
-          dy[x + 16 * hi4] = 1;
-          dz[x + 16 * lo4] = 1;
+    // The brick's own fixed point: line sweeps along x, y and z.  In round 1
+    // every line is swept (sites were set, keys reset or the pass starts from
+    // nothing).  Later a brick's keys are a fixed point of its own relaxation
+    // (its last processing ended at one, or the previous pass's result is
+    // one), so only the lines through voxels that a neighbour's offer lowered
+    // can change; and a line is swept again along its axis only after another
+    // axis changed a voxel on it.  The loop ends with an iteration whose y and
+    // z sweeps change nothing: an x sweep's changes are swept along y and z in
+    // the same iteration, a y sweep's along z.  (`more` is written in the y and
+    // z stages only, and read before the x stage's barrier.)
+    for (uint32_t it = 1;; ++it) {
+      const bool all = r == 1 && it == 1;
+      {  // row t = (ly, lz)
+        const uint32_t pd = L.pend[t];
+        if (all || pd) {
+          const uint32_t c = br_sweep<KT>(K, t * kBRRow, 1, mx, hop);
+          L.pend[t] = 0u;
+          chg[t] |= pd | c;  // only this thread touches row t's words in this stage
+          if (c) {
+            atomicOr(&L.yl[hi4], c);
+            atomicOr(&L.zl[lo4], c);
+          }
         }
       }
       __syncthreads();
-      if (dy[t]) {  // y line (lx, lz) = (lo4, hi4)
-        dy[t] = 0;
-        uint32_t c = br_sweep<KT>(K, 16 * kBRRow * hi4 + lo4, kBRRow, my, hop);
-        while (c) {
-          const int y = __builtin_ctz(c);
-          c &= c - 1;
-          atomicOr(&chg[y + 16 * hi4], 1u << lo4);
-          dx[y + 16 * hi4] = 1;
-          dz[lo4 + 16 * y] = 1;
-        }
+      {  // y line (lx, lz) = (lo4, hi4); yl[lz] is this wave's alone here
+        const uint32_t yl = L.yl[hi4];
+        if (lo4 == 0) L.yl[hi4] = 0u;
+        uint32_t c = 0;
+        if (all || (yl >> lo4 & 1u)) c = br_sweep<KT>(K, 16 * kBRRow * hi4 + lo4, kBRRow, my, hop);
+        br_spread(c, L.pend, L.zl, &L.more, it, [&](int y, int q) { return y + 16 * ((hi4 & ~3) + q); });
       }
       __syncthreads();
-      if (dz[t]) {  // z line (lx, ly) = (lo4, hi4)
-        dz[t] = 0;
-        uint32_t c = br_sweep<KT>(K, hi4 * kBRRow + lo4, 16 * kBRRow, mz, hop);
-        while (c) {
-          const int z = __builtin_ctz(c);
-          c &= c - 1;
-          atomicOr(&chg[hi4 + 16 * z], 1u << lo4);
-          dx[hi4 + 16 * z] = 1;
-          dy[lo4 + 16 * z] = 1;
-        }
+      {  // z line (lx, ly) = (lo4, hi4)
+        const uint32_t zl = L.zl[hi4];
+        if (lo4 == 0) L.zl[hi4] = 0u;
+        uint32_t c = 0;
+        if (all || (zl >> lo4 & 1u)) c = br_sweep<KT>(K, hi4 * kBRRow + lo4, 16 * kBRRow, mz, hop);
+        br_spread(c, L.pend, L.yl, &L.more, it, [&](int z, int q) { return (hi4 & ~3) + q + 16 * z; });
       }
-      __syncthreads();  // every dirty mark of the z stage is visible before the test
-      if (!__syncthreads_or(dx[t] | dy[t] | dz[t])) break;
+      __syncthreads();
+      if (L.more != it) {
+        if (A.dbg && t == 0) {
+          atomicAdd(&A.dbg[0], 1ull);
+          atomicAdd(&A.dbg[1], (unsigned long long)it);
+        }
+        break;
+      }
     }
     // Which neighbours work in round r + 1: a face voxel that changed, has a
     // same-band edge across the face and whose key plus one hop beats the
     // neighbour's voxel across it as read at the top.  Keys only decrease
     // within a pass, so a neighbour whose key already was no larger can never
-    // take the offer.  Thread t checks the face voxels it offered to above.
-    uint32_t fc = 0;
+    // take the offer.  Thread t checks the face voxels it offered to above, and
+    // each wave marks for itself (every writer stores the same tag).
     {
       auto gain = [&](bool has, bool edge, int lx, int row, KT nbk) {
         if (!has || !edge || !((chg[row] >> lx) & 1u)) return false;
         const KT k = K[br_at(lx, row)];
         return KO::add(k, hop) < nbk;
       };
-      fc |= gain(hxm, mx & 1u, 0, t, fxm) ? 2u : 0u;
-      fc |= gain(hxp, (mx >> 31) & 1u, 15, t, fxp) ? 4u : 0u;
-      fc |= gain(hym, my & 1u, lo4, 16 * hi4, fym) ? 8u : 0u;
-      fc |= gain(hyp, (my >> 31) & 1u, lo4, 15 + 16 * hi4, fyp) ? 16u : 0u;
-      fc |= gain(hzm, mz & 1u, lo4, hi4, fzm) ? 32u : 0u;
-      fc |= gain(hzp, (mz >> 31) & 1u, lo4, hi4 + 16 * 15, fzp) ? 64u : 0u;
+      uint32_t f = 0;
+      f |= __ballot(gain(hxm, mx & 1u, 0, t, fxm)) ? 2u : 0u;
+      f |= __ballot(gain(hxp, (mx >> 16) & 1u, 15, t, fxp)) ? 4u : 0u;
+      f |= __ballot(gain(hym, my & 1u, lo4, 16 * hi4, fym)) ? 8u : 0u;
+      f |= __ballot(gain(hyp, (my >> 16) & 1u, lo4, 15 + 16 * hi4, fyp)) ? 16u : 0u;
+      f |= __ballot(gain(hzm, mz & 1u, lo4, hi4, fzm)) ? 32u : 0u;
+      f |= __ballot(gain(hzp, (mz >> 16) & 1u, lo4, hi4 + 16 * 15, fzp)) ? 64u : 0u;
+      const int lane = lane_id();
+      if (lane < 7 && (f >> lane & 1u)) br_mark(A, bx, by, bz, lane, r + 1);
+      if (f && lane == 0) A.alive[(r + 1) % 3] = 1u;
     }
-    if (fc) atomicOr(&flags[0], fc);
     // store what changed.  The thread index is passed through an empty asm
     // statement so that the store addresses are recomputed here instead of
     // being kept live (in registers) from the loads at the top across the
@@ -1264,37 +1339,25 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
     // unreached: stored by the fused reset, it flags nothing).
     int tt = t;
     asm volatile("" : "+v"(tt));
-    bool far = false;
+    uint32_t top = 0;  // the largest stored key plus one (0 for unreached)
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int loc = i * kBRThreads + tt;
-      const int lx = loc & 15, row = loc >> 4;
+      const int lx = tt & 15, row = (tt >> 4) + 16 * i;
       if (fuse || ((chg[row] >> lx) & 1u)) {
         const KT k = K[br_at(lx, row)];
-        if (sizeof(KT) == 4) far |= (uint32_t)k >= A.lim32 && k != kInf;
-        key[(size_t)b * kB + loc] = k;
+        if (sizeof(KT) == 4) top = max(top, (uint32_t)k + 1u);
+        key[(size_t)b * kB + i * kBRThreads + tt] = k;
         if (lx == 0) xface[(size_t)b * 512 + row] = k;
         if (lx == BX - 1) xface[(size_t)b * 512 + 256 + row] = k;
       }
     }
-    if (sizeof(KT) == 4 && far) atomicOr(&A.ctl[3], 4u);
-    if (A.dbg && t == 0) {
-      atomicAdd(&A.dbg[0], 1ull);
-      atomicAdd(&A.dbg[1], (unsigned long long)sweeps);
-    }
-    __syncthreads();
-    // the neighbours that can gain work in round r + 1
-    const uint32_t nb_exists = (hxm ? 2u : 0u) | (hxp ? 4u : 0u) | (hym ? 8u : 0u) | (hyp ? 16u : 0u) |
-                               (hzm ? 32u : 0u) | (hzp ? 64u : 0u);
-    const uint32_t f = flags[0] & nb_exists;
-    if (t >= 1 && t < 7 && ((f >> t) & 1u)) br_mark(A, bx, by, bz, t, r + 1);
-    if (t == 0 && f) A.alive[(r + 1) % 3] = 1u;
+    if (sizeof(KT) == 4 && top > A.lim32) atomicOr(&A.ctl[3], 4u);
     __syncthreads();
   }
 }
 
 template <class KT>
-__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 5 : 4) void k_br_round(BRArgs A, int32_t i) {
+__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_round(BRArgs A, int32_t i) {
   __shared__ BRLds<KT> L;
   const uint32_t r = *A.rnd + 1u + (uint32_t)i;
   const uint32_t count = *br_count(A, r);
@@ -1923,6 +1986,7 @@ struct VTState {
   uint32_t br_rounds_inc = 0;  // rounds of the last incremental one
   hipGraphExec_t br_graph = nullptr;  // kGraphRounds relaxation rounds of this call's workspace (narrow keys)
   hipGraphExec_t br_graph_w = nullptr;  // the same with wide keys
+  bool bricks = false;      // passes by brick relaxation (else by level search)
   bool keys_set = false;    // the key width of the brick relaxation is chosen at its first pass
   uint32_t id_bits = 0;     // narrow keys: the id field's bits; 0: wide keys
   VTState() = default;
@@ -2086,8 +2150,15 @@ unsigned finish_grid(const VTGrid &bg) {
   return (unsigned)(g < 65535 ? g : 65535);
 }
 
-int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, hipStream_t s) {
+// The schedule of the call's passes, and the edge masks of the bands in its form.
+int32_t vt_prepare(const uint8_t *band, const Geom &g, uint32_t S, CvtWork &W, VTState &st, hipStream_t s) {
   VTGrid bg = vt_grid(g);
+  st.bricks = vt_engine(g, S) == VTEngine::Bricks;
+  if (st.bricks) {
+    hipLaunchKernelGGL(k_br_masks, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, band, g, bg, W.eq);
+    LSRVT_LAUNCHED();
+    return LSRVT_OK;
+  }
   const int64_t slots = bg.nbricks * kRows * BX;
   const unsigned grid = (unsigned)std::min<int64_t>((slots + kVTThreads - 1) / kVTThreads, 65535);
   hipLaunchKernelGGL(k_vt_eq, dim3(grid), dim3(kVTThreads), 0, s, band, g, bg, W.eq);
@@ -2374,16 +2445,15 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     hipLaunchKernelGGL(k_count_moved, dim3(std::min<uint32_t>((S + 255) / 256, 256) + (S == 0)), dim3(256), 0, s,
                        W.moved, S, W.ctl + 1);
     // The separate reset reads every key and lets round 1 work on the bricks
-    // that hold reset voxels; the fused one costs about 1.5 rounds over
-    // every brick.  A cube of the mean cell volume n / S overlaps about
-    // (edge / 16 + 1)^3 bricks; the first round after a separate reset was
-    // measured to work on far more (on the flame workload on nearly every
-    // brick with 3 % of the sites moved: the reset bricks, the sites' bricks
-    // and their neighbours), so eight times that count is taken, and the
-    // fused reset once the moved sites would cover about 80 % of the bricks
-    // by that estimate.
+    // that hold reset voxels; the fused one works on every brick in round 1
+    // and reads the keys once.  Always fusing takes 108.8 ms for the flame
+    // loop (1024 x 512 x 512, 30 updates), never 113.9, and 1.6 ms less than
+    // with 1.25 % of the sites as the limit, so the limit lies lower: a cube
+    // of the mean cell volume n / S overlaps about (edge / 16 + 1)^3 bricks,
+    // the bricks beside them work too, and 32 times that count over 80 % of
+    // the bricks is 0.3 % of the sites there.
     const double edge = std::cbrt((double)g.n / std::max<uint32_t>(S, 1u));
-    const double overlap = 8.0 * std::pow(edge / BX + 1.0, 3.0);
+    const double overlap = 32.0 * std::pow(edge / BX + 1.0, 3.0);
     const uint32_t fuse_min = (uint32_t)std::min(0.8 * (double)bg.nbricks / overlap, 4294967295.0);
     hipLaunchKernelGGL(k_br_reset_or_fuse<KT>, dim3((unsigned)std::min<int64_t>((nkeys + 255) / 256, 65535)),
                        dim3(256), 0, s, W.moved, A, fuse_min, tuning(LSRVT_TUNE_RESET));
@@ -2395,7 +2465,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   }
   const unsigned lgrid = (unsigned)std::min<int64_t>((bg.nbricks + 255) / 256, 4096);
   const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
-  const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 2048);
+  const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 8192);
   // kGraphRounds rounds (two launches each, and one that advances the
   // round base) captured once per call and replayed as one graph launch
   hipGraphExec_t &graph = sizeof(KT) == 4 ? st.br_graph : st.br_graph_w;
@@ -2492,7 +2562,7 @@ int32_t run_br(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell,
 // takes the centroid sums of the update that follows.
 int32_t vt_pass(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell, CvtWork &W, VTState &st, bool inc,
                 hipStream_t s, const Fuse *fz = nullptr) {
-  if (vt_engine(g, S) == VTEngine::Bricks) return run_br(g, sites, S, cell, W, st, inc, s, fz);
+  if (st.bricks) return run_br(g, sites, S, cell, W, st, inc, s, fz);
   return inc ? run_vt_inc(g, sites, S, cell, W, st, s, fz) : run_vt(g, sites, S, cell, W, st, s, fz);
 }
 
@@ -2561,9 +2631,9 @@ struct JobDev {
   uint32_t *fb_list, *fb_cnt;
 };
 
-__global__ __launch_bounds__(kVTThreads) void kb_vt_eq(const JobDev *J) {
+__global__ __launch_bounds__(kVTThreads) void kb_br_masks(const JobDev *J) {
   const JobDev &j = J[blockIdx.y];
-  d_vt_eq(j.band, j.g, j.A.bg, j.eq);
+  d_br_masks(j.band, j.g, j.A.bg, j.eq);
 }
 
 __global__ void kb_init_sites(const JobDev *J) {
@@ -2751,12 +2821,12 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
   auto cap = [](int64_t v, int64_t m) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(v, m)); };
   const unsigned g_sites = cap((c.max_sites + 255) / 256, 1 << 20);
   hipLaunchKernelGGL(kb_init_sites, dim3(g_sites, N), dim3(256), 0, s, dj);
-  hipLaunchKernelGGL(kb_vt_eq, dim3(cap((c.max_keys + kVTThreads - 1) / kVTThreads, 65535), N), dim3(kVTThreads), 0,
+  hipLaunchKernelGGL(kb_br_masks, dim3(cap(c.max_keys / (kRows * BX), 65535), N), dim3(kVTThreads), 0,
                      s, dj);
   LSRVT_LAUNCHED();
   const unsigned g_clear = cap((c.max_keys + 255) / 256, 8192);
   const unsigned g_list = cap((c.max_nb + 255) / 256, 4096);
-  const unsigned g_round = cap(c.sum_nb, tuning(LSRVT_TUNE_BR_GRID) > 0 ? tuning(LSRVT_TUNE_BR_GRID) : 2048);
+  const unsigned g_round = cap(c.sum_nb, tuning(LSRVT_TUNE_BR_GRID) > 0 ? tuning(LSRVT_TUNE_BR_GRID) : 8192);
   const unsigned g_fin = cap(c.max_slabs, 65535);
   const unsigned g_tiles = cap(c.max_tiles, 65535);
   const unsigned g_fb = cap(c.max_sites, 1024);
@@ -2938,8 +3008,8 @@ extern "C" int32_t lsrvt_vt(const uint8_t *d_band, lsrvt_dims dims, const uint32
   if ((rc = carve_cvt(d_work, work_bytes, g, n_sites, 0, W))) return rc;
   hipStream_t s = as_stream(stream);
   if ((rc = begin(W, g, s))) return rc;
-  if ((rc = vt_prepare(d_band, g, W, s))) return rc;
   VTState st;
+  if ((rc = vt_prepare(d_band, g, n_sites, W, st, s))) return rc;
   if ((rc = vt_pass(g, d_sites, n_sites, d_cell, W, st, false, s))) return rc;
   return vt_errors(W, s);
 }
@@ -2975,8 +3045,8 @@ extern "C" int32_t lsrvt_cvt(const uint8_t *d_band, const uint32_t *d_comp, lsrv
                        d_site_comp, W.err);
     LSRVT_LAUNCHED();
   }
-  if ((rc = vt_prepare(d_band, g, W, s))) return rc;
   VTState st;
+  if ((rc = vt_prepare(d_band, g, n_sites, W, st, s))) return rc;
   const Fuse fz{d_weights, n_sites,
                 Sums{W.sums, W.sums + n_sites, W.sums + 2 * (size_t)n_sites, W.sums + 3 * (size_t)n_sites}};
   for (int32_t t = 0; t <= iters; ++t) {
