@@ -130,11 +130,13 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 }
 
 // Slot of key c in an open-addressing LDS table of Cap keys (kNone = empty),
-// inserting it if absent; -1 when the table is full.
-template <int Cap>
+// inserting it if absent; -1 when it is not found and has no place within the
+// first Probes slots (a full table is given up on after that many LDS round
+// trips rather than Cap).
+template <int Cap, int Probes = Cap>
 __device__ __forceinline__ int lds_slot(uint32_t *keys, uint32_t c) {
   uint32_t h = (c * 2654435761u) & (Cap - 1);
-  for (int probe = 0; probe < Cap; ++probe) {
+  for (int probe = 0; probe < Probes; ++probe) {
     uint32_t k = __hip_atomic_load(&keys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (k == c) return (int)h;
     if (k == kNone) {

@@ -1372,23 +1372,59 @@ __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_roun
 // ----------------------------------------------------------------------------
 // update
 
+// Per site: mass, mass-weighted x, y and z (M, S_x, S_y, S_z together, so that
+// the four additions for a cell fall into one 32-byte sector).
 struct Sums {
-  unsigned long long *M, *Sx, *Sy, *Sz;
+  unsigned long long *p;  // [S][4]
+  __device__ __forceinline__ void add(uint32_t c, unsigned long long M, unsigned long long X, unsigned long long Y,
+                                      unsigned long long Z) const {
+    atomicAdd(&p[4 * (size_t)c], M);
+    atomicAdd(&p[4 * (size_t)c + 1], X);
+    atomicAdd(&p[4 * (size_t)c + 2], Y);
+    atomicAdd(&p[4 * (size_t)c + 3], Z);
+  }
+};
+
+// Cells as the update reads them: the caller's C-order array, or the search's
+// own brick-major keys (inside the Lloyd loop the C-order cells are written by
+// the last pass only).
+struct CellView {
+  const uint32_t *cell;
+  int32_t nx, ny;
+  __device__ __forceinline__ uint32_t id(int32_t x, int32_t y, int32_t z) const {
+    return cell[x + (int64_t)nx * (y + (int64_t)ny * z)];
+  }
+};
+template <class KT>
+struct KeyView {
+  const KT *key;
+  VTGrid bg;
+  uint32_t idmask;  // all ones for the level search's cells
+  __device__ __forceinline__ uint32_t id(int32_t x_, int32_t y_, int32_t z_) const {
+    const uint32_t x = (uint32_t)x_, y = (uint32_t)y_, z = (uint32_t)z_;
+    const uint32_t b = x / BX + (uint32_t)bg.nbx * (y / BY + (uint32_t)bg.nby * (z / BZ));
+    const KT k = key[(size_t)b * (kRows * BX) + x % BX + BX * (y % BY) + BX * BY * (z % BZ)];
+    return k == (KT)~(KT)0 ? kNone : (uint32_t)k & idmask;
+  }
 };
 
 // The centroid sums of the update (Sec. 3.1: mass and mass-weighted
 // position of every cell, exact uint64 integers, so their order does not
-// matter) taken at the end of the Voronoi pass that produces the cells: the
-// pass's last kernel holds every voxel's cell id once anyway, so the sums
-// cost no second read of the cell array.  Partial sums go into an LDS
-// table keyed by cell id (global atomics when the table is full), flushed
-// with one set of global atomics per distinct cell of the workgroup's part.
-// The level search's finish takes one workgroup per 16^3 brick: thread t
-// takes voxel t, t + 256, ... of the brick, so the 16 lanes of each quarter
-// wave hold one row along x, and a segmented scan over those 16 lanes (DPP
-// row shifts) sums (w, w * (x - x0)) over every run of equal cell id, whose
-// last lane adds it into the table.  The relaxation's finish keeps running
-// sums per lane instead (d_br_finish_slabs).
+// matter) taken at the end of the Voronoi pass that produces the cells, from
+// the search's own brick-major keys.  Partial sums go into an LDS table keyed by
+// cell id (global atomics where a cell finds no place), flushed with one set
+// of global atomics per distinct cell of the workgroup's part.  Two forms:
+//  - wide cells: one workgroup per slab of four bricks with running sums per
+//    lane (d_br_finish_slabs): 0.39 ms for 2^28 voxels (0.56 with the C-order
+//    cells written too);
+//  - narrow cells (fewer than kSlabSites voxels per site): one workgroup per
+//    brick, whose table has room for the hundreds of cells of a brick
+//    (d_brick_sums).  Thread t takes voxel t, t + 256, ... of the brick, so the
+//    16 lanes of each quarter wave hold one row along x, and a segmented scan
+//    over those 16 lanes (DPP row shifts) sums (w, w * (x - x0)) over every run
+//    of equal cell id, whose last lane adds it into the table.  All sums are
+//    relative to the brick's corner and so below 2^32: five words a cell.
+constexpr int64_t kSlabSites = 512;
 struct Fuse {
   const uint16_t *w;  // weights (C order) or null for unit weights
   uint32_t S;
@@ -1399,6 +1435,11 @@ constexpr int kFinTab = 256;
 struct FinTab {
   uint32_t tkey[kFinTab];
   unsigned long long tM[kFinTab], tX[kFinTab], tY[kFinTab], tZ[kFinTab];
+};
+constexpr int kBrickTab = 1024;
+constexpr int kProbes = 16;
+struct BrickTab {
+  uint32_t key[kBrickTab], v[4][kBrickTab];
 };
 
 __device__ __forceinline__ void fin_clear(FinTab &T) {
@@ -1417,9 +1458,10 @@ __device__ __forceinline__ uint32_t row_shift(uint32_t v) {
 
 // One voxel per lane, 16 lanes per row (lane & 15 = x - x0, every lane of
 // the wave active): adds the runs of equal cell id of the wave's four rows
-// into the table.  c = kNone for voxels outside the volume (weight 0).
-__device__ __forceinline__ void fin_row_runs(FinTab &T, const Fuse &F, uint32_t c, uint32_t wv, uint32_t x0,
-                                             uint32_t y, uint32_t z) {
+// (ly, lz) of the brick into the table.  c = kNone for voxels outside the
+// volume (weight 0).
+__device__ __forceinline__ void brick_row_runs(BrickTab &T, const Fuse &F, uint32_t c, uint32_t wv, uint32_t x0,
+                                               uint32_t y0, uint32_t z0, uint32_t ly, uint32_t lz) {
   const uint32_t lx = threadIdx.x & 15;
   const uint32_t cl = (uint32_t)__builtin_amdgcn_update_dpp((int)kNone, (int)c, 0x111, 0xF, 0xF, false);  // row_shr:1
   const uint32_t cr = (uint32_t)__builtin_amdgcn_update_dpp((int)kNone, (int)c, 0x101, 0xF, 0xF, false);  // row_shl:1
@@ -1441,20 +1483,94 @@ __device__ __forceinline__ void fin_row_runs(FinTab &T, const Fuse &F, uint32_t 
 #undef LSRVT_SEG_STEP
   const bool tail = lx == 15 || cr != c;
   if (tail && c < F.S && m) {
-    const unsigned long long M = m, X = (unsigned long long)m * x0 + sx, Y = (unsigned long long)m * y,
-                             Z = (unsigned long long)m * z;
-    const int sl = lds_slot<kFinTab>(T.tkey, c);
+    const int sl = lds_slot<kBrickTab, kProbes>(T.key, c);
     if (sl >= 0) {
-      atomicAdd(&T.tM[sl], M);
-      atomicAdd(&T.tX[sl], X);
-      atomicAdd(&T.tY[sl], Y);
-      atomicAdd(&T.tZ[sl], Z);
+      atomicAdd(&T.v[0][sl], m);
+      if (sx) atomicAdd(&T.v[1][sl], sx);
+      if (ly) atomicAdd(&T.v[2][sl], m * ly);
+      if (lz) atomicAdd(&T.v[3][sl], m * lz);
     } else {
-      atomicAdd(&F.sums.M[c], M);
-      atomicAdd(&F.sums.Sx[c], X);
-      atomicAdd(&F.sums.Sy[c], Y);
-      atomicAdd(&F.sums.Sz[c], Z);
+      F.sums.add(c, m, (unsigned long long)m * x0 + sx, (unsigned long long)m * (y0 + ly),
+                 (unsigned long long)m * (z0 + lz));
     }
+  }
+}
+
+// Cell ids of a brick's voxels at the end of a pass: the relaxation's keys,
+// or the level search's cells, where a voxel not reached (in an incremental
+// pass: an invalid one not reached again) is set to NONE on the way.
+template <class KT>
+struct KeySource {
+  const KT *key;
+  uint32_t idmask;
+  __device__ __forceinline__ uint32_t id(int64_t b, int loc) const {
+    const KT k = key[b * (kRows * BX) + loc];
+    return k == (KT)~(KT)0 ? kNone : (uint32_t)k & idmask;
+  }
+};
+template <bool INC>
+struct LevelSource {
+  const uint16_t *vis, *inv;
+  uint32_t *cellb;
+  __device__ __forceinline__ uint32_t id(int64_t b, int loc) const {
+    const int64_t rr = b * kRows + (loc >> 4);
+    bool miss = !((vis[rr] >> (loc & 15)) & 1u);
+    if (INC) miss = miss && ((inv[rr] >> (loc & 15)) & 1u);
+    const size_t bi = (size_t)b * (kRows * BX) + loc;
+    if (miss) cellb[bi] = kNone;
+    return miss ? kNone : cellb[bi];
+  }
+};
+
+// One workgroup per brick.  Workgroups are dealt to the eight XCDs in turn:
+// XCD i % 8 takes the i-th eighth of the bricks, so that x-adjacent bricks,
+// which share the 128-byte lines of the weights, meet in one L2.
+//
+// Bound by the row scans and the LDS table.  379 x 251 x 147 voxels in 77192
+// cells take 52 us; slabs with a table of 256 cells, which a slab's thousands
+// overflow, 207 us, and a full table searched to its end before the global
+// atomics (249 us for one 64^3 volume in 12627 cells; now 18).
+template <class Src>
+__device__ __forceinline__ void d_brick_sums(const Src &src, Geom g, VTGrid bg, const Fuse &F, BrickTab &T) {
+  const int t = threadIdx.x;
+  const int64_t per = (bg.nbricks + 7) / 8;
+  for (int64_t i = blockIdx.x; i < 8 * per; i += gridDim.x) {
+    const int64_t b = (i & 7) * per + (i >> 3);
+    if (b >= bg.nbricks) continue;
+    const int x0 = (int)(b % bg.nbx) * BX, y0 = (int)((b / bg.nbx) % bg.nby) * BY,
+              z0 = (int)(b / ((int64_t)bg.nbx * bg.nby)) * BZ;
+    for (int k = t; k < kBrickTab; k += kVTThreads) {
+      T.key[k] = kNone;
+      T.v[0][k] = T.v[1][k] = T.v[2][k] = T.v[3][k] = 0u;
+    }
+    __syncthreads();
+    const int x = x0 + (t & 15), y = y0 + (t >> 4);
+    const bool xy = x < g.nx && y < g.ny;
+    constexpr int kAhead = 4;  // voxels whose loads are issued together
+    for (int z1 = 0; z1 < BZ; z1 += kAhead) {
+      uint32_t c[kAhead], wt[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const bool in = xy && z0 + z1 + u < g.nz;
+        c[u] = in ? src.id(b, (z1 + u) * kVTThreads + t) : kNone;
+        wt[u] = !in ? 0u : F.w ? (uint32_t)F.w[x + (int64_t)g.nx * (y + (int64_t)g.ny * (z0 + z1 + u))] : 1u;
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        brick_row_runs(T, F, c[u], wt[u], (uint32_t)x0, (uint32_t)y0, (uint32_t)z0, (uint32_t)t >> 4,
+                       (uint32_t)(z1 + u));
+    }
+    __syncthreads();
+    // four lanes a cell, one sum each
+    const uint32_t org = (t & 3) == 1 ? (uint32_t)x0 : (t & 3) == 2 ? (uint32_t)y0 : (uint32_t)z0;
+    for (int k = t; k < 4 * kBrickTab; k += kVTThreads) {
+      const uint32_t c = T.key[k >> 2], m = T.v[0][k >> 2];
+      if (c == kNone || m == 0u) continue;
+      const unsigned long long v =
+          (k & 3) == 0 ? (unsigned long long)m : (unsigned long long)m * org + T.v[k & 3][k >> 2];
+      atomicAdd(&F.sums.p[4 * (size_t)c + (k & 3)], v);
+    }
+    __syncthreads();
   }
 }
 
@@ -1463,18 +1579,13 @@ __device__ __forceinline__ void fin_row_runs(FinTab &T, const Fuse &F, uint32_t 
 __device__ __forceinline__ void fin_flush(FinTab &T, const Fuse &F) {
   for (int i = threadIdx.x; i < kFinTab; i += blockDim.x) {
     const uint32_t c = T.tkey[i];
-    if (c != kNone && T.tM[i]) {
-      atomicAdd(&F.sums.M[c], T.tM[i]);
-      atomicAdd(&F.sums.Sx[c], T.tX[i]);
-      atomicAdd(&F.sums.Sy[c], T.tY[i]);
-      atomicAdd(&F.sums.Sz[c], T.tZ[i]);
-    }
+    if (c != kNone && T.tM[i]) F.sums.add(c, T.tM[i], T.tX[i], T.tY[i], T.tZ[i]);
   }
   __syncthreads();
 }
 
 // End of a relaxation pass: the keys to C-order cells (kNone where
-// unreached) and, with SUMS, the centroid sums of the update that follows.
+// unreached) or, with SUMS, the centroid sums of the update that follows.
 // One workgroup per slab of four x-adjacent bricks (64 x 16 x 16 voxels);
 // lane l of every wave owns x = 64 sx + l, so a row's cells (256 B) and
 // weights (128 B) are contiguous and each brick's 16 keys of the row are
@@ -1510,17 +1621,14 @@ __device__ __forceinline__ void d_br_finish_slabs(const KT *__restrict__ key, Ge
         const unsigned long long M = m, X = (unsigned long long)m * (uint32_t)x,
                                  Y = (unsigned long long)m * (uint32_t)y0 + sy,
                                  Z = (unsigned long long)m * (uint32_t)z0 + sz;
-        const int slot = lds_slot<kFinTab>(T->tkey, cur);
+        const int slot = lds_slot<kFinTab, kProbes>(T->tkey, cur);
         if (slot >= 0) {
           atomicAdd(&T->tM[slot], M);
           atomicAdd(&T->tX[slot], X);
           atomicAdd(&T->tY[slot], Y);
           atomicAdd(&T->tZ[slot], Z);
         } else {
-          atomicAdd(&F.sums.M[cur], M);
-          atomicAdd(&F.sums.Sx[cur], X);
-          atomicAdd(&F.sums.Sy[cur], Y);
-          atomicAdd(&F.sums.Sz[cur], Z);
+          F.sums.add(cur, M, X, Y, Z);
         }
       }
     };
@@ -1543,8 +1651,9 @@ __device__ __forceinline__ void d_br_finish_slabs(const KT *__restrict__ key, Ge
         const int ly = r & 15, lz = r >> 4;
         const bool in = xin && y0 + ly < g.ny && z0 + lz < g.nz;
         const uint32_t c = k[u] == BRKey<KT>::inf ? kNone : (uint32_t)k[u] & idmask;
-        if (in) cell[(int64_t)g.nx * ((y0 + ly) + (int64_t)g.ny * (z0 + lz)) + x] = c;
-        if constexpr (SUMS) {
+        if constexpr (!SUMS) {
+          if (in) cell[(int64_t)g.nx * ((y0 + ly) + (int64_t)g.ny * (z0 + lz)) + x] = c;
+        } else {
           const uint32_t cc = in ? c : kNone;
           if (cc != cur) {
             flush();
@@ -1567,9 +1676,14 @@ __device__ __forceinline__ void d_br_finish_slabs(const KT *__restrict__ key, Ge
 
 template <class KT>
 __global__ __launch_bounds__(kVTThreads) void k_br_finish_sums(const KT *__restrict__ key, Geom g, VTGrid bg,
-                                                               uint32_t idmask, uint32_t *__restrict__ cell, Fuse F) {
+                                                               uint32_t idmask, Fuse F) {
   __shared__ FinTab T;
-  d_br_finish_slabs<KT, true>(key, g, bg, idmask, cell, F, &T);
+  d_br_finish_slabs<KT, true>(key, g, bg, idmask, nullptr, F, &T);
+}
+template <class Src>
+__global__ __launch_bounds__(kVTThreads) void k_brick_sums(Src src, Geom g, VTGrid bg, Fuse F) {
+  __shared__ BrickTab T;
+  d_brick_sums(src, g, bg, F, T);
 }
 template <class KT>
 __global__ __launch_bounds__(kVTThreads) void k_br_finish(const KT *__restrict__ key, Geom g, VTGrid bg,
@@ -1586,7 +1700,7 @@ __global__ __launch_bounds__(kVTThreads) void k_br_finish(const KT *__restrict__
 constexpr int TX = 64, TY = 8, TZ = 8;
 constexpr int kTabCap = 512;
 
-__device__ __forceinline__ void d_centroid(const uint32_t *__restrict__ cell, const uint16_t *__restrict__ w,
+__global__ __launch_bounds__(256) void k_centroid(const uint32_t *__restrict__ cell, const uint16_t *__restrict__ w,
                                                   Geom g, uint32_t S, Sums sums) {
   __shared__ uint32_t tkey[kTabCap];
   __shared__ unsigned long long tM[kTabCap], tX[kTabCap], tY[kTabCap], tZ[kTabCap];
@@ -1627,35 +1741,25 @@ __device__ __forceinline__ void d_centroid(const uint32_t *__restrict__ cell, co
         }
       }
       if (tail && c < S && m) {
-        const int sl = lds_slot<kTabCap>(tkey, c);
+        const int sl = lds_slot<kTabCap, kProbes>(tkey, c);
         if (sl >= 0) {
           atomicAdd(&tM[sl], (unsigned long long)m);
           atomicAdd(&tX[sl], (unsigned long long)sx);
           atomicAdd(&tY[sl], (unsigned long long)m * (uint64_t)y);
           atomicAdd(&tZ[sl], (unsigned long long)m * (uint64_t)z);
         } else {
-          atomicAdd(&sums.M[c], (unsigned long long)m);
-          atomicAdd(&sums.Sx[c], (unsigned long long)sx);
-          atomicAdd(&sums.Sy[c], (unsigned long long)m * (uint64_t)y);
-          atomicAdd(&sums.Sz[c], (unsigned long long)m * (uint64_t)z);
+          sums.add(c, m, sx, (unsigned long long)m * (uint64_t)y, (unsigned long long)m * (uint64_t)z);
         }
       }
     }
     __syncthreads();
     for (int i = t; i < kTabCap; i += 256) {
       const uint32_t c = tkey[i];
-      if (c != kNone && tM[i]) {
-        atomicAdd(&sums.M[c], tM[i]);
-        atomicAdd(&sums.Sx[c], tX[i]);
-        atomicAdd(&sums.Sy[c], tY[i]);
-        atomicAdd(&sums.Sz[c], tZ[i]);
-      }
+      if (c != kNone && tM[i]) sums.add(c, tM[i], tX[i], tY[i], tZ[i]);
     }
     __syncthreads();
   }
 }
-__global__ __launch_bounds__(256) void k_centroid(const uint32_t *__restrict__ cell, const uint16_t *__restrict__ w,
-                                                  Geom g, uint32_t S, Sums sums) { d_centroid(cell, w, g, S, sums); }
 
 
 struct U128 {
@@ -1681,20 +1785,22 @@ __device__ __forceinline__ double move_len(uint32_t a, uint32_t b, Geom g) {
 
 // moved[s] records whether site s moved (the next Voronoi pass is
 // incremental over the moved sites).
-__device__ __forceinline__ void d_snap(const uint32_t *__restrict__ cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds,
-                       uint8_t *moved, uint32_t *fb_list, uint32_t *fb_cnt) {
+template <class View>
+__device__ __forceinline__ void d_snap(const View &cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds,
+                                       uint8_t *moved, uint32_t *fb_list, uint32_t *fb_cnt) {
   uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= S) return;
-  uint64_t M = sums.M[s];
+  const unsigned long long *sm = sums.p + 4 * (size_t)s;
+  const uint64_t M = sm[0];
   uint32_t old = sites[s];
   moved[s] = 0;
   if (M == 0) {
     if (ds) ds[s] = 0.0;
     return;
   }
-  uint64_t qx = round_half_down(sums.Sx[s], M), qy = round_half_down(sums.Sy[s], M), qz = round_half_down(sums.Sz[s], M);
-  uint32_t q = (uint32_t)(qx + (uint64_t)g.nx * (qy + (uint64_t)g.ny * qz));
-  if (cell[q] == s) {
+  const uint64_t qx = round_half_down(sm[1], M), qy = round_half_down(sm[2], M), qz = round_half_down(sm[3], M);
+  const uint32_t q = (uint32_t)(qx + (uint64_t)g.nx * (qy + (uint64_t)g.ny * qz));
+  if (cell.id((int32_t)qx, (int32_t)qy, (int32_t)qz) == s) {
     sites[s] = q;
     moved[s] = q != old;
     if (ds) ds[s] = move_len(old, q, g);
@@ -1703,94 +1809,228 @@ __device__ __forceinline__ void d_snap(const uint32_t *__restrict__ cell, Geom g
     fb_list[pos] = s;
   }
 }
-__global__ void k_snap(const uint32_t *__restrict__ cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds,
-                       uint8_t *moved, uint32_t *fb_list, uint32_t *fb_cnt) { d_snap(cell, g, S, sums, sites, ds, moved, fb_list, fb_cnt); }
+template <class View>
+__global__ void k_snap(View cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds, uint8_t *moved,
+                       uint32_t *fb_list, uint32_t *fb_cnt) {
+  d_snap(cell, g, S, sums, sites, ds, moved, fb_list, fb_cnt);
+}
 
-
-// Exact nearest in-cell voxel by growing cubes; one workgroup per site.
-__device__ __forceinline__ void d_snap_fallback(const uint32_t *__restrict__ cell, Geom g, Sums sums,
-                                                       uint32_t *sites, double *ds, uint8_t *moved,
-                                                       const uint32_t *fb_list, const uint32_t *fb_cnt) {
-  __shared__ uint64_t r_hi[256], r_lo[256];
-  __shared__ uint32_t r_v[256];
-  const int t = threadIdx.x;
-  const uint32_t count = *fb_cnt;
-  for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) {
-    const uint32_t s = fb_list[item];
-    const uint64_t M = sums.M[s];
-    const uint64_t Sa[3] = {sums.Sx[s], sums.Sy[s], sums.Sz[s]};
-    const int64_t q[3] = {(int64_t)round_half_down(Sa[0], M), (int64_t)round_half_down(Sa[1], M),
-                          (int64_t)round_half_down(Sa[2], M)};
-    const int64_t ext[3] = {g.nx, g.ny, g.nz};
-    U128 best{~0ull, ~0ull};
-    uint32_t bestv = kNone;
-    for (int64_t r = 1;; r *= 2) {
-      int64_t lo[3], hi[3], len[3];
-      bool whole = true;
-      for (int a = 0; a < 3; ++a) {
-        lo[a] = q[a] - r < 0 ? 0 : q[a] - r;
-        hi[a] = q[a] + r > ext[a] - 1 ? ext[a] - 1 : q[a] + r;
-        len[a] = hi[a] - lo[a] + 1;
-        whole = whole && lo[a] == 0 && hi[a] == ext[a] - 1;
-      }
-      const int64_t vol = len[0] * len[1] * len[2];
-      for (int64_t i = t; i < vol; i += 256) {
-        int64_t cx = lo[0] + i % len[0];
-        int64_t rr = i / len[0];
-        int64_t cy = lo[1] + rr % len[1];
-        int64_t cz = lo[2] + rr / len[1];
-        int64_t v = cx + (int64_t)g.nx * (cy + (int64_t)g.ny * cz);
-        if (cell[v] != s) continue;
-        U128 D = sq64(absdiff(M * (uint64_t)cx, Sa[0]));
-        D = add128(D, sq64(absdiff(M * (uint64_t)cy, Sa[1])));
-        D = add128(D, sq64(absdiff(M * (uint64_t)cz, Sa[2])));
-        if (lt128(D, best) || (D.hi == best.hi && D.lo == best.lo && (uint32_t)v < bestv)) {
-          best = D;
-          bestv = (uint32_t)v;
+// Exact nearest in-cell voxel by growing cubes around the centroid: half-widths
+// up to kSnapNear by one wave (W = 1), from 2 kSnapNear on by a team of W waves.
+// The site's own voxel, which lies in the cell, is a first candidate, and a
+// voxel farther from the centroid than the best one so far is left out without
+// being read, in float64 with a margin far above its rounding.  What is read is
+// compared exactly, so the answer is that of the whole search.  The team's waves
+// take planes of the cube, 16, 32 or 64 lanes a row of it (by its width), eight
+// rows in flight.  Returns false when the search has to go on beyond kSnapNear.
+constexpr int32_t kSnapNear = 4;
+struct SnapLds {
+  uint64_t hi[16], lo[16];
+  uint32_t v[16];
+};
+template <int W, class View>
+__device__ __forceinline__ bool snap_search(const View &cell, Geom g, const unsigned long long *sm, uint32_t s,
+                                            uint32_t old, int w, SnapLds *L, uint32_t &bestv) {
+  constexpr int kRowsAhead = 8;
+  const int lane = lane_id();
+  const uint64_t M = sm[0];
+  const uint64_t Sa[3] = {sm[1], sm[2], sm[3]};
+  const int32_t q[3] = {(int32_t)round_half_down(Sa[0], M), (int32_t)round_half_down(Sa[1], M),
+                        (int32_t)round_half_down(Sa[2], M)};
+  const int32_t ext[3] = {g.nx, g.ny, g.nz};
+  const double dM = (double)M;
+  const double cx = (double)Sa[0] / dM, cy = (double)Sa[1] / dM, cz = (double)Sa[2] / dM;
+  auto dist = [&](int32_t x, int32_t y, int32_t z) {  // (M |v - c|)^2
+    U128 D = sq64(absdiff(M * (uint64_t)x, Sa[0]));
+    D = add128(D, sq64(absdiff(M * (uint64_t)y, Sa[1])));
+    return add128(D, sq64(absdiff(M * (uint64_t)z, Sa[2])));
+  };
+  U128 best{~0ull, ~0ull};
+  bestv = kNone;
+  auto take = [&](U128 D, uint32_t v) {
+    if (lt128(D, best) || (D.hi == best.hi && D.lo == best.lo && v < bestv)) {
+      best = D;
+      bestv = v;
+    }
+  };
+  {
+    const int32_t ox = (int32_t)(old % (uint32_t)g.nx), oy = (int32_t)(old / (uint32_t)g.nx % (uint32_t)g.ny),
+                  oz = (int32_t)(old / (uint32_t)g.nx / (uint32_t)g.ny);
+    if (cell.id(ox, oy, oz) == s) take(dist(ox, oy, oz), old);
+  }
+  // squared distance of the best voxel so far
+  auto reach = [&]() {
+    return bestv == kNone ? __builtin_inf()
+                          : ((double)best.hi * 0x1p64 + (double)best.lo) / (dM * dM) * (1.0 + 1e-9) + 1e-3;
+  };
+  auto wave_best = [&](uint32_t before) {  // the best of the wave's lanes, unless none found a new one
+    if (__ballot(bestv != before) == 0ull) return;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint64_t h = __shfl_xor(best.hi, o, kWave), l = __shfl_xor(best.lo, o, kWave);
+      const uint32_t v = __shfl_xor(bestv, o, kWave);
+      take(U128{h, l}, v);
+    }
+  };
+  auto done = [&](int32_t r) {
+    bool whole = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) whole = whole && q[a] - r <= 0 && q[a] + r >= ext[a] - 1;
+    return whole || (bestv != kNone && lt128(shl2(best), sq64(M * (uint64_t)(2 * (int64_t)r + 1))));
+  };
+  if constexpr (W == 1) {
+    // cubes of fixed size, their voxels over the lanes
+    auto cube = [&](auto half) {
+      constexpr int R = decltype(half)::value, kSide = 2 * R + 1, kAll = kSide * kSide * kSide;
+      constexpr int kAhead = kAll < 8 * kWave ? (kAll + kWave - 1) / kWave : 6;
+      const double rho2 = reach();
+      const uint32_t before = bestv;
+      for (int i0 = lane; i0 < kAll + lane; i0 += kAhead * kWave) {
+        uint32_t id[kAhead];
+        int32_t x[kAhead], y[kAhead], z[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int i = i0 + u * kWave;
+          x[u] = q[0] - R + i % kSide;
+          y[u] = q[1] - R + i / kSide % kSide;
+          z[u] = q[2] - R + i / (kSide * kSide);
+          const double ex = x[u] - cx, ey = y[u] - cy, ez = z[u] - cz;
+          const bool in = i < kAll && x[u] >= 0 && y[u] >= 0 && z[u] >= 0 && x[u] < ext[0] && y[u] < ext[1] &&
+                          z[u] < ext[2] && ex * ex + ey * ey + ez * ez <= rho2;
+          id[u] = in ? cell.id(x[u], y[u], z[u]) : kNone;
         }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (id[u] == s) take(dist(x[u], y[u], z[u]), (uint32_t)(x[u] + (int64_t)g.nx * (y[u] + (int64_t)g.ny * z[u])));
       }
-      r_hi[t] = best.hi;
-      r_lo[t] = best.lo;
-      r_v[t] = bestv;
-      __syncthreads();
-      for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) {
-          U128 a{r_hi[t], r_lo[t]}, b{r_hi[t + o], r_lo[t + o]};
-          uint32_t av = r_v[t], bv = r_v[t + o];
-          if (lt128(b, a) || (b.hi == a.hi && b.lo == a.lo && bv < av)) {
-            r_hi[t] = b.hi;
-            r_lo[t] = b.lo;
-            r_v[t] = bv;
+      wave_best(before);
+      return done(R);
+    };
+    if (cube(std::integral_constant<int, kSnapNear / 2>{})) return true;
+    return cube(std::integral_constant<int, kSnapNear>{});
+  }
+  for (int32_t r = 2 * kSnapNear;; r *= 2) {
+    int32_t lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = q[a] - r < 0 ? 0 : q[a] - r;
+      hi[a] = q[a] + r > ext[a] - 1 ? ext[a] - 1 : q[a] + r;
+    }
+    const double rho2 = reach();
+    const uint32_t before = bestv;
+    const int32_t width = hi[0] - lo[0] + 1;
+    const int32_t XL = width <= 16 ? 16 : width <= 32 ? 32 : kWave;  // lanes of a row
+    const int32_t per = kWave / XL;
+    for (int32_t z = lo[2] + w; z <= hi[2]; z += W) {
+      const double ez2 = (z - cz) * (z - cz);
+      if (ez2 > rho2) continue;
+      // the rows and the part of them within reach of the plane
+      int32_t y0 = lo[1], y1 = hi[1], x0 = lo[0], x1 = hi[0];
+      if (rho2 < 1e12) {
+        const double half = sqrt(rho2 - ez2) + 1.0;
+        y0 = max(y0, (int32_t)(cy - half));
+        y1 = min(y1, (int32_t)(cy + half) + 1);
+        x0 = max(x0, (int32_t)(cx - half));
+        x1 = min(x1, (int32_t)(cx + half) + 1);
+      }
+      for (int32_t xc = x0; xc <= x1; xc += XL)
+        for (int32_t yc = y0; yc <= y1; yc += kRowsAhead * per) {
+          const int32_t x = xc + lane % XL;
+          const double ex2 = (x - cx) * (x - cx) + ez2;
+          uint32_t id[kRowsAhead];
+#pragma unroll
+          for (int u = 0; u < kRowsAhead; ++u) {
+            const int32_t y = yc + u * per + lane / XL;
+            const double ey = y - cy;
+            id[u] = x <= x1 && y <= y1 && ex2 + ey * ey <= rho2 ? cell.id(x, y, z) : kNone;
+          }
+#pragma unroll
+          for (int u = 0; u < kRowsAhead; ++u) {
+            if (id[u] != s) continue;
+            const int32_t y = yc + u * per + lane / XL;
+            take(dist(x, y, z), (uint32_t)(x + (int64_t)g.nx * (y + (int64_t)g.ny * z)));
           }
         }
-        __syncthreads();
-      }
-      best = U128{r_hi[0], r_lo[0]};
-      bestv = r_v[0];
-      __syncthreads();
-      bool done = whole;
-      if (!done && bestv != kNone) {
-        U128 bound = sq64(M * (uint64_t)(2 * r + 1));
-        done = lt128(shl2(best), bound);
-      }
-      if (done) break;
     }
-    if (t == 0) {
-      uint32_t old = sites[s];
-      if (bestv != kNone) {
-        sites[s] = bestv;
-        moved[s] = bestv != old;
-        if (ds) ds[s] = move_len(old, bestv, g);
-      } else if (ds) {
-        ds[s] = 0.0;
-      }
+    wave_best(before);
+    if (lane == 0) {
+      L->hi[w] = best.hi;
+      L->lo[w] = best.lo;
+      L->v[w] = bestv;
     }
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < W; ++i) take(U128{L->hi[i], L->lo[i]}, L->v[i]);
+    __syncthreads();
+    if (done(r)) return true;
   }
 }
-__global__ __launch_bounds__(256) void k_snap_fallback(const uint32_t *__restrict__ cell, Geom g, Sums sums,
-                                                       uint32_t *sites, double *ds, uint8_t *moved,
-                                                       const uint32_t *fb_list, const uint32_t *fb_cnt) { d_snap_fallback(cell, g, sums, sites, ds, moved, fb_list, fb_cnt); }
+
+__device__ __forceinline__ void snap_store(Geom g, uint32_t s, uint32_t old, uint32_t v, uint32_t *sites, double *ds,
+                                           uint8_t *moved) {
+  if (v != kNone) {
+    sites[s] = v;
+    moved[s] = v != old;
+    if (ds) ds[s] = move_len(old, v, g);
+  } else if (ds) {
+    ds[s] = 0.0;
+  }
+}
+
+// The sites whose rounded centroid lies outside their cell, in two steps: one
+// wave a site looks within kSnapNear voxels, which is enough for almost all of
+// them, and takes the finished ones off the list (kNone); the rest get a
+// workgroup of sixteen waves each.
+//
+// Bound by the latency of the reads: 379 x 251 x 147 voxels in 77192 cells take
+// 32 us an update (42 us with one workgroup of four waves for every site, one
+// cube after another and all of it read), the flame loop (1024 x 512 x 512),
+// whose few far sites are searched over cubes of 65^3 voxels and more, 110 us
+// (326 us, with a 64-bit division per voxel).
+constexpr int kSnapFarThreads = 1024;
+template <class View>
+__device__ __forceinline__ void d_snap_near(const View &cell, Geom g, Sums sums, uint32_t *sites, double *ds,
+                                            uint8_t *moved, uint32_t *fb_list, const uint32_t *fb_cnt) {
+  const uint32_t count = *fb_cnt;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  for (uint32_t item = blockIdx.x * (256 / kWave) + w; item < count; item += gridDim.x * (256 / kWave)) {
+    const uint32_t s = fb_list[item];
+    const uint32_t old = sites[s];
+    uint32_t v;
+    if (!snap_search<1>(cell, g, sums.p + 4 * (size_t)s, s, old, 0, nullptr, v)) continue;
+    if (lane_id() == 0) {
+      snap_store(g, s, old, v, sites, ds, moved);
+      fb_list[item] = kNone;
+    }
+  }
+}
+template <class View>
+__device__ __forceinline__ void d_snap_far(const View &cell, Geom g, Sums sums, uint32_t *sites, double *ds,
+                                           uint8_t *moved, const uint32_t *fb_list, const uint32_t *fb_cnt) {
+  __shared__ SnapLds L;
+  const uint32_t count = *fb_cnt;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) {
+    const uint32_t s = fb_list[item];
+    if (s == kNone) continue;  // uniform
+    const uint32_t old = sites[s];
+    uint32_t v;
+    snap_search<kSnapFarThreads / kWave>(cell, g, sums.p + 4 * (size_t)s, s, old, w, &L, v);
+    __syncthreads();  // every wave has read the site
+    if (threadIdx.x == 0) snap_store(g, s, old, v, sites, ds, moved);
+  }
+}
+template <class View>
+__global__ __launch_bounds__(256) void k_snap_near(View cell, Geom g, Sums sums, uint32_t *sites, double *ds,
+                                                   uint8_t *moved, uint32_t *fb_list, const uint32_t *fb_cnt) {
+  d_snap_near(cell, g, sums, sites, ds, moved, fb_list, fb_cnt);
+}
+template <class View>
+__global__ __launch_bounds__(kSnapFarThreads) void k_snap_far(View cell, Geom g, Sums sums, uint32_t *sites,
+                                                              double *ds, uint8_t *moved, const uint32_t *fb_list,
+                                                              const uint32_t *fb_cnt) {
+  d_snap_far(cell, g, sums, sites, ds, moved, fb_list, fb_cnt);
+}
 
 
 // Mean of ds[0..S) in a fixed order: 256 contiguous chunks summed by 256
@@ -2092,47 +2332,6 @@ __global__ __launch_bounds__(kVTThreads) void k_vt_finish(const uint16_t *__rest
   }
 }
 
-// The same end of a level-search pass with the centroid sums of the update
-// that follows, one workgroup per brick (segmented row scans, see Fuse).
-template <bool INC>
-__global__ __launch_bounds__(kVTThreads) void k_vt_finish_sums(const uint16_t *__restrict__ vis,
-                                                               const uint16_t *__restrict__ inv, Geom g, VTGrid bg,
-                                                               uint32_t *__restrict__ cellb,
-                                                               uint32_t *__restrict__ cell, Fuse F) {
-  __shared__ FinTab T;
-  const int t = threadIdx.x;
-  for (int64_t b = blockIdx.x; b < bg.nbricks; b += gridDim.x) {
-    const int bx = (int)(b % bg.nbx), by = (int)((b / bg.nbx) % bg.nby), bz = (int)(b / ((int64_t)bg.nbx * bg.nby));
-    fin_clear(T);
-    __syncthreads();
-#pragma unroll 4
-    for (int i = 0; i < BX; ++i) {
-      const int loc = i * kVTThreads + t;
-      const int lx = loc & 15;
-      const int64_t rr = b * kRows + (loc >> 4);
-      const int x = bx * BX + lx, y = by * BY + ((loc >> 4) & 15), z = bz * BZ + (loc >> 8);
-      const bool in = x < g.nx && y < g.ny && z < g.nz;
-      const size_t bi = (size_t)b * (kRows * BX) + loc;
-      uint32_t c = kNone;
-      if (in) {
-        bool miss = !((vis[rr] >> lx) & 1u);
-        if (INC) miss = miss && ((inv[rr] >> lx) & 1u);
-        c = cellb[bi];
-        if (miss) {
-          c = kNone;
-          cellb[bi] = kNone;
-        }
-      }
-      const int64_t v = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
-      if (in) cell[v] = c;
-      const uint32_t wv = in ? (F.w ? (uint32_t)F.w[v] : 1u) : 0u;
-      fin_row_runs(T, F, c, wv, (uint32_t)(bx * BX), (uint32_t)y, (uint32_t)z);
-    }
-    __syncthreads();
-    fin_flush(T, F);
-  }
-}
-
 // Site voxels cleared before level 0 of a full pass (brick-major cells).
 __global__ void k_sites_clear(const uint32_t *__restrict__ sites, uint32_t S, BFSArgs A) {
   uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2140,6 +2339,8 @@ __global__ void k_sites_clear(const uint32_t *__restrict__ sites, uint32_t S, BF
 }
 
 unsigned brick_grid(const VTGrid &bg) { return (unsigned)std::min<int64_t>(bg.nbricks, 65535); }
+// workgroups of d_brick_sums (a multiple of 8)
+unsigned sums_grid(const VTGrid &bg) { return (unsigned)std::min<int64_t>((bg.nbricks + 7) / 8 * 8, 65528); }
 
 // Workgroups of the relaxation's finish: one per slab of four x-adjacent bricks.
 int64_t br_slabs(const VTGrid &bg) { return (int64_t)((bg.nbx + 3) / 4) * bg.nby * bg.nbz; }
@@ -2303,8 +2504,8 @@ int32_t run_vt(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell,
     if ((rc = run_levels<false>(g, A, W, st, s, &redo))) return rc;
   }
   if (fz)
-    hipLaunchKernelGGL(k_vt_finish_sums<false>, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, W.vis, W.inv, g, bg,
-                       W.cellb, cell, *fz);
+    hipLaunchKernelGGL(k_brick_sums<LevelSource<false>>, dim3(sums_grid(bg)), dim3(kVTThreads), 0, s,
+                       (LevelSource<false>{W.vis, W.inv, W.cellb}), g, bg, *fz);
   else
     hipLaunchKernelGGL(k_vt_finish<false>, dim3(finish_grid(bg)), dim3(kVTThreads), 0, s, W.vis, W.inv, g, bg,
                        W.cellb, cell);
@@ -2342,8 +2543,8 @@ int32_t run_vt_inc(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *c
     return run_vt(g, sites, S, cell, W, st, s, fz);
   }
   if (fz)
-    hipLaunchKernelGGL(k_vt_finish_sums<true>, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, W.vis, W.inv, g, bg,
-                       W.cellb, cell, *fz);
+    hipLaunchKernelGGL(k_brick_sums<LevelSource<true>>, dim3(sums_grid(bg)), dim3(kVTThreads), 0, s,
+                       (LevelSource<true>{W.vis, W.inv, W.cellb}), g, bg, *fz);
   else
     hipLaunchKernelGGL(k_vt_finish<true>, dim3(finish_grid(bg)), dim3(kVTThreads), 0, s, W.vis, W.inv, g, bg,
                        W.cellb, cell);
@@ -2523,9 +2724,12 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     fprintf(stderr, "\n");
   }
   const KT *keys = static_cast<const KT *>(A.key);
-  if (fz)
+  if (fz && g.n / (int64_t)std::max<uint32_t>(S, 1u) < kSlabSites)
+    hipLaunchKernelGGL(k_brick_sums<KeySource<KT>>, dim3(sums_grid(bg)), dim3(kVTThreads), 0, s,
+                       (KeySource<KT>{keys, A.idmask}), g, bg, *fz);
+  else if (fz)
     hipLaunchKernelGGL(k_br_finish_sums<KT>, dim3(slab_grid(bg)), dim3(kVTThreads), 0, s, keys, g, bg, A.idmask,
-                       cell, *fz);
+                       *fz);
   else
     hipLaunchKernelGGL(k_br_finish<KT>, dim3(slab_grid(bg)), dim3(kVTThreads), 0, s, keys, g, bg, A.idmask, cell);
   LSRVT_LAUNCHED();
@@ -2576,26 +2780,44 @@ int32_t vt_errors(CvtWork &W, hipStream_t s) {
   return LSRVT_OK;
 }
 
-// The site update; with `summed` the centroid sums are already in W.sums
-// (taken by the pass that produced the cells).
+// The sites' moves from the centroid sums, the cells seen through `cell`.
+template <class View>
+int32_t run_snap(const View &cell, const Geom &g, uint32_t *sites, uint32_t S, double *ds, CvtWork &W, hipStream_t s) {
+  const Sums sm{W.sums};
+  hipLaunchKernelGGL(k_snap<View>, dim3((S + 255) / 256), dim3(256), 0, s, cell, g, S, sm, sites, ds, W.moved,
+                     W.fb_list, W.fb_cnt);
+  hipLaunchKernelGGL(k_snap_near<View>, dim3(std::min<uint32_t>((S + 3) / 4, 2048)), dim3(256), 0, s, cell, g, sm, sites,
+                     ds, W.moved, W.fb_list, W.fb_cnt);
+  hipLaunchKernelGGL(k_snap_far<View>, dim3(std::min<uint32_t>(S, 512)), dim3(kSnapFarThreads), 0, s, cell, g, sm, sites,
+                     ds, W.moved, W.fb_list, W.fb_cnt);
+  LSRVT_LAUNCHED();
+  return LSRVT_OK;
+}
+
+// One site update from a C-order cell array.
 int32_t run_update(const uint32_t *cell, const Geom &g, const uint16_t *w, uint32_t *sites, uint32_t S, double *ds,
-                   CvtWork &W, hipStream_t s, bool summed = false) {
+                   CvtWork &W, hipStream_t s) {
   if (S == 0) return LSRVT_OK;
   int32_t rc;
   if ((rc = fill<uint32_t>(W.fb_cnt, 1, 0u, s))) return rc;
-  Sums sm{W.sums, W.sums + S, W.sums + 2 * (size_t)S, W.sums + 3 * (size_t)S};
-  if (!summed) {
-    if ((rc = fill<unsigned long long>(W.sums, 4 * (int64_t)S, 0ull, s))) return rc;
-    const int64_t ntiles = (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + TZ - 1) / TZ);
-    hipLaunchKernelGGL(k_centroid, dim3((unsigned)(ntiles < 65535 ? ntiles : 65535)), dim3(256), 0, s, cell, w, g, S,
-                       sm);
-  }
-  hipLaunchKernelGGL(k_snap, dim3((S + 255) / 256), dim3(256), 0, s, cell, g, S, sm, sites, ds, W.moved, W.fb_list,
-                     W.fb_cnt);
-  hipLaunchKernelGGL(k_snap_fallback, dim3(S < 1024 ? S : 1024), dim3(256), 0, s, cell, g, sm, sites, ds, W.moved,
-                     W.fb_list, W.fb_cnt);
+  if ((rc = fill<unsigned long long>(W.sums, 4 * (int64_t)S, 0ull, s))) return rc;
+  const int64_t ntiles = (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + TZ - 1) / TZ);
+  hipLaunchKernelGGL(k_centroid, dim3((unsigned)(ntiles < 65535 ? ntiles : 65535)), dim3(256), 0, s, cell, w, g, S,
+                     Sums{W.sums});
   LSRVT_LAUNCHED();
-  return LSRVT_OK;
+  return run_snap(CellView{cell, g.nx, g.ny}, g, sites, S, ds, W, s);
+}
+
+// The update inside the Lloyd loop: the sums were taken by the pass that
+// produced the cells, which are still in the pass's own arrays.
+int32_t run_loop_update(const Geom &g, uint32_t *sites, uint32_t S, CvtWork &W, const VTState &st, hipStream_t s) {
+  int32_t rc;
+  if ((rc = fill<uint32_t>(W.fb_cnt, 1, 0u, s))) return rc;
+  const VTGrid bg = vt_grid(g);
+  if (st.bricks && !st.id_bits)
+    return run_snap(KeyView<unsigned long long>{reinterpret_cast<unsigned long long *>(W.cellb), bg, ~0u}, g, sites, S,
+                    W.ds, W, s);
+  return run_snap(KeyView<uint32_t>{W.cellb, bg, st.bricks ? (1u << st.id_bits) - 1u : ~0u}, g, sites, S, W.ds, W, s);
 }
 
 int32_t begin(CvtWork &W, const Geom &g, hipStream_t s) {
@@ -2744,9 +2966,19 @@ __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 5 : 4) void kb_round(
 
 template <class KT>
 __global__ __launch_bounds__(kVTThreads) void kb_finish(const JobDev *J, int32_t t) {
+  __shared__ union {
+    FinTab slab;
+    BrickTab brick;
+  } T;
   const JobDev &j = J[blockIdx.y];
   if (t > j.iters) return;
-  d_br_finish_slabs<KT, false>(static_cast<const KT *>(j.A.key), j.g, j.A.bg, j.A.idmask, j.cell, Fuse{}, nullptr);
+  const KT *key = static_cast<const KT *>(j.A.key);
+  if (t == j.iters || j.S == 0)
+    d_br_finish_slabs<KT, false>(key, j.g, j.A.bg, j.A.idmask, j.cell, Fuse{}, nullptr);
+  else if (j.g.n / (int64_t)j.S < kSlabSites)
+    d_brick_sums(KeySource<KT>{key, j.A.idmask}, j.g, j.A.bg, Fuse{j.w, j.S, j.sums}, T.brick);
+  else
+    d_br_finish_slabs<KT, true>(key, j.g, j.A.bg, j.A.idmask, nullptr, Fuse{j.w, j.S, j.sums}, &T.slab);
 }
 
 __global__ __launch_bounds__(256) void kb_update_clear(const JobDev *J, int32_t t) {
@@ -2754,26 +2986,31 @@ __global__ __launch_bounds__(256) void kb_update_clear(const JobDev *J, int32_t 
   if (t >= j.iters) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = i0; i < 4 * (int64_t)j.S; i += stride) j.sums.M[i] = 0ull;  // M, Sx, Sy, Sz are contiguous
+  for (int64_t i = i0; i < 4 * (int64_t)j.S; i += stride) j.sums.p[i] = 0ull;
   if (i0 == 0) *j.fb_cnt = 0u;
 }
 
-__global__ __launch_bounds__(256) void kb_centroid(const JobDev *J, int32_t t) {
-  const JobDev &j = J[blockIdx.y];
-  if (t >= j.iters) return;
-  d_centroid(j.cell, j.w, j.g, j.S, j.sums);
-}
-
+template <class KT>
 __global__ void kb_snap(const JobDev *J, int32_t t) {
   const JobDev &j = J[blockIdx.y];
   if (t >= j.iters) return;
-  d_snap(j.cell, j.g, j.S, j.sums, j.sites, j.ds, j.moved, j.fb_list, j.fb_cnt);
+  d_snap(KeyView<KT>{static_cast<const KT *>(j.A.key), j.A.bg, j.A.idmask}, j.g, j.S, j.sums, j.sites, j.ds, j.moved,
+         j.fb_list, j.fb_cnt);
 }
 
-__global__ __launch_bounds__(256) void kb_snap_fallback(const JobDev *J, int32_t t) {
+template <class KT>
+__global__ __launch_bounds__(256) void kb_snap_near(const JobDev *J, int32_t t) {
   const JobDev &j = J[blockIdx.y];
   if (t >= j.iters) return;
-  d_snap_fallback(j.cell, j.g, j.sums, j.sites, j.ds, j.moved, j.fb_list, j.fb_cnt);
+  d_snap_near(KeyView<KT>{static_cast<const KT *>(j.A.key), j.A.bg, j.A.idmask}, j.g, j.sums, j.sites, j.ds, j.moved,
+              j.fb_list, j.fb_cnt);
+}
+template <class KT>
+__global__ __launch_bounds__(kSnapFarThreads) void kb_snap_far(const JobDev *J, int32_t t) {
+  const JobDev &j = J[blockIdx.y];
+  if (t >= j.iters) return;
+  d_snap_far(KeyView<KT>{static_cast<const KT *>(j.A.key), j.A.bg, j.A.idmask}, j.g, j.sums, j.sites, j.ds, j.moved,
+             j.fb_list, j.fb_cnt);
 }
 
 }  // namespace
@@ -2802,7 +3039,7 @@ struct BatchCtx {
   std::vector<JobDev> *hj;
   std::vector<CvtWork> *Ws;
   int32_t tmax;
-  int64_t max_keys, max_sites, max_tiles, max_nb, max_slabs, sum_nb;
+  int64_t max_keys, max_sites, max_nb, sum_nb;
 };
 
 // The Lloyd loops of the batch with keys KT, from the seeds.  status[i]
@@ -2827,9 +3064,8 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
   const unsigned g_clear = cap((c.max_keys + 255) / 256, 8192);
   const unsigned g_list = cap((c.max_nb + 255) / 256, 4096);
   const unsigned g_round = cap(c.sum_nb, tuning(LSRVT_TUNE_BR_GRID) > 0 ? tuning(LSRVT_TUNE_BR_GRID) : 8192);
-  const unsigned g_fin = cap(c.max_slabs, 65535);
-  const unsigned g_tiles = cap(c.max_tiles, 65535);
-  const unsigned g_fb = cap(c.max_sites, 1024);
+  const unsigned g_fin = cap((c.max_nb + 7) / 8 * 8, 65528);
+  const unsigned g_near = cap((c.max_sites + 3) / 4, 512), g_far = cap(c.max_sites, 64);
   uint32_t rounds_hint = 0;
   // kGraphRounds rounds of every job captured once and replayed as one graph launch
   VTState gs;
@@ -2865,12 +3101,12 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
       batch = kGraphRounds;
     }
     rounds_hint = r;
+    if (t < c.tmax) hipLaunchKernelGGL(kb_update_clear, dim3(g_sites, N), dim3(256), 0, s, dj, t);
     hipLaunchKernelGGL(kb_finish<KT>, dim3(g_fin, N), dim3(kVTThreads), 0, s, dj, t);
     if (t < c.tmax) {
-      hipLaunchKernelGGL(kb_update_clear, dim3(g_sites, N), dim3(256), 0, s, dj, t);
-      hipLaunchKernelGGL(kb_centroid, dim3(g_tiles, N), dim3(256), 0, s, dj, t);
-      hipLaunchKernelGGL(kb_snap, dim3(g_sites, N), dim3(256), 0, s, dj, t);
-      hipLaunchKernelGGL(kb_snap_fallback, dim3(g_fb, N), dim3(256), 0, s, dj, t);
+      hipLaunchKernelGGL(kb_snap<KT>, dim3(g_sites, N), dim3(256), 0, s, dj, t);
+      hipLaunchKernelGGL(kb_snap_near<KT>, dim3(g_near, N), dim3(256), 0, s, dj, t);
+      hipLaunchKernelGGL(kb_snap_far<KT>, dim3(g_far, N), dim3(kSnapFarThreads), 0, s, dj, t);
     }
     LSRVT_LAUNCHED();
     if (timed) {
@@ -2946,7 +3182,7 @@ int32_t cvt_batch(const CvtBatchJob *jobs, int32_t n, void *work, size_t bytes, 
     j.S = b.n_sites;
     j.iters = b.iters;
     const size_t S = b.n_sites;
-    j.sums = Sums{W.sums, W.sums + S, W.sums + 2 * S, W.sums + 3 * S};
+    j.sums = Sums{W.sums};
     j.ds = W.ds;
     j.moved = W.moved;
     j.fb_list = W.fb_list;
@@ -2956,10 +3192,7 @@ int32_t cvt_batch(const CvtBatchJob *jobs, int32_t n, void *work, size_t bytes, 
     c.max_nb = std::max<int64_t>(c.max_nb, bg.nbricks);
     c.sum_nb += bg.nbricks;
     c.max_keys = std::max<int64_t>(c.max_keys, bg.nbricks * kRows * BX);
-    c.max_slabs = std::max<int64_t>(c.max_slabs, br_slabs(bg));
     c.max_sites = std::max<int64_t>(c.max_sites, (int64_t)S);
-    c.max_tiles = std::max<int64_t>(c.max_tiles, (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) *
-                                                     ((g.nz + TZ - 1) / TZ));
   }
   c.hj = &hj;
   c.Ws = &Ws;
@@ -3047,8 +3280,7 @@ extern "C" int32_t lsrvt_cvt(const uint8_t *d_band, const uint32_t *d_comp, lsrv
   }
   VTState st;
   if ((rc = vt_prepare(d_band, g, n_sites, W, st, s))) return rc;
-  const Fuse fz{d_weights, n_sites,
-                Sums{W.sums, W.sums + n_sites, W.sums + 2 * (size_t)n_sites, W.sums + 3 * (size_t)n_sites}};
+  const Fuse fz{d_weights, n_sites, Sums{W.sums}};
   for (int32_t t = 0; t <= iters; ++t) {
     // the first pass covers every voxel; later ones only what the moved sites change.  A pass
     // followed by an update also takes the update's centroid sums.
@@ -3056,7 +3288,7 @@ extern "C" int32_t lsrvt_cvt(const uint8_t *d_band, const uint32_t *d_comp, lsrv
     if (upd && (rc = fill<unsigned long long>(W.sums, 4 * (int64_t)n_sites, 0ull, s))) return rc;
     if ((rc = vt_pass(g, d_sites, n_sites, d_cell, W, st, t > 0, s, upd ? &fz : nullptr))) return rc;
     if (t == iters) break;
-    if ((rc = run_update(d_cell, g, d_weights, d_sites, n_sites, W.ds, W, s, true))) return rc;
+    if (upd && (rc = run_loop_update(g, d_sites, n_sites, W, st, s))) return rc;
     hipLaunchKernelGGL(k_mean_ds_part, dim3(kMeanParts), dim3(256), 0, s, W.ds, n_sites, W.mean_part);
     hipLaunchKernelGGL(k_mean_ds, dim3(1), dim3(256), 0, s, W.mean_part, n_sites, W.mean + t);
     LSRVT_LAUNCHED();
