@@ -843,7 +843,7 @@ __global__ __launch_bounds__(256) void k_wake_min(const uint32_t *__restrict__ w
 // has every distance below D and is exact.
 constexpr int kBRThreads = 256;
 constexpr int kBRRow = BX + 1;  // LDS row stride (keys): padding against bank conflicts
-constexpr int kGraphRounds = 8;  // relaxation rounds per captured graph
+constexpr int kGraphRounds = 8;  // relaxation rounds of a batch per captured graph
 
 struct BRArgs {
   Geom g;
@@ -855,11 +855,11 @@ struct BRArgs {
   uint32_t idmask;                 // the id bits of a key (0xFFFFFFFF for wide keys)
   uint32_t lim32;                  // narrow keys: the smallest key whose distance is D (flagged when stored)
   uint32_t *mark;                  // [2][nbricks]: mark[r & 1][b] == r when brick b works in round r
-  uint32_t *list;                  // [nbricks] bricks of the current round
-  uint32_t *ctl;                   // [0] list length, [2] reset fused into round 1, [3] error bits
+  uint32_t *list;                  // [nbricks] bricks of the current round (large volumes)
+  uint32_t *cnt;                   // [2] length of round r's list at r & 1
+  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into round 1, [3] error bits, [13] last round
   const uint8_t *moved;            // the sites the last update moved (fused reset)
   const uint32_t *fsites;          // the sites' voxels (fused reset)
-  uint32_t *rnd;                   // the current round (advanced on the device, so rounds replay from a graph)
   uint32_t *alive;                 // [3] round alive flags (by r % 3); shared by the jobs of a batch
   uint32_t *hist;                  // [kHistLen] bricks that worked in each round
   unsigned long long *dbg;         // diagnostics (LSRVT_DEBUG_LEVELS only): processings, sweep rounds
@@ -1037,13 +1037,25 @@ __global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restr
 }
 
 
-// The bricks marked for round r, listed (one counter atomic per block on
-// *cnt, zero before the launch).
-__device__ __forceinline__ void d_br_list(BRArgs A, uint32_t r, uint32_t *cnt) {
+// How the workgroups of a round find its marked bricks.  Up to kDirectBricks
+// bricks there is one workgroup for each, which looks at its brick's mark and
+// ends if it is not set.  Larger volumes have the marks listed by a launch
+// before the round (k_br_list) and the round's workgroups stride over the
+// list, so that a round with few bricks does not start a workgroup for every
+// brick.  Loops listed and direct: 256 x 128 x 128 voxels (1024 bricks) with
+// 20 updates 10.1 and 9.3 ms, 256^3 (4096) with 20 updates 16.9 and 16.3,
+// 512 x 256 x 256 (8192) with 10 updates 8.59 and 8.45, 512 x 512 x 256
+// (16384) with 10 updates 12.45 and 12.41, 512^3 (32768) 19.6 and 20.7.
+// (Rounds that list the next round's bricks themselves, one counter atomic a
+// brick, take 542 us instead of 204 for 16000 bricks: the atomics on one word
+// queue up.)
+constexpr int64_t kDirectBricks = 16384;
+
+// The bricks marked for round r, listed (one counter atomic per block).
+__device__ __forceinline__ void d_br_list(const BRArgs &A, uint32_t r) {
   __shared__ uint32_t base_s;
   __shared__ uint32_t wcount[256 / kWave];
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
-  if (blockIdx.x == 0 && t == 0) A.alive[(r + 2) % 3] = 0u;  // round r + 2 sets its flag during round r + 1
   const uint32_t *mk = A.mark + (size_t)(r & 1) * A.bg.nbricks;
   for (int64_t b0 = (int64_t)blockIdx.x * 256; b0 < A.bg.nbricks; b0 += (int64_t)gridDim.x * 256) {
     const int64_t b = b0 + t;
@@ -1054,7 +1066,7 @@ __device__ __forceinline__ void d_br_list(BRArgs A, uint32_t r, uint32_t *cnt) {
     if (t == 0) {
       uint32_t tot = 0;
       for (int q = 0; q < 256 / kWave; ++q) tot += wcount[q];
-      base_s = tot ? atomicAdd(cnt, tot) : 0u;
+      base_s = tot ? atomicAdd(&A.cnt[r & 1], tot) : 0u;
     }
     __syncthreads();
     uint32_t off = base_s;
@@ -1063,22 +1075,7 @@ __device__ __forceinline__ void d_br_list(BRArgs A, uint32_t r, uint32_t *cnt) {
     __syncthreads();
   }
 }
-// Rounds are replayed from a graph of kGraphRounds rounds: the round at
-// position i of a replay is *rnd + 1 + i, and the graph's last kernel
-// advances *rnd by kGraphRounds.  Round r's list length is counted in
-// ctl[0] (odd r) or ctl[12] (even r); round r empties the counter of round
-// r + 1 (nobody else touches it while round r runs).
-__device__ __forceinline__ uint32_t *br_count(const BRArgs &A, uint32_t r) {
-  return (r & 1u) ? &A.ctl[0] : &A.ctl[12];
-}
-__global__ void k_br_advance(BRArgs A) {
-  if (threadIdx.x == 0) *A.rnd += (uint32_t)kGraphRounds;
-}
-__global__ __launch_bounds__(256) void k_br_list(BRArgs A, int32_t i) {
-  const uint32_t r = *A.rnd + 1u + (uint32_t)i;
-  d_br_list(A, r, br_count(A, r));
-}
-
+__global__ __launch_bounds__(256) void k_br_list(BRArgs A, uint32_t r) { d_br_list(A, r); }
 
 __device__ __forceinline__ int br_at(int lx, int row) { return row * kBRRow + lx; }
 
@@ -1357,17 +1354,27 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
 }
 
 template <class KT>
-__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_round(BRArgs A, int32_t i) {
+__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_round(BRArgs A, uint32_t r) {
   __shared__ BRLds<KT> L;
-  const uint32_t r = *A.rnd + 1u + (uint32_t)i;
-  const uint32_t count = *br_count(A, r);
+  const uint32_t count = A.cnt[r & 1];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    A.hist[r % kHistLen] = count;  // bricks that work in round r
-    *br_count(A, r + 1u) = 0u;
+    A.alive[(r + 2) % 3] = 0u;  // round r + 1 sets it
+    A.cnt[(r + 1) & 1] = 0u;    // the list of round r + 1 counts in it
+    A.hist[r % kHistLen] = count;
+    if (count) A.ctl[13] = r;   // the last round that had work
   }
   for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) br_process<KT>(A, A.list[item], r, L);
 }
 
+// The same round with one workgroup for every brick.
+template <class KT>
+__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_round_all(BRArgs A, uint32_t r) {
+  __shared__ BRLds<KT> L;
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.alive[(r + 2) % 3] = 0u;  // round r + 1 sets it
+  if (A.mark[(size_t)(r & 1) * A.bg.nbricks + blockIdx.x] != r) return;
+  if (threadIdx.x == 0) A.ctl[13] = r;  // the last round that had work
+  br_process<KT>(A, blockIdx.x, r, L);
+}
 
 // ----------------------------------------------------------------------------
 // update
@@ -2116,6 +2123,7 @@ void cvt_layout(A &a, const Geom &g, uint32_t S, int32_t iters, CvtWork *W) {
   size_t s1 = S ? S : 1;
   const bool inc = iters > 0;  // incremental passes follow the first one
   auto eq = a.template take<uint32_t>(nb * kRows * 3);
+  // the search state of a pass, cleared together (clear_pass, run_br_k)
   auto fr = a.template take<uint16_t>(2 * nb * kRows);
   auto vis = a.template take<uint16_t>(nb * kRows);
   auto xf = a.template take<unsigned long long>(2 * nb * 8);
@@ -2216,44 +2224,47 @@ int32_t capture_rounds(hipGraphExec_t *exec, F launch_round) {
   return LSRVT_OK;
 }
 
+// An executable graph, destroyed with its owner.
+struct RoundGraph {
+  hipGraphExec_t exec = nullptr;
+  RoundGraph() = default;
+  RoundGraph(const RoundGraph &) = delete;
+  RoundGraph &operator=(const RoundGraph &) = delete;
+  ~RoundGraph() {
+    if (exec) (void)hipGraphExecDestroy(exec);
+  }
+};
+
 // Driver state of one Lloyd run: the levels or rounds of the previous
-// passes, which size the first batch of launches of the next one, and the
-// captured graphs of relaxation rounds.
+// passes, which size the first batch of launches of the next one.
 struct VTState {
   uint32_t levels = 0;      // levels of the last full pass
   uint32_t inc_levels = 0;  // levels of the first run of the last incremental pass
   uint32_t br_rounds = 0;   // rounds of the last full brick relaxation pass
   uint32_t br_rounds_inc = 0;  // rounds of the last incremental one
-  hipGraphExec_t br_graph = nullptr;  // kGraphRounds relaxation rounds of this call's workspace (narrow keys)
-  hipGraphExec_t br_graph_w = nullptr;  // the same with wide keys
   bool bricks = false;      // passes by brick relaxation (else by level search)
   bool keys_set = false;    // the key width of the brick relaxation is chosen at its first pass
   uint32_t id_bits = 0;     // narrow keys: the id field's bits; 0: wide keys
-  VTState() = default;
-  VTState(const VTState &) = delete;
-  VTState &operator=(const VTState &) = delete;
-  ~VTState() {
-    if (br_graph) hipGraphExecDestroy(br_graph);
-    if (br_graph_w) hipGraphExecDestroy(br_graph_w);
-  }
 };
 
 // Which schedule computes the Voronoi passes: the level-synchronous search
 // or the brick relaxation (both give the same regions bit for bit).  The
-// choice is made per host thread (lsrvt_set_vt_engine); by default, the
-// brick relaxation for volumes with many voxels per site (wide cells: many
-// levels per pass, few relaxation rounds) and the level search otherwise.
+// choice is made per host thread (lsrvt_set_vt_engine); by default the brick
+// relaxation, which is the faster one whatever the volume and the cells.
+// Levels against bricks: 8^3 with a site for every voxel or two, 10 updates,
+// 1.52 and 1.18 ms; 25^3 with a site a voxel, one pass, 0.165 and 0.138; 64^3,
+// 1.6 voxels a site, 10 updates, 1.80 and 1.41; one pass of 192 x 96 x 96 1.6
+// and 0.67; 379 x 251 x 147 with 20 updates 27.3 and 12.3; 512 x 256 x 256
+// flame block with 10 updates 52.9 and 8.4.
 enum class VTEngine { Auto = 0, Levels = 1, Bricks = 2 };
 
 thread_local VTEngine t_engine = VTEngine::Auto;
 
-VTEngine vt_engine(const Geom &g, uint32_t S) {
+VTEngine vt_engine() {
   VTEngine e = t_engine;
   if (e == VTEngine::Auto) {
     static const char *env = getenv("LSRVT_VT_ENGINE");
-    if (env && env[0] == 'l') return VTEngine::Levels;
-    if (env && env[0] == 'b') return VTEngine::Bricks;
-    e = (S == 0 || g.n / (int64_t)S >= 1024) ? VTEngine::Bricks : VTEngine::Levels;
+    e = env && env[0] == 'l' ? VTEngine::Levels : VTEngine::Bricks;
   }
   return e;
 }
@@ -2354,7 +2365,7 @@ unsigned finish_grid(const VTGrid &bg) {
 // The schedule of the call's passes, and the edge masks of the bands in its form.
 int32_t vt_prepare(const uint8_t *band, const Geom &g, uint32_t S, CvtWork &W, VTState &st, hipStream_t s) {
   VTGrid bg = vt_grid(g);
-  st.bricks = vt_engine(g, S) == VTEngine::Bricks;
+  st.bricks = vt_engine() == VTEngine::Bricks;
   if (st.bricks) {
     hipLaunchKernelGGL(k_br_masks, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, band, g, bg, W.eq);
     LSRVT_LAUNCHED();
@@ -2392,16 +2403,11 @@ BFSArgs bfs_args(const Geom &g, CvtWork &W) {
 }
 
 // Clears the per-pass search state (frontiers, reached rows, marks, flags).
-int32_t clear_pass(const VTGrid &bg, CvtWork &W, hipStream_t s) {
-  int32_t rc;
-  // 16-bit and 64-bit arrays are cleared as 32-bit words (even lengths)
-  if ((rc = fill<uint32_t>(reinterpret_cast<uint32_t *>(W.fr), bg.nbricks * kRows, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(reinterpret_cast<uint32_t *>(W.vis), bg.nbricks * kRows / 2, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(reinterpret_cast<uint32_t *>(W.xf), 2 * bg.nbricks * 16, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(reinterpret_cast<uint32_t *>(W.yf), bg.nbricks * 32, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(W.act, 2 * bg.nbricks, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(W.ctl, 3, 0u, s))) return rc;
-  return LSRVT_OK;
+int32_t clear_pass(CvtWork &W, hipStream_t s) {
+  // fr, vis, xf, yf, act and ctl follow each other in the workspace (cvt_layout),
+  // the last up to its level flags ctl[0 .. 2]: one launch
+  uint32_t *from = reinterpret_cast<uint32_t *>(W.fr);
+  return fill<uint32_t>(from, W.ctl + 3 - from, 0u, s);
 }
 
 // Launches of the level kernel from level 1 on, enqueued in batches (the
@@ -2494,7 +2500,7 @@ int32_t run_vt(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell,
                hipStream_t s, const Fuse *fz = nullptr) {
   VTGrid bg = vt_grid(g);
   int32_t rc;
-  if ((rc = clear_pass(bg, W, s))) return rc;
+  if ((rc = clear_pass(W, s))) return rc;
   BFSArgs A = bfs_args(g, W);
   if (S) {
     hipLaunchKernelGGL(k_sites_clear, dim3((S + 255) / 256), dim3(256), 0, s, sites, S, A);
@@ -2527,7 +2533,7 @@ int32_t run_vt_inc(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *c
   if (!W.inv || S == 0) return run_vt(g, sites, S, cell, W, st, s, fz);
   VTGrid bg = vt_grid(g);
   int32_t rc;
-  if ((rc = clear_pass(bg, W, s))) return rc;
+  if ((rc = clear_pass(W, s))) return rc;
   BFSArgs A = bfs_args(g, W);
   const int64_t slots = bg.nbricks * kRows * BX;
   const unsigned rgrid = (unsigned)std::min<int64_t>((slots + kVTThreads - 1) / kVTThreads, 65535);
@@ -2611,7 +2617,7 @@ BRArgs br_args(const Geom &g, CvtWork &W, uint32_t id_bits) {
   A.xface = W.xface;
   A.mark = W.act;
   A.list = W.brlist;
-  A.rnd = W.ctl + 7;
+  A.cnt = W.ctl + 14;
   A.ctl = W.ctl;
   A.alive = W.ctl + 4;
   A.hist = W.hist;
@@ -2636,9 +2642,9 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   constexpr KT kInf = BRKey<KT>::inf;
   int32_t rc;
   const int64_t nkeys = bg.nbricks * kRows * BX;
-  if ((rc = fill<uint32_t>(W.act, 2 * bg.nbricks, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(W.ctl, 3, 0u, s))) return rc;
-  if ((rc = fill<uint32_t>(W.ctl + 4, 4, 0u, s))) return rc;  // alive flags and the round counter
+  // marks (act and ctl follow each other), flags, the last round and the list lengths
+  if ((rc = fill<uint32_t>(W.act, W.ctl + 3 - W.act, 0u, s))) return rc;
+  if ((rc = fill<uint32_t>(W.ctl + 4, 12, 0u, s))) return rc;
   if (!inc) {
     if ((rc = fill<KT>(static_cast<KT *>(A.key), nkeys, kInf, s))) return rc;
     if ((rc = fill<KT>(static_cast<KT *>(A.xface), bg.nbricks * 512, kInf, s))) return rc;
@@ -2666,34 +2672,34 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   }
   const unsigned lgrid = (unsigned)std::min<int64_t>((bg.nbricks + 255) / 256, 4096);
   const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
+  const bool direct = tg == 0 && !A.dbg && bg.nbricks <= kDirectBricks;
   const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 8192);
-  // kGraphRounds rounds (two launches each, and one that advances the
-  // round base) captured once per call and replayed as one graph launch
-  hipGraphExec_t &graph = sizeof(KT) == 4 ? st.br_graph : st.br_graph_w;
-  if (!graph) {
-    rc = capture_rounds(&graph, [&](hipStream_t cs, int i) -> int32_t {
-      hipLaunchKernelGGL(k_br_list, dim3(lgrid), dim3(256), 0, cs, A, (int32_t)i);
-      hipLaunchKernelGGL(k_br_round<KT>, dim3(rgrid), dim3(kBRThreads), 0, cs, A, (int32_t)i);
-      if (i == kGraphRounds - 1) hipLaunchKernelGGL(k_br_advance, dim3(1), dim3(64), 0, cs, A);
-      LSRVT_LAUNCHED();
-      return LSRVT_OK;
-    });
-    if (rc) return rc;
-  }
   uint32_t r = 0;
+  // Rounds are launched as plain kernels, one each (a captured graph of eight
+  // rounds replayed is slower: 14.0 against 13.4 ms for 379 x 251 x 147 voxels
+  // and 20 updates, 0.79 against 0.71 ms for one pass of 192 x 96 x 96, whose
+  // graph is built for it alone), and a pass rarely needs more than the one
+  // before it plus one.
   uint32_t &hint = inc ? st.br_rounds_inc : st.br_rounds;
-  int batch = hint ? (int)hint : inc ? 2 * kGraphRounds : kGraphRounds;
-  uint32_t c[8];
+  int batch = hint ? (int)hint + 1 : 12;
+  uint32_t c[14];
   const int64_t max_rounds = 4 * g.n + 8;
   while (true) {
     const bool timed = timer().on;
     std::pair<hipEvent_t, hipEvent_t> ev;
-    const int graphs = (batch + kGraphRounds - 1) / kGraphRounds;
     if (timed && (rc = timed_begin(s, ev))) return rc;
-    for (int i = 0; i < graphs; ++i) LSRVT_HIP(hipGraphLaunch(graph, s));
-    r += (uint32_t)(graphs * kGraphRounds);
-    if (timed && (rc = timed_end(s, ev, (uint64_t)graphs * kGraphRounds))) return rc;
-    if ((rc = read_words(W.ctl, 8, c, s))) return rc;
+    for (int i = 0; i < batch; ++i) {
+      ++r;
+      if (direct) {
+        hipLaunchKernelGGL(k_br_round_all<KT>, dim3((unsigned)bg.nbricks), dim3(kBRThreads), 0, s, A, r);
+      } else {
+        hipLaunchKernelGGL(k_br_list, dim3(lgrid), dim3(256), 0, s, A, r);
+        hipLaunchKernelGGL(k_br_round<KT>, dim3(rgrid), dim3(kBRThreads), 0, s, A, r);
+      }
+    }
+    LSRVT_LAUNCHED();
+    if (timed && (rc = timed_end(s, ev, (uint64_t)batch))) return rc;
+    if ((rc = read_words(W.ctl, 14, c, s))) return rc;
     if (c[3] & 1u) return LSRVT_EINVAL;
     if (c[3] & ~4u) return LSRVT_EDEVICE;
     if (c[3] & 4u) {  // a narrow key reached the largest exact distance
@@ -2702,24 +2708,21 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     }
     if (c[4 + (r + 1) % 3] == 0) break;
     if ((int64_t)r > max_rounds) return LSRVT_EDEVICE;
-    batch = kGraphRounds;
+    batch = 4;
   }
   // the rounds that had work size the first batch of the next pass
-  const uint32_t nl = std::min<uint32_t>(r + 1, kHistLen);
-  std::vector<uint32_t> h(nl, 0);
-  LSRVT_HIP(hipMemcpyAsync(h.data(), W.hist, sizeof(uint32_t) * nl, hipMemcpyDeviceToHost, s));
-  LSRVT_HIP(hipStreamSynchronize(s));
-  uint32_t worked = 0;
-  while (worked + 1 < nl && h[worked + 1]) ++worked;
-  hint = worked;
+  hint = c[13];
   static const bool debug_levels = getenv("LSRVT_DEBUG_LEVELS") != nullptr;
   if (debug_levels) {
     unsigned long long d[2];
     LSRVT_HIP(hipMemcpyAsync(d, W.ctl + 8, sizeof(d), hipMemcpyDeviceToHost, s));
     LSRVT_HIP(hipStreamSynchronize(s));
-    if ((rc = fill<uint32_t>(W.ctl + 8, 4, 0u, s))) return rc;
     fprintf(stderr, "[lsrvt] br %s processings=%llu sweep rounds=%llu\n", inc ? "inc" : "full", d[0], d[1]);
-    fprintf(stderr, "[lsrvt] br %s rounds=%u launched=%u bricks per round:", inc ? "inc" : "full", worked, r);
+    const uint32_t nl = std::min<uint32_t>(r + 1, kHistLen);
+    std::vector<uint32_t> h(nl, 0);
+    LSRVT_HIP(hipMemcpyAsync(h.data(), W.hist, sizeof(uint32_t) * nl, hipMemcpyDeviceToHost, s));
+    LSRVT_HIP(hipStreamSynchronize(s));
+    fprintf(stderr, "[lsrvt] br %s rounds=%u launched=%u bricks per round:", inc ? "inc" : "full", hint, r);
     for (uint32_t i = 1; i < nl; ++i) fprintf(stderr, " %u", h[i]);
     fprintf(stderr, "\n");
   }
@@ -2863,20 +2866,20 @@ __global__ void kb_init_sites(const JobDev *J) {
   d_init_sites(j.seeds, j.S, j.comp, j.g, j.sites, j.site_comp, j.A.ctl + 3);
 }
 
-// Start of pass t: marks and list counters cleared, and for a full pass
-// (t = 0) every key and packed face unreached.  Block (0, 0) clears the
-// shared round flags and round counter and records the pass (the shared
-// words after the flags: [3] round, [4] pass, read by the graph-replayed
-// round kernels).
+// Start of pass t: marks and list lengths cleared (of every job: one that has
+// stopped keeps an empty list), and for a full pass (t = 0) every key and
+// packed face unreached.  Block (0, 0) clears the shared round flags and round
+// counter and records the pass (the shared words after the flags: [3] round,
+// [4] pass, read by the graph-replayed round kernels).
 template <class KT>
 __global__ __launch_bounds__(256) void kb_pass_clear(const JobDev *J, int32_t t) {
   const JobDev &j = J[blockIdx.y];
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 5) j.A.alive[threadIdx.x] = threadIdx.x == 4 ? (uint32_t)t : 0u;
+  if (blockIdx.x == 0 && threadIdx.x < 2) j.A.cnt[threadIdx.x] = 0u;
   if (t > j.iters) return;
   const int64_t nb = j.A.bg.nbricks, stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t i = i0; i < 2 * nb; i += stride) j.A.mark[i] = 0u;
-  if (i0 == 0) j.A.ctl[0] = 0u;
   if (t == 0) {
     KT *key = static_cast<KT *>(j.A.key), *xface = static_cast<KT *>(j.A.xface);
     for (int64_t i = i0; i < nb * kRows * BX; i += stride) key[i] = BRKey<KT>::inf;
@@ -2898,35 +2901,29 @@ __global__ void kb_sites(const JobDev *J, int32_t t) {
   d_br_sites<KT>(j.sites, j.S, j.A);
 }
 
-// Start of a round: every job's list emptied, the shared round advanced.
-__global__ void kb_round_prep(const JobDev *J) {
-  if (threadIdx.x == 0) {
-    const JobDev &j = J[blockIdx.y];
-    j.A.ctl[0] = 0u;
-    if (blockIdx.y == 0) j.A.alive[3] += 1u;
-  }
-}
-
+// The shared round advances and every job's marked bricks are listed; the
+// flag that round r + 1 will set and the lengths it will count are emptied by
+// kb_offsets and the first thread of kb_round.
 __global__ __launch_bounds__(256) void kb_list(const JobDev *J) {
   const JobDev &j = J[blockIdx.y];
   if ((int32_t)j.A.alive[4] > j.iters) return;
-  d_br_list(j.A, j.A.alive[3], &j.A.ctl[0]);
+  d_br_list(j.A, j.A.alive[3] + 1u);
 }
 
 // The round's work list of the whole batch: the jobs' lists back to back,
 // job j's at off[j] .. off[j + 1] (an exclusive prefix sum of the list
-// counts, by one workgroup).  A job that has stopped taking part has an empty
+// lengths, by one workgroup).  A job that has stopped taking part has an empty
 // list.
 __global__ __launch_bounds__(1024) void kb_offsets(const JobDev *J, int32_t n, uint32_t *off) {
   __shared__ uint32_t part[1024];
   const int t = threadIdx.x;
   const int32_t per = (n + 1023) / 1024, a = t * per, e = a + per < n ? a + per : n;
-  const uint32_t r = J[0].A.alive[3];
+  uint32_t *alive = J[0].A.alive;
+  const uint32_t r = alive[3] + 1u;
   uint32_t sum = 0;
   for (int32_t i = a; i < e; ++i) {
-    const uint32_t c = J[i].A.ctl[0];
-    J[i].A.hist[r % kHistLen] = c;
-    sum += c;
+    sum += J[i].A.cnt[r & 1];
+    J[i].A.cnt[(r + 1) & 1] = 0u;
   }
   part[t] = sum;
   __syncthreads();
@@ -2939,9 +2936,13 @@ __global__ __launch_bounds__(1024) void kb_offsets(const JobDev *J, int32_t n, u
   uint32_t run = part[t] - sum;
   for (int32_t i = a; i < e; ++i) {
     off[i] = run;
-    run += J[i].A.ctl[0];
+    run += J[i].A.cnt[r & 1];
   }
-  if (t == 1023) off[n] = part[1023];
+  if (t == 1023) {
+    off[n] = part[1023];
+    alive[3] = r;
+    alive[(r + 2) % 3] = 0u;
+  }
 }
 
 // One relaxation round of the whole batch: the workgroups stride over the
@@ -3068,10 +3069,9 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
   const unsigned g_near = cap((c.max_sites + 3) / 4, 512), g_far = cap(c.max_sites, 64);
   uint32_t rounds_hint = 0;
   // kGraphRounds rounds of every job captured once and replayed as one graph launch
-  VTState gs;
+  RoundGraph gs;
   uint32_t *offs = c.offs;
-  rc = capture_rounds(&gs.br_graph, [&](hipStream_t cs, int) -> int32_t {
-    hipLaunchKernelGGL(kb_round_prep, dim3(1, N), dim3(64), 0, cs, dj);
+  rc = capture_rounds(&gs.exec, [&](hipStream_t cs, int) -> int32_t {
     hipLaunchKernelGGL(kb_list, dim3(g_list, N), dim3(256), 0, cs, dj);
     hipLaunchKernelGGL(kb_offsets, dim3(1), dim3(1024), 0, cs, dj, n, offs);
     hipLaunchKernelGGL(kb_round<KT>, dim3(g_round), dim3(kBRThreads), 0, cs, dj, n, (const uint32_t *)offs);
@@ -3092,7 +3092,7 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
       std::pair<hipEvent_t, hipEvent_t> ev;
       const int graphs = (batch + kGraphRounds - 1) / kGraphRounds;
       if (timed && (rc = timed_begin(s, ev))) return rc;
-      for (int k = 0; k < graphs; ++k) LSRVT_HIP(hipGraphLaunch(gs.br_graph, s));
+      for (int k = 0; k < graphs; ++k) LSRVT_HIP(hipGraphLaunch(gs.exec, s));
       r += (uint32_t)(graphs * kGraphRounds);
       if (timed && (rc = timed_end(s, ev, (uint64_t)graphs * kGraphRounds))) return rc;
       if ((rc = read_words(c.alive, 3, w, s))) return rc;

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
                                    (33, 17, 34)])
 @pytest.mark.parametrize("n_bands", [1, 2, 5])
 @pytest.mark.parametrize("bits", [0, 64])
-def test_bricks_at_brick_edges(shape, n_bands, bits):
+@pytest.mark.parametrize("grid", [0, 1024])  # a workgroup for every brick; the marked bricks listed
+def test_bricks_at_brick_edges(shape, n_bands, bits, grid):
     rng = np.random.default_rng(sum(shape) + n_bands)
     n = int(np.prod(shape))
     band = rng.integers(0, n_bands, size=shape).astype(np.uint8)
@@ -25,16 +26,18 @@ def test_bricks_at_brick_edges(shape, n_bands, bits):
     cc = oracle.components(band, n_bands)
     seeds = rng.choice(n, size=max(1, min(n, n // 300 + 2)), replace=False).astype(np.uint32)
     w = rng.integers(0, 65536, size=shape).astype(np.uint16)
-    banner(f"brick edges {shape} bands={n_bands} bits={bits}")
+    banner(f"brick edges {shape} bands={n_bands} bits={bits} grid={grid}")
     b, c, q, wd = dev(band), dev(cc.comp), dev(seeds), dev(w)
     prev_e = L.lsrvt_set_vt_engine(L.VT_BRICKS)
     prev_k = L.lsrvt_set_tuning(L.TUNE_KEY_BITS, bits)
+    prev_g = L.lsrvt_set_tuning(L.TUNE_BR_GRID, grid)
     try:
         cell = L.lsrvt_vt(b, q)
         r = L.lsrvt_cvt(b, c, q, wd, 3)
     finally:
         L.lsrvt_set_vt_engine(prev_e)
         L.lsrvt_set_tuning(L.TUNE_KEY_BITS, prev_k)
+        L.lsrvt_set_tuning(L.TUNE_BR_GRID, prev_g)
     assert np.array_equal(host(cell, np.uint32), oracle.vt(cc.comp, seeds))
     want = oracle.cvt(cc.comp, seeds, w, 3)
     assert np.array_equal(host(r.cell, np.uint32), want.cell)
