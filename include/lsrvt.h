@@ -466,7 +466,7 @@ int32_t lsrvt_seed(const uint32_t *d_comp, const uint32_t *d_comp_first, lsrvt_d
  * LSRVT_EINVAL when an anchor is outside the volume or its component or
  * does not hold its site; LSRVT_ELIMIT for S >= 2^31 or a stage that has not
  * converged after 100000 sweeps.  Synchronises the stream after every batch
- * of 8 sweeps.  Workspace: lsrvt_los_workspace(dims, n_sites).
+ * of sweeps.  Workspace: lsrvt_los_workspace(dims, n_sites).
  *
  * lsrvt_los_update: M = sum m_v and S = sum m_v x_phi(v) over each cell
  * (exact uint64; m_v the uint16 weight, 1 without weights); the target is

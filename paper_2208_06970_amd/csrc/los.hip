@@ -29,12 +29,34 @@ namespace {
 
 constexpr uint32_t kSite = LSRVT_LOS_SITE;
 constexpr int kLosThreads = 256;
-constexpr int kSweepBatch = 8;
+constexpr int kSweepBatch = 16;  // sweeps launched before the host looks, when it has no better guess
 constexpr int32_t kMaxSweeps = 100000;
 constexpr int kPhiRounds = 40;
 constexpr double kShorter = 1.0 - 0x1p-40;
 constexpr double kNear = 1.0 + 0x1p-40;
-constexpr int kMarkPer = 16;  // voxels per thread in mark and apply (a chunk: 4096 voxels)
+constexpr int kPhiHops = 32;
+constexpr int kRadius = 31;  // the largest cube radius (plus one) kept per voxel (5 bits)
+constexpr int kSpec = 4;     // crossings of a ray looked at together
+
+// A tile of a sweep: 32 x 4 x 4 voxels, one wave, one word of each bit plane
+// per row.  Tiles of 512 voxels give a 3 Mvoxel volume about six waves for
+// every SIMD, which its chains of dependent loads need.
+constexpr int kTX = 32, kTY = 4, kTZ = 4;
+constexpr int kTWords = kTY * kTZ;
+constexpr int kLanes = kWave / kTWords;  // lanes that hold a word of the tile
+
+// Division of u < 2^31 by a fixed d >= 1 as a multiplication: with
+// 2^(l - 1) < d <= 2^l and m = ceil(2^(31 + l) / d), m d exceeds 2^(31 + l) by
+// less than d <= 2^l, so u m / 2^(31 + l) is above u / d by less than 1 / d.
+struct Div {
+  uint32_t m, s;
+};
+Div make_div(uint32_t d) {
+  uint32_t l = 0;
+  while ((1ull << l) < d) ++l;
+  return Div{(uint32_t)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
+}
+__device__ __forceinline__ uint32_t quot(uint32_t u, Div d) { return (uint32_t)(((uint64_t)u * d.m) >> d.s); }
 
 struct LosArgs {
   const uint32_t *comp;
@@ -46,14 +68,25 @@ struct LosArgs {
   uint32_t *src;          // [N] sources (the caller's output)
   double *pd;             // [N] proposed lengths
   uint32_t *ps;           // [N] proposed sources
-  uint8_t *chg;           // [N] changed in this sweep
-  uint8_t *flag;          // [N] v or its source changed in the sweep before
-  uint8_t *chunk_any;     // [chunks] some flag of the chunk is set
-  uint32_t *list;         // [N] voxels to evaluate in this sweep
-  uint32_t *count;        // length of list
-  uint32_t *alive;        // [kSweepBatch] a voxel changed in sweep j of the batch
+  uint32_t *nbh;          // [N] the neighbourhood word (k_los_nbh)
+  uint8_t *blk;           // [N] bit i: the ray to the source of face neighbour i is blocked
+  uint32_t *chg;          // bit plane: changed in this sweep
+  uint32_t *flag;         // bit plane: v or its source changed in the sweep before
+  uint32_t *last;         // the last sweep of the stage that changed a voxel (1-based)
   uint32_t *err;
+  Div dx, dy;             // division by g.nx, g.ny
+  int32_t pw;             // words of a row of a bit plane
+  int32_t tx, ty;         // tiles along x, y
+  uint32_t ntiles;
 };
+
+__device__ __forceinline__ void xyz(uint32_t u, const LosArgs &A, int32_t &x, int32_t &y, int32_t &z) {
+  const uint32_t row = quot(u, A.dx);
+  const uint32_t zz = quot(row, A.dy);
+  x = (int32_t)(u - row * (uint32_t)A.g.nx);
+  y = (int32_t)(row - zz * (uint32_t)A.g.ny);
+  z = (int32_t)zz;
+}
 
 // Coordinates of voxel v (v < 2^31, so 32-bit division is exact).
 __device__ __forceinline__ void xyz(int64_t v, const Geom &g, int32_t &x, int32_t &y, int32_t &z) {
@@ -75,41 +108,103 @@ __device__ __forceinline__ double len_site(int32_t x, int32_t y, int32_t z, cons
   return sqrt((double)(dx * dx + dy * dy + dz * dz)) / 256.0;
 }
 
+// The neighbourhood word of a voxel: bit b = (dx + 1) + 3 (dy + 1) + 9 (dz + 1),
+// less one past the middle, says that the voxel at (dx, dy, dz) is in the same
+// component (26 bits); the top bits hold r, one more than the radius of the
+// largest cube around the voxel that lies in its component (the part of it in
+// the volume).
+constexpr int kNbhBits = 26;
+__device__ __forceinline__ uint32_t nbh_bit(int32_t dx, int32_t dy, int32_t dz) {
+  const int32_t b = 13 + dx + 3 * dy + 9 * dz;
+  return (uint32_t)(b > 13 ? b - 1 : b);
+}
+
 // True when every voxel whose closed cube meets the segment between the
-// centres of a and b belongs to component c.  Plane crossings of axis i
+// centres of a and b belongs to a's component.  Plane crossings of axis i
 // happen at t = (2k + 1) / (2 L_i); they are ordered by cross-multiplication
 // ((2k + 1) L_j < 2^31 under the extent limit), and at a crossing shared by
 // several axes every combination of their steps is touched.  The walk stays
 // in the bounding box of a and b, so every read is in bounds.
-__device__ bool ray_clear(const uint32_t *__restrict__ comp, const Geom &g, int32_t ax, int32_t ay, int32_t az,
-                          int32_t bx, int32_t by, int32_t bz, uint32_t c) {
-  const uint32_t L[3] = {(uint32_t)abs(bx - ax), (uint32_t)abs(by - ay), (uint32_t)abs(bz - az)};
-  const int64_t stp[3] = {bx > ax ? 1 : -1, (by > ay ? 1 : -1) * (int64_t)g.nx,
-                          (bz > az ? 1 : -1) * (int64_t)g.nx * g.ny};
-  uint32_t m[3] = {0, 0, 0};
-  int64_t cur = ax + (int64_t)g.nx * (ay + (int64_t)g.ny * az);
+//
+// A ray is a chain of dependent loads, and nothing else bounds it, so the walk
+// needs few: one word of a voxel tells all that a crossing from it touches; the
+// words of the next kSpec voxels of the path are loaded together; and the
+// walk leaps.  Every voxel within K = r - 1 of the current one is in the
+// component, so a box that reaches no further needs no walk at all, and
+// otherwise the next K crossings of the longest axis touch nothing else (the
+// other axes cross at most as often in between, since their crossings lie no
+// closer together).
+__device__ __forceinline__ bool ray_clear(const LosArgs &A, int32_t ax, int32_t ay, int32_t az, int32_t bx, int32_t by,
+                                          int32_t bz) {
+  const uint32_t Lx = (uint32_t)abs(bx - ax), Ly = (uint32_t)abs(by - ay), Lz = (uint32_t)abs(bz - az);
+  const int32_t nx = A.g.nx, nxy = A.g.nx * A.g.ny;
+  const int32_t dx = bx > ax ? 1 : -1, dy = by > ay ? 1 : -1, dz = bz > az ? 1 : -1;
+  const int32_t sx = dx, sy = dy * nx, sz = dz * nxy;
+  const uint32_t LM = max(Lx, max(Ly, Lz));
+  const int32_t start = ax + nx * ay + nxy * az;
+  uint32_t mx = 0, my = 0, mz = 0;
+  int32_t cur = start;
   for (;;) {
-    int best = -1;
+    // the next kSpec crossings: the voxel before each, and what it must hold
+    uint32_t at[kSpec], must[kSpec];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      if (m[i] >= L[i]) continue;
-      if (best < 0 || (2 * m[i] + 1) * L[best] < (2 * m[best] + 1) * L[i]) best = i;
+    for (int k = 0; k < kSpec; ++k) {
+      at[k] = (uint32_t)cur;
+      // the smallest (2 m + 1) / L over the axes still to cross
+      const bool wx = mx < Lx, wy = my < Ly, wz = mz < Lz;
+      const uint32_t ox = 2 * mx + 1, oy = 2 * my + 1, oz = 2 * mz + 1;
+      uint32_t bo = ox, bL = wx ? Lx : 0;
+      if (wy && (!bL || oy * bL < bo * Ly)) { bo = oy; bL = Ly; }
+      if (wz && (!bL || oz * bL < bo * Lz)) { bo = oz; bL = Lz; }
+      const bool cx = wx && ox * bL == bo * Lx, cy = wy && oy * bL == bo * Ly, cz = wz && oz * bL == bo * Lz;
+      uint32_t m = 0;
+      if (cx) m |= 1u << nbh_bit(dx, 0, 0);
+      if (cy) m |= 1u << nbh_bit(0, dy, 0);
+      if (cz) m |= 1u << nbh_bit(0, 0, dz);
+      if (cx && cy) m |= 1u << nbh_bit(dx, dy, 0);
+      if (cx && cz) m |= 1u << nbh_bit(dx, 0, dz);
+      if (cy && cz) m |= 1u << nbh_bit(0, dy, dz);
+      if (cx && cy && cz) m |= 1u << nbh_bit(dx, dy, dz);
+      must[k] = m;
+      if (k + 1 < kSpec) {
+        mx += cx;
+        my += cy;
+        mz += cz;
+        cur += (cx ? sx : 0) + (cy ? sy : 0) + (cz ? sz : 0);
+      }
     }
-    if (best < 0) return true;
-    uint32_t tied = 0;
+    uint32_t w[kSpec], r = 0;
+    bool ok = true;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-      if (m[i] < L[i] && (2 * m[i] + 1) * L[best] == (2 * m[best] + 1) * L[i]) tied |= 1u << i;
-    for (uint32_t sub = tied; sub; sub = (sub - 1) & tied) {
-      int64_t q = cur;
-      if (sub & 1u) q += stp[0];
-      if (sub & 2u) q += stp[1];
-      if (sub & 4u) q += stp[2];
-      if (comp[q] != c) return false;
+    for (int k = 0; k < kSpec; ++k) w[k] = A.nbh[at[k]];
+#pragma unroll
+    for (int k = 0; k < kSpec; ++k) {
+      r = w[k] >> kNbhBits;
+      if (k + 1 < kSpec) ok = ok && (w[k] & must[k]) == must[k];
     }
-    if (tied & 1u) { cur += stp[0]; m[0] += 1; }
-    if (tied & 2u) { cur += stp[1]; m[1] += 1; }
-    if (tied & 4u) { cur += stp[2]; m[2] += 1; }
+    if ((w[0] >> kNbhBits) > LM) return true;  // (at the start: the whole box)
+    if (!ok) return false;
+    // now at the last of them
+    const uint32_t rem = max(Lx - mx, max(Ly - my, Lz - mz));
+    if (r > rem) return true;
+    if (r > 1) {
+      // the state right after the K-th next crossing of the longest axis
+      const uint32_t M = (Lx == LM ? mx : Ly == LM ? my : mz) + r - 1;  // its crossings so far (M <= LM)
+      const uint32_t t = 2 * M - 1;                                     // t / (2 LM)
+      mx = Lx == LM ? M : (t * Lx + LM) / (2 * LM);
+      my = Ly == LM ? M : (t * Ly + LM) / (2 * LM);
+      mz = Lz == LM ? M : (t * Lz + LM) / (2 * LM);
+      cur = start + sx * (int32_t)mx + sy * (int32_t)my + sz * (int32_t)mz;
+    } else {
+      const uint32_t m = must[kSpec - 1];
+      if ((w[kSpec - 1] & m) != m) return false;
+      const bool cx = m & (1u << nbh_bit(dx, 0, 0)), cy = m & (1u << nbh_bit(0, dy, 0)),
+                 cz = m & (1u << nbh_bit(0, 0, dz));
+      mx += cx;
+      my += cy;
+      mz += cz;
+      cur += (cx ? sx : 0) + (cy ? sy : 0) + (cz ? sz : 0);
+    }
   }
 }
 
@@ -166,268 +261,424 @@ __global__ void k_anchor_set(LosArgs A) {
   if (A.ps[a] != s) return;
   A.d[a] = A.pd[a];
   A.src[a] = kSite | s;
-  A.flag[a] = 1;  // the anchors' neighbourhoods are evaluated in the first sweep
-  A.chunk_any[a / ((uint32_t)kLosThreads * kMarkPer)] = 1;
+  // the anchors' neighbourhoods are evaluated in the first sweep
+  int32_t x, y, z;
+  xyz(a, A, x, y, z);
+  atomicOr(&A.flag[x / 32 + A.pw * (y + A.g.ny * z)], 1u << (x & 31));
+}
+
+// ---------------------------------------------------------------- cube radii
+// rad along one axis after the other: the largest r <= kRadius such that every
+// voxel of the volume less than r away along the axes done so far is in v's
+// component.  Along the next axis a voxel k away limits r to max(k, its own
+// value) (to k if it is in another component).
+template <int Axis>
+__global__ __launch_bounds__(kLosThreads) void k_los_radius(const uint32_t *__restrict__ comp, Geom g, Div dx, Div dy,
+                                                            const uint8_t *__restrict__ in, uint8_t *__restrict__ out) {
+  const int64_t v = (int64_t)blockIdx.x * kLosThreads + threadIdx.x;
+  if (v >= g.n) return;
+  const uint32_t row = quot((uint32_t)v, dx), z = quot(row, dy);
+  const uint32_t at = Axis == 0 ? (uint32_t)v - row * (uint32_t)g.nx : Axis == 1 ? row - z * (uint32_t)g.ny : z;
+  const uint32_t len = (uint32_t)(Axis == 0 ? g.nx : Axis == 1 ? g.ny : g.nz);
+  const int64_t step = Axis == 0 ? 1 : Axis == 1 ? g.nx : (int64_t)g.nx * g.ny;
+  const uint32_t c = comp[v];
+  uint32_t m = Axis == 0 ? kRadius : in[v];
+  for (uint32_t k = 1; k < m; ++k) {
+    const bool lo = at >= k, hi = at + k < len;
+    const int64_t a = lo ? v - step * (int64_t)k : v, b = hi ? v + step * (int64_t)k : v;
+    const uint32_t ca = comp[a], cb = comp[b];
+    uint32_t q = m;
+    if (Axis) q = min((uint32_t)(lo ? in[a] : m), (uint32_t)(hi ? in[b] : m));
+    if (ca != c || cb != c) q = 0;
+    m = min(m, max(k, q));
+  }
+  out[v] = (uint8_t)m;
+}
+
+// The neighbourhood words, from the radii along all three axes.
+__global__ __launch_bounds__(kLosThreads) void k_los_nbh(const uint32_t *__restrict__ comp, Geom g, Div dx, Div dy,
+                                                         const uint8_t *__restrict__ rad, uint32_t *__restrict__ nbh) {
+  const int64_t v = (int64_t)blockIdx.x * kLosThreads + threadIdx.x;
+  if (v >= g.n) return;
+  const uint32_t row = quot((uint32_t)v, dx), zz = quot(row, dy);
+  const int32_t x = (int32_t)((uint32_t)v - row * (uint32_t)g.nx), y = (int32_t)(row - zz * (uint32_t)g.ny), z = (int32_t)zz;
+  const int64_t sy = g.nx, sz = (int64_t)g.nx * g.ny;
+  const uint32_t c = comp[v];
+  uint32_t w = (uint32_t)rad[v] << kNbhBits;
+#pragma unroll
+  for (int k = -1; k <= 1; ++k)
+#pragma unroll
+    for (int j = -1; j <= 1; ++j)
+#pragma unroll
+      for (int i = -1; i <= 1; ++i) {
+        if (i == 0 && j == 0 && k == 0) continue;
+        const bool in = x + i >= 0 && x + i < g.nx && y + j >= 0 && y + j < g.ny && z + k >= 0 && z + k < g.nz;
+        const uint32_t o = comp[in ? v + i + sy * j + sz * k : v];
+        w |= (in && o == c ? 1u : 0u) << nbh_bit(i, j, k);
+      }
+  nbh[v] = w;
 }
 
 // ---------------------------------------------------------------- sweeps
-// A sweep is three launches.  mark: every component voxel whose flag or a
-// face neighbour's flag is set (or every one, in the first sweep of a stage)
-// is listed, and the change plane is cleared.  eval: each listed voxel
-// evaluates its candidates against the state of the previous sweep and
-// writes a proposal if it changes.  apply: proposals are installed and flag
-// is set for each voxel that changed or whose source changed.  A voxel left
-// out reads nothing that changed since it was last evaluated, so it would
-// compute the same result: the sweep equals a full synchronous sweep.
+// A sweep is two launches.  eval: a wave takes a tile, spreads the flag plane
+// to the face neighbours in registers (or takes every voxel, in the first
+// sweep of stage 2), lists the voxels so marked in LDS, and each evaluates its
+// candidates against the state of the previous sweep and writes a proposal if
+// it changes.  apply: proposals are installed and flag is set for each voxel
+// that changed or whose source changed.  A voxel left out reads nothing that
+// changed since it was last evaluated, so it would compute the same result:
+// the sweep equals a full synchronous sweep.
 
-__global__ void __launch_bounds__(kLosThreads) k_los_mark(LosArgs A, int all_dirty) {
-  __shared__ uint32_t part[kLosThreads];
-  __shared__ uint32_t base;
-  __shared__ uint32_t live;
-  const Geom g = A.g;
-  const int64_t C = (int64_t)kLosThreads * kMarkPer;
-  const int64_t chunk = (int64_t)blockIdx.x * C;
-  if (!all_dirty) {
-    // A voxel of this chunk can be dirty only if a flag is set in the chunk
-    // or in a chunk that holds one of its face neighbours (offsets 1, nx and
-    // nx*ny).  Any change of the chunk itself in the sweep before set a flag
-    // here, so a skipped chunk has nothing to clear either.
-    if (threadIdx.x == 0) {
-      const int64_t nch = (g.n + C - 1) / C;
-      const int64_t off[3] = {1, g.nx, (int64_t)g.nx * g.ny};
-      uint32_t any = A.chunk_any[blockIdx.x];
-      for (int k = 0; k < 3 && !any; ++k)
-        for (int sgn = -1; sgn <= 1 && !any; sgn += 2) {
-          int64_t lo = (chunk + sgn * off[k]) / C, hi = (chunk + C - 1 + sgn * off[k]) / C;
-          if (chunk + sgn * off[k] < 0) lo = 0;
-          lo = lo < 0 ? 0 : lo;
-          hi = hi >= nch ? nch - 1 : hi;
-          for (int64_t b = lo; b <= hi && !any; ++b) any = A.chunk_any[b];
-        }
-      live = any;
-    }
-    __syncthreads();
-    if (!live) return;
-  }
-  uint32_t bits = 0, cnt = 0;
-#pragma unroll 4
-  for (int j = 0; j < kMarkPer; ++j) {
-    const int64_t v = chunk + (int64_t)j * kLosThreads + threadIdx.x;
-    if (v >= g.n) break;
-    A.chg[v] = 0;
-    if (A.comp[v] == kNone) continue;
-    int32_t x, y, z;
-    xyz(v, g, x, y, z);
-    const int64_t sy = g.nx, sz = (int64_t)g.nx * g.ny;
-    // every load is issued (clamped to v at the volume's faces), then combined
-    const uint32_t f = (uint32_t)A.flag[v] | A.flag[x > 0 ? v - 1 : v] | A.flag[x < g.nx - 1 ? v + 1 : v] |
-                       A.flag[y > 0 ? v - sy : v] | A.flag[y < g.ny - 1 ? v + sy : v] |
-                       A.flag[z > 0 ? v - sz : v] | A.flag[z < g.nz - 1 ? v + sz : v];
-    const bool dirty = all_dirty || f != 0;
-    if (dirty) { bits |= 1u << j; ++cnt; }
-  }
-  // block-wide exclusive scan of the per-thread counts, one atomic per block
-  part[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int o = 1; o < kLosThreads; o <<= 1) {
-    const uint32_t t = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0u;
-    __syncthreads();
-    part[threadIdx.x] += t;
-    __syncthreads();
-  }
-  if (threadIdx.x == kLosThreads - 1) base = part[kLosThreads - 1] ? atomicAdd(A.count, part[kLosThreads - 1]) : 0u;
-  __syncthreads();
-  uint32_t at = base + part[threadIdx.x] - cnt;
-  for (int j = 0; j < kMarkPer && bits; ++j)
-    if (bits & (1u << j)) {
-      A.list[at++] = (uint32_t)(chunk + (int64_t)j * kLosThreads + threadIdx.x);
-      bits &= ~(1u << j);
-    }
+// The wave's tile: blocks b, b + 8, ... run on one XCD, so each gets a run of
+// neighbouring tiles, which share their halos in its L2.
+__device__ __forceinline__ uint32_t my_tile() { return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
+
+struct Tile {
+  int32_t tx, y0, z0;
+};
+__device__ __forceinline__ Tile tile_at(const LosArgs &A, uint32_t t) {
+  const uint32_t q = t / (uint32_t)A.tx;
+  return Tile{(int32_t)(t - q * (uint32_t)A.tx), (int32_t)(q % (uint32_t)A.ty) * kTY, (int32_t)(q / (uint32_t)A.ty) * kTZ};
 }
 
-// The segment from voxel (x, y, z) to the ray target of candidate code cc
-// (the voxel itself, or the anchor of a site) is clear.
-__device__ __forceinline__ bool clear_to(const LosArgs &A, int32_t x, int32_t y, int32_t z, uint32_t cc, uint32_t c) {
-  const uint32_t t = (cc & kSite) ? A.anchor[cc & ~kSite] : cc;
-  int32_t ux, uy, uz;
-  xyz(t, A.g, ux, uy, uz);
-  return ray_clear(A.comp, A.g, x, y, z, ux, uy, uz, c);
+// The set bits of the tile's words as a list of (word << 5 | bit), in order;
+// lane l holds word l / kLanes and lists its part l % kLanes of it.  Returns
+// their number.
+__device__ __forceinline__ uint32_t tile_list(uint32_t word, uint16_t *list) {
+  const int lane = lane_id();
+  constexpr int kPart = 32 / kLanes;
+  uint32_t bits = (word >> (kPart * (lane % kLanes))) & ((1u << kPart) - 1u);
+  const uint32_t cnt = (uint32_t)__popc(bits);
+  uint32_t inc = cnt;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t up = __shfl_up(inc, o, kWave);
+    if (lane >= o) inc += up;
+  }
+  uint32_t at = inc - cnt;
+  while (bits) {
+    const int b = __ffs(bits) - 1;
+    list[at++] = (uint16_t)((lane / kLanes) << 5 | (lane % kLanes) * kPart | b);
+    bits &= bits - 1;
+  }
+  return __shfl(inc, kWave - 1, kWave);
 }
 
-template <int Stage>
-__device__ __forceinline__ bool los_eval(const LosArgs &A, uint32_t v) {
+// Whether v takes a new path; its proposal is written if so.  The candidates
+// of stage 1 are the sites of the face neighbours; those of stage 2 the
+// sources of the neighbours, the neighbours themselves and the voxel's own
+// path measured again.  A neighbour's source needs a clear ray; the other two
+// are valid as they are.  Neighbours that share a source are one candidate, and
+// one that has v's own source is none: its path is v's own measured again.
+// What is left differs from lane to lane, so each lane walks its own few
+// candidates, kept in LDS (in registers, under compile-time slots, every lane
+// pays for all thirteen, and three waves fit a SIMD instead of five).
+//
+// Most marked voxels have no candidate that is short enough.  Probe says
+// whether v has one; the wave then takes the voxels that have, packed, so that
+// the rays, which cost most, do not run with a quarter of the lanes.
+//
+// Bit i of fresh: face neighbour i was flagged in the sweep before.  A ray
+// that was found blocked is blocked for good, so it is remembered until the
+// neighbour's flag is set (which has v evaluated): without this the same
+// blocked rays are walked again in every sweep that a voxel takes part in.
+template <int Stage, bool Probe>
+__device__ __forceinline__ bool los_eval(const LosArgs &A, int32_t x, int32_t y, int32_t z, uint32_t fresh,
+                                         double (*cds)[kWave], uint32_t (*code)[kWave],
+                                         uint32_t (*aim)[kWave]) {
   const Geom g = A.g;
-  const uint32_t c = A.comp[v];
-  int32_t x, y, z;
-  xyz(v, g, x, y, z);
+  const int lane = lane_id();
   const uint32_t sy = (uint32_t)g.nx, sz = (uint32_t)g.nx * (uint32_t)g.ny;
+  const uint32_t v = (uint32_t)x + sy * (uint32_t)y + sz * (uint32_t)z;
+  const uint32_t c = A.comp[v];
   const uint32_t sv = A.src[v];
   const double dh = A.d[v];
-  // candidates: length cd, source code cc; bit i of need: a ray must be
-  // clear; known/ok: validity decided / valid (not shorter counts invalid)
-  // Fixed slots, so every index is a compile-time constant: stage 1 has the
-  // path through the site of neighbour i in slot i; stage 2 has the path
-  // through src(w_i) in slot 2i, through w_i in slot 2i + 1, and the voxel's
-  // own path re-measured in slot 12.  Bit i of `have` marks a candidate.
-  constexpr int kCand = Stage == 1 ? 6 : 13;
-  double cd[kCand];
-  uint32_t cc[kCand];
-  uint32_t need = 0, have = 0;
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) { cd[i] = 0.0; cc[i] = 0u; }
-  if (Stage == 2 && sv != kNone && !(sv & kSite)) {
-    int32_t ux, uy, uz;
-    xyz(sv, g, ux, uy, uz);
-    cd[kCand - 1] = len_vox(x, y, z, ux, uy, uz) + A.d[sv];
-    cc[kCand - 1] = sv;
-    have |= 1u << (kCand - 1);
-  }
+  const uint32_t blk0 = A.blk[v];
+  const uint32_t nb[6] = {x > 0 ? v - 1 : v,  x < g.nx - 1 ? v + 1 : v,  y > 0 ? v - sy : v,
+                          y < g.ny - 1 ? v + sy : v, z > 0 ? v - sz : v, z < g.nz - 1 ? v + sz : v};
+  uint32_t nc[6], nu[6];
+  double nd[6];
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
-    const bool in = i == 0 ? x > 0 : i == 1 ? x < g.nx - 1 : i == 2 ? y > 0 : i == 3 ? y < g.ny - 1
-                  : i == 4 ? z > 0 : z < g.nz - 1;
-    if (!in) continue;
-    const uint32_t w = i == 0 ? v - 1 : i == 1 ? v + 1 : i == 2 ? v - sy : i == 3 ? v + sy : i == 4 ? v - sz : v + sz;
-    if (A.comp[w] != c) continue;
-    const uint32_t u = A.src[w];
-    if (u == kNone) continue;
-    constexpr int kStep = Stage == 1 ? 1 : 2;
-    if (u & kSite) {
-      cd[kStep * i] = len_site(x, y, z, A.site_q + 3 * (size_t)(u & ~kSite));
-      cc[kStep * i] = u;
-      need |= 1u << (kStep * i);
-      have |= 1u << (kStep * i);
-    } else if (Stage == 2 && u != v) {
-      int32_t ux, uy, uz;
-      xyz(u, g, ux, uy, uz);
-      cd[kStep * i] = len_vox(x, y, z, ux, uy, uz) + A.d[u];
-      cc[kStep * i] = u;
-      need |= 1u << (kStep * i);
-      have |= 1u << (kStep * i);
+    nc[i] = A.comp[nb[i]];
+    nu[i] = A.src[nb[i]];
+    nd[i] = Stage == 2 ? A.d[nb[i]] : 0.0;
+  }
+  if (c == kNone) return false;
+  const bool has_own = Stage == 2 && sv != kNone && !(sv & kSite);
+  double own = __builtin_inf();
+  if (has_own) {
+    int32_t ux, uy, uz;
+    xyz(sv, A, ux, uy, uz);
+    own = len_vox(x, y, z, ux, uy, uz) + A.d[sv];
+  }
+  double base = own;  // the shortest candidate that needs no ray
+  uint32_t ray = 0, valid = 0;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const uint32_t u = nu[i];
+    const bool in = nb[i] != v && nc[i] == c && u != kNone;
+    if (Stage == 2 && in) {
+      nd[i] += 1.0;
+      valid |= 1u << i;
+      base = nd[i] < base ? nd[i] : base;
     }
-    if (Stage == 2) {
-      cd[2 * i + 1] = A.d[w] + 1.0;
-      cc[2 * i + 1] = w;
-      have |= 1u << (2 * i + 1);
+    if (in && u != sv && u != v) {
+      ray |= 1u << i;
+      code[i][lane] = u;
     }
   }
-  // Every loop below runs over the compile-time bound kCand (fully
-  // unrolled), so the candidate arrays stay in registers.
-  uint32_t known = 0, ok = 0;
+  // one candidate for each source; blocked for one neighbour, blocked for all that share it
+  auto sharing = [&](uint32_t u) {
+    uint32_t m = 0;
 #pragma unroll
-  for (int i = 0; i < kCand; ++i)
-    if ((have & (1u << i)) && !(cd[i] < dh)) known |= 1u << i;
-  // decides the candidate with code bc and every other undecided one with
-  // the same code that needs a ray (the same segment)
-  auto decide = [&](int bi, uint32_t bc, bool bneed) {
-    bool good = true;
-    if (bneed) {
-      good = clear_to(A, x, y, z, bc, c);
-#pragma unroll
-      for (int j = 0; j < kCand; ++j)
-        if ((have & (1u << j)) && !(known & (1u << j)) && (need & (1u << j)) && cc[j] == bc) {
-          known |= 1u << j;
-          if (good) ok |= 1u << j;
-        }
-    }
-    known |= 1u << bi;
-    if (good) ok |= 1u << bi;
-    return good;
+    for (int i = 0; i < 6; ++i) m |= (nu[i] == u ? 1u : 0u) << i;
+    return m & ray;
   };
-  // the shortest valid candidate, deciding shortest first
-  double dmin = __builtin_inf();
+  uint32_t blk = blk0 & ~fresh, cand = 0;
+  double lim = base * kNear;
+  for (uint32_t todo = ray; todo;) {
+    const int i = __ffs(todo) - 1;
+    const uint32_t u = code[i][lane], same = sharing(u);
+    todo &= ~same;
+    if (blk & same) {
+      blk |= same;
+      continue;
+    }
+    double cd;
+    uint32_t t = u;
+    if (u & kSite) {
+      if (!Probe) t = A.anchor[u & ~kSite];
+      cd = len_site(x, y, z, A.site_q + 3 * (size_t)(u & ~kSite));
+    } else {
+      int32_t ux, uy, uz;
+      xyz(u, A, ux, uy, uz);
+      cd = len_vox(x, y, z, ux, uy, uz) + A.d[u];
+    }
+    if (cd < dh && !(cd > lim)) {
+      if (!Probe) {
+        cds[i][lane] = cd;
+        aim[i][lane] = t;
+      }
+      cand |= 1u << i;
+    }
+  }
+  if (Probe) return cand != 0u || base < dh * kShorter;
+  // First the shortest valid candidate, trying rays shortest first; then, of
+  // the candidates near it, the preferred valid one, trying the rays of the
+  // preferred first (the others' codes cannot win).
+  bool found = false;
+  double dmin = base, bestd = 0.0;
+  uint32_t best = 0, bestc = 0;
   for (;;) {
     int bi = -1;
     double bd = 0.0;
     uint32_t bc = 0;
+    for (uint32_t t = cand; t; t &= t - 1) {
+      const int i = __ffs(t) - 1;
+      const double d = cds[i][lane];
+      const uint32_t u = code[i][lane];
+      const bool take = !found ? bi < 0 || d < bd
+                               : !(d > lim) && pref(u) < best && (bi < 0 || pref(u) < pref(bc));
+      if (take) { bi = i; bd = d; bc = u; }
+    }
+    if (!found && (bi < 0 || !(bd < base) || !(bd < dh * kShorter))) {
+      bi = -1;  // what needs no ray is as short, or nothing is short enough
+      if (!(dmin < dh * kShorter)) break;
+    }
+    bool good = bi < 0;
+    if (bi >= 0) {
+      int32_t ux, uy, uz;
+      xyz(aim[bi][lane], A, ux, uy, uz);
+      good = ray_clear(A, x, y, z, ux, uy, uz);
+      cand &= ~(1u << bi);
+      if (!good) blk |= sharing(bc);
+    }
+    if (!good) continue;
+    if (found) {
+      if (bi >= 0) { bestc = bc; bestd = bd; }
+      break;
+    }
+    found = true;
+    best = ~0u;  // (no candidate's preference: kNone has no path)
+    if (bi >= 0) { dmin = bd; best = pref(bc); bestc = bc; bestd = bd; }
+    lim = dmin * kNear;
 #pragma unroll
-    for (int i = 0; i < kCand; ++i)
-      if ((have & (1u << i)) && !(known & (1u << i)) && (bi < 0 || cd[i] < bd)) { bi = i; bd = cd[i]; bc = cc[i]; }
-    if (bi < 0) break;
-    if (decide(bi, bc, (need >> bi) & 1u)) { dmin = bd; break; }
+    for (int i = 0; i < 6; ++i)
+      if (Stage == 2 && (valid >> i & 1u) && nd[i] < dh && !(nd[i] > lim) && pref(nb[i]) < best) {
+        best = pref(nb[i]);
+        bestc = nb[i];
+        bestd = nd[i];
+      }
+    if (has_own && own < dh && !(own > lim) && pref(sv) < best) { best = pref(sv); bestc = sv; bestd = own; }
   }
-  if (!(dmin < dh * kShorter)) return false;
-  const double lim = dmin * kNear;
-  bool got = false;
-  double sd = 0.0;
-  uint32_t sc = 0;
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) {
-    if (!(have & (1u << i)) || cd[i] > lim) continue;
-    if (!(known & (1u << i))) decide(i, cc[i], (need >> i) & 1u);
-    if (!(ok & (1u << i))) continue;
-    if (!got || pref(cc[i]) < pref(sc) || (cc[i] == sc && cd[i] < sd)) { got = true; sd = cd[i]; sc = cc[i]; }
+  if (blk != blk0) A.blk[v] = (uint8_t)blk;
+  if (found) {
+    A.pd[v] = bestd;
+    A.ps[v] = bestc;
   }
-  A.pd[v] = sd;
-  A.ps[v] = sc;
-  A.chg[v] = 1;
-  return true;
+  return found;
 }
 
 // One synchronous sweep of stage 1 (paths only through sites) or stage 2
-// over the listed voxels; slot names the sweep in the batch.
+// over the marked voxels, the sweep-th of its stage.  A sweep past the one
+// that changed nothing ends at once.
+//
+// Bound by the chains of dependent loads (the voxels, their sources, then one
+// load a stretch of a ray) of the few voxels that each sweep works on, so it
+// needs many waves and short chains.  At 160 x 144 x 128 voxels a sweep takes
+// 15-100 us, where one launch for the marks, one for the evaluation and one for
+// the proposals took 60-290 us, and a loop of 3 updates 17.4 ms instead of 43:
+// 30.2 with the marks as bit planes and rays that leap, 28.2 with blocked rays
+// remembered, 22.3 with each lane's own candidates, 19.0 with packed rays over
+// neighbourhood words, 17.4 with fewer waits by the host.  (Tiles of 256 voxels
+// instead of 512 cost 20.3 instead of 19.0, five waves a SIMD 19.5.)
 template <int Stage>
-__global__ void __launch_bounds__(kLosThreads) k_los_eval(LosArgs A, int slot) {
-  const uint32_t n = *A.count;
-  bool changed = false;
-  for (uint32_t i = blockIdx.x * kLosThreads + threadIdx.x; i < n; i += gridDim.x * kLosThreads)
-    changed = los_eval<Stage>(A, A.list[i]) || changed;
-  if (__ballot(changed) != 0ull && lane_id() == 0) A.alive[slot] = 1u;
+__global__ __launch_bounds__(kWave, 4) void k_los_eval(LosArgs A, uint32_t sweep, int all_dirty) {
+  __shared__ uint16_t list[kTWords * 32];
+  __shared__ uint32_t chg[kTWords];
+  __shared__ uint32_t nbf[6][kTWords];  // the flags of the face neighbours
+  __shared__ double cds[6][kWave];      // each lane's candidates
+  __shared__ uint32_t code[6][kWave], aim[6][kWave];
+  const uint32_t t = my_tile();
+  if (t >= A.ntiles || *A.last + 1 < sweep) return;
+  const int lane = lane_id();
+  const Tile T = tile_at(A, t);
+  const int row = lane / kLanes, y = T.y0 + row % kTY, z = T.z0 + row / kTY;
+  const bool in = y < A.g.ny && z < A.g.nz;
+  const int64_t at = T.tx + (int64_t)A.pw * (y + (int64_t)A.g.ny * z);
+  uint32_t w = 0;
+  if (in) {
+    const uint32_t *F = A.flag + at;
+    const int64_t py = A.pw, pz = (int64_t)A.pw * A.g.ny;
+    const int left = A.g.nx - T.tx * kTX;
+    const uint32_t valid = left >= 32 ? ~0u : (1u << left) - 1u;
+    const uint32_t m = F[0], xl = T.tx > 0 ? F[-1] : 0u, xr = T.tx < A.pw - 1 ? F[1] : 0u;
+    const uint32_t f[6] = {m << 1 | xl >> 31,           m >> 1 | xr << 31,          y > 0 ? F[-py] : 0u,
+                           y < A.g.ny - 1 ? F[py] : 0u, z > 0 ? F[-pz] : 0u, z < A.g.nz - 1 ? F[pz] : 0u};
+    w = m;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      w |= f[i];
+      if (lane % kLanes == 0) nbf[i][row] = f[i];
+    }
+    w = (all_dirty ? ~0u : w) & valid;
+  }
+  if (lane < kTWords) chg[lane] = 0u;
+  const uint32_t n = tile_list(w, list);
+  __syncthreads();
+  auto fresh = [&](uint32_t e) {
+    uint32_t f = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) f |= (nbf[k][e >> 5] >> (e & 31) & 1u) << k;
+    return f;
+  };
+  uint32_t some = 0;  // listed voxels that have a candidate, moved to the front
+  for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+    const uint32_t e = i0 + lane < n ? list[i0 + lane] : 0u, r = e >> 5;
+    const bool yes = i0 + lane < n && los_eval<Stage, true>(A, T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY),
+                                                            T.z0 + (int)(r / kTY), fresh(e), cds, code, aim);
+    const uint64_t bal = __ballot(yes);
+    if (yes) list[some + (uint32_t)__popcll(bal & lanemask_lt())] = (uint16_t)e;
+    some += (uint32_t)__popcll(bal);
+  }
+  __syncthreads();
+  for (uint32_t i = lane; i < some; i += kWave) {
+    const uint32_t e = list[i], r = e >> 5;
+    if (los_eval<Stage, false>(A, T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY), T.z0 + (int)(r / kTY), fresh(e),
+                               cds, code, aim))
+      atomicOr(&chg[r], 1u << (e & 31));
+  }
+  __syncthreads();
+  const uint32_t out = chg[row];
+  if (in && lane % kLanes == 0) A.chg[at] = out;
+  if (__ballot(out != 0u) != 0ull && lane == 0) *A.last = sweep;
 }
 
-__global__ void __launch_bounds__(kLosThreads) k_los_apply(LosArgs A) {
-  const Geom g = A.g;
-  const int64_t chunk = (int64_t)blockIdx.x * kLosThreads * kMarkPer;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *A.count = 0u;  // eval of this sweep has finished
-  int any = 0;
-#pragma unroll 4
-  for (int j = 0; j < kMarkPer; ++j) {
-    const int64_t v = chunk + (int64_t)j * kLosThreads + threadIdx.x;
-    if (v >= g.n) break;
-    uint32_t s = A.src[v];
-    const uint8_t ch = A.chg[v];
+// Installs the proposals of a tile and writes its words of the flag plane.  In
+// stage 1 no voxel has another voxel as its source, so only the changed ones
+// are touched; stage 2 reads the source of every voxel and its change bit.
+template <int Stage>
+__global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) {
+  __shared__ uint16_t list[kTWords * 32];
+  const uint32_t t = my_tile();
+  if (t >= A.ntiles || *A.last + 1 < sweep) return;
+  const int lane = lane_id();
+  const Tile T = tile_at(A, t);
+  const int row = lane / kLanes, yy = T.y0 + row % kTY, zz = T.z0 + row / kTY;
+  const bool in = yy < A.g.ny && zz < A.g.nz;
+  const int64_t at = T.tx + (int64_t)A.pw * (yy + (int64_t)A.g.ny * zz);
+  const uint32_t w = in ? A.chg[at] : 0u;
+  const int64_t sy = A.g.nx, sz = (int64_t)A.g.nx * A.g.ny;
+  if (Stage == 1) {
+    if (in && lane % kLanes == 0) A.flag[at] = w;
+    const uint32_t n = tile_list(w, list);
+    __syncthreads();
+    for (uint32_t i = lane; i < n; i += kWave) {
+      const uint32_t e = list[i], r = e >> 5;
+      const int64_t v = T.tx * kTX + (int)(e & 31) + sy * (T.y0 + (int)(r % kTY)) + sz * (T.z0 + (int)(r / kTY));
+      A.d[v] = A.pd[v];
+      A.src[v] = A.ps[v];
+    }
+    return;
+  }
+  const int x = T.tx * kTX + (lane & 31), half = lane >> 5;
+  uint32_t s[kTWords / 2];
+#pragma unroll
+  for (int k = 0; k < kTWords / 2; ++k) {
+    const int r = 2 * k + half, y = T.y0 + r % kTY, z = T.z0 + r / kTY;
+    const bool ok = x < A.g.nx && y < A.g.ny && z < A.g.nz;
+    const int64_t v = x + sy * y + sz * z;
+    const bool ch = (__shfl(w, kLanes * r, kWave) >> (lane & 31)) & 1u;
+    s[k] = !ok ? kNone : ch ? A.ps[v] : A.src[v];
     if (ch) {
       A.d[v] = A.pd[v];
-      s = A.ps[v];
-      A.src[v] = s;
+      A.src[v] = s[k];
     }
-    const int f = (ch || (s != kNone && !(s & kSite) && A.chg[s])) ? 1 : 0;
-    A.flag[v] = (uint8_t)f;
-    any |= f;
   }
-  any = __syncthreads_or(any);
-  if (threadIdx.x == 0) A.chunk_any[blockIdx.x] = any ? 1 : 0;
+  uint32_t sc[kTWords / 2];
+#pragma unroll
+  for (int k = 0; k < kTWords / 2; ++k) {
+    sc[k] = 0u;
+    if (s[k] != kNone && !(s[k] & kSite)) {
+      int32_t ux, uy, uz;
+      xyz(s[k], A, ux, uy, uz);
+      sc[k] = A.chg[ux / 32 + (int64_t)A.pw * (uy + (int64_t)A.g.ny * uz)] >> (ux & 31);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kTWords / 2; ++k) {
+    const int r = 2 * k + half, y = T.y0 + r % kTY, z = T.z0 + r / kTY;
+    const uint64_t bal = __ballot((sc[k] & 1u) != 0u);
+    const uint32_t f = (uint32_t)(bal >> (32 * half)) | __shfl(w, kLanes * r, kWave);
+    if ((lane & 31) == 0 && y < A.g.ny && z < A.g.nz) A.flag[T.tx + (int64_t)A.pw * (y + (int64_t)A.g.ny * z)] = f;
+  }
 }
 
 // ---------------------------------------------------------------- phi, cells
-__global__ void k_phi_init(const uint32_t *__restrict__ src, int64_t n, uint32_t *__restrict__ phi) {
+// The line-of-sight voxel of each path (the last voxel before the site), and
+// the site it sees.  Each thread follows its path for up to kPhiHops voxels;
+// what is longer goes on in another launch, through the voxels that the
+// launch before reached (any value read, old or new, lies on the same path, so
+// in-place updates are safe).
+template <bool First>
+__global__ void k_phi(const uint32_t *__restrict__ src, int64_t n, uint32_t *phi, uint32_t *__restrict__ cell,
+                      uint32_t *flag) {
   const int64_t v = (int64_t)blockIdx.x * kLosThreads + threadIdx.x;
-  if (v >= n) return;
-  const uint32_t s = src[v];
-  phi[v] = s == kNone ? kNone : (s & kSite) ? (uint32_t)v : s;
-}
-
-// Pointer jumping towards the line-of-sight voxel of each path; any value
-// read (old or new) lies on the same path, so in-place updates are safe.
-__global__ void k_phi_jump(const uint32_t *__restrict__ src, int64_t n, uint32_t *phi, uint32_t *flag) {
-  const int64_t v = (int64_t)blockIdx.x * kLosThreads + threadIdx.x;
-  bool moved = false;
+  bool more = false;
   if (v < n) {
-    const uint32_t p = phi[v];
-    if (p != kNone && !(src[p] & kSite)) {
-      phi[v] = phi[p];
-      moved = true;
+    uint32_t p = First ? (uint32_t)v : phi[v];
+    uint32_t s = p == kNone ? kNone : src[p];
+    if (s == kNone) p = kNone;
+    for (int h = 0; h < kPhiHops && !(s & kSite); ++h) {
+      p = First ? s : phi[p];
+      s = src[p];
     }
+    more = !(s & kSite);
+    phi[v] = p;
+    cell[v] = s == kNone ? kNone : s & ~kSite;
   }
-  if (__ballot(moved) != 0ull && lane_id() == 0) flag[0] = 1u;
-}
-
-__global__ void k_phi_cell(const uint32_t *__restrict__ src, const uint32_t *__restrict__ phi, int64_t n,
-                           uint32_t *__restrict__ cell) {
-  const int64_t v = (int64_t)blockIdx.x * kLosThreads + threadIdx.x;
-  if (v >= n) return;
-  const uint32_t p = phi[v];
-  cell[v] = p == kNone ? kNone : (src[p] & ~kSite);
+  if (__ballot(more) != 0ull && lane_id() == 0) flag[0] = 1u;
 }
 
 // ---------------------------------------------------------------- update
@@ -607,11 +858,10 @@ __global__ void k_los_seed(const uint32_t *__restrict__ comp, Geom g, const uint
 struct LosWork {
   double *pd;
   uint32_t *ps;
-  uint8_t *chg;
-  uint8_t *flag;
-  uint8_t *chunk_any;
-  uint32_t *list;
-  uint32_t *ctl;  // [0] err, [1] phi flag, [2..2+kSweepBatch) alive, [2+kSweepBatch] list length
+  uint32_t *nbh;
+  uint8_t *blk;
+  uint32_t *chg, *flag;
+  uint32_t *ctl;  // [0] err, [1] phi flag, [2] last sweep
   unsigned long long *acc;
 };
 
@@ -619,13 +869,28 @@ template <class C>
 void los_layout(C &cv, const Geom &g, uint32_t S, LosWork *W) {
   double *pd = cv.template take<double>((size_t)g.n);
   uint32_t *ps = cv.template take<uint32_t>((size_t)g.n);
-  uint8_t *chg = cv.template take<uint8_t>((size_t)g.n);
-  uint8_t *flag = cv.template take<uint8_t>((size_t)g.n);
-  uint8_t *chunk_any = cv.template take<uint8_t>((size_t)(g.n / ((int64_t)kLosThreads * kMarkPer) + 1));
-  uint32_t *list = cv.template take<uint32_t>((size_t)g.n);
+  uint32_t *nbh = cv.template take<uint32_t>((size_t)g.n);
+  uint8_t *blk = cv.template take<uint8_t>((size_t)g.n);
+  const size_t words = (size_t)((g.nx + 31) / 32) * g.ny * g.nz;
+  uint32_t *chg = cv.template take<uint32_t>(words);
+  uint32_t *flag = cv.template take<uint32_t>(words);
   uint32_t *ctl = cv.template take<uint32_t>(64);
   unsigned long long *acc = cv.template take<unsigned long long>(4 * (size_t)(S ? S : 1));
-  if (W) *W = LosWork{pd, ps, chg, flag, chunk_any, list, ctl, acc};
+  if (W) *W = LosWork{pd, ps, nbh, blk, chg, flag, ctl, acc};
+}
+
+// The neighbourhood words of the component volume, which every pass over it
+// reads (scratch: the proposals, which no sweep has written yet).
+int32_t los_nbh(const uint32_t *d_comp, const Geom &g, const LosWork &W, hipStream_t s) {
+  const dim3 gv((unsigned)((g.n + kLosThreads - 1) / kLosThreads)), b(kLosThreads);
+  const Div dx = make_div((uint32_t)g.nx), dy = make_div((uint32_t)g.ny);
+  uint8_t *p = reinterpret_cast<uint8_t *>(W.pd), *q = reinterpret_cast<uint8_t *>(W.ps);
+  hipLaunchKernelGGL(k_los_radius<0>, gv, b, 0, s, d_comp, g, dx, dy, (const uint8_t *)nullptr, p);
+  hipLaunchKernelGGL(k_los_radius<1>, gv, b, 0, s, d_comp, g, dx, dy, (const uint8_t *)p, q);
+  hipLaunchKernelGGL(k_los_radius<2>, gv, b, 0, s, d_comp, g, dx, dy, (const uint8_t *)q, p);
+  hipLaunchKernelGGL(k_los_nbh, gv, b, 0, s, d_comp, g, dx, dy, (const uint8_t *)p, W.nbh);
+  LSRVT_LAUNCHED();
+  return LSRVT_OK;
 }
 
 int32_t read_err(const uint32_t *d_err, hipStream_t s) {
@@ -637,16 +902,20 @@ int32_t read_err(const uint32_t *d_err, hipStream_t s) {
   return e ? LSRVT_EINVAL : LSRVT_OK;
 }
 
+// sweeps: in, what the stages took in the pass before (0: unknown); out, what
+// they took.
 int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const uint32_t *d_anchor, uint32_t S,
-               double *d_dist, uint32_t *d_src, uint32_t *d_phi, uint32_t *d_cell, int32_t *sweeps,
+               double *d_dist, uint32_t *d_src, uint32_t *d_phi, uint32_t *d_cell, int32_t sweeps[2],
                const LosWork &W, hipStream_t s) {
   int32_t rc;
   const unsigned gs = grid_for(S, 256, 1 << 20);
   const unsigned gv = (unsigned)((g.n + kLosThreads - 1) / kLosThreads);
-  LosArgs A{d_comp, g,      d_q,         d_anchor, S, d_dist, d_src, W.pd, W.ps, W.chg, W.flag, W.chunk_any,
-            W.list, W.ctl + 2 + kSweepBatch, W.ctl + 2, W.ctl};
-  const unsigned gm = (unsigned)((g.n + (int64_t)kLosThreads * kMarkPer - 1) / ((int64_t)kLosThreads * kMarkPer));
-  const unsigned ge = 2048;
+  const int32_t tx = (g.nx + kTX - 1) / kTX, ty = (g.ny + kTY - 1) / kTY, tz = (g.nz + kTZ - 1) / kTZ;
+  const uint32_t ntiles = (uint32_t)tx * (uint32_t)ty * (uint32_t)tz;
+  LosArgs A{d_comp, g, d_q, d_anchor, S, d_dist, d_src, W.pd, W.ps, W.nbh, W.blk, W.chg, W.flag, W.ctl + 2,
+            W.ctl,
+            make_div((uint32_t)g.nx), make_div((uint32_t)g.ny), tx, tx, ty, ntiles};
+  const dim3 gt((ntiles + 7) / 8 * 8), bt(kWave);
   if ((rc = fill<uint32_t>(W.ctl, 2, 0u, s))) return rc;
   if (S) {
     hipLaunchKernelGGL(k_los_check, dim3(gs), dim3(256), 0, s, d_comp, g, d_q, d_anchor, S, W.ctl);
@@ -655,12 +924,8 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
   }
   if ((rc = fill<double>(d_dist, g.n, __builtin_inf(), s))) return rc;
   if ((rc = fill<uint32_t>(d_src, g.n, kNone, s))) return rc;
-  // mark skips chunks with no flag nearby, so it does not clear the change
-  // plane everywhere: start every pass with it clear
-  if ((rc = fill<uint8_t>(W.chg, g.n, 0, s))) return rc;
-  if ((rc = fill<uint8_t>(W.flag, g.n, 0, s))) return rc;
-  if ((rc = fill<uint8_t>(W.chunk_any, gm, 0, s))) return rc;
-  if ((rc = fill<uint32_t>(W.ctl + 2 + kSweepBatch, 1, 0u, s))) return rc;
+  if ((rc = fill<uint8_t>(W.blk, g.n, 0, s))) return rc;
+  if ((rc = fill<uint32_t>(W.flag, (int64_t)tx * g.ny * g.nz, 0u, s))) return rc;
   if (S) {
     hipLaunchKernelGGL(k_anchor_reset, dim3(gs), dim3(256), 0, s, A);
     hipLaunchKernelGGL(k_anchor_len, dim3(gs), dim3(256), 0, s, A);
@@ -669,52 +934,42 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
     LSRVT_LAUNCHED();
   }
   for (int stage = 1; stage <= 2; ++stage) {
-    int32_t done = 0;
-    bool first = true;
-    for (;;) {
-      if (done >= kMaxSweeps) return LSRVT_ELIMIT;
-      if ((rc = fill<uint32_t>(W.ctl + 2, kSweepBatch, 0u, s))) return rc;
-      for (int j = 0; j < kSweepBatch; ++j) {
-        // the first sweep of stage 2 re-evaluates everything: new candidates
-        hipLaunchKernelGGL(k_los_mark, dim3(gm), dim3(kLosThreads), 0, s, A, (first && stage == 2) ? 1 : 0);
-        if (stage == 1)
-          hipLaunchKernelGGL(k_los_eval<1>, dim3(ge), dim3(kLosThreads), 0, s, A, j);
-        else
-          hipLaunchKernelGGL(k_los_eval<2>, dim3(ge), dim3(kLosThreads), 0, s, A, j);
-        hipLaunchKernelGGL(k_los_apply, dim3(gm), dim3(kLosThreads), 0, s, A);
-        first = false;
+    // as many sweeps as the stage took in the pass before, then a few at a time
+    int32_t &took = sweeps[stage - 1];
+    int32_t batch = took ? took + 2 : kSweepBatch;
+    uint32_t launched = 0, last = 0;
+    if ((rc = fill<uint32_t>(A.last, 1, 0u, s))) return rc;
+    while (launched == last) {
+      if (launched >= (uint32_t)kMaxSweeps) return LSRVT_ELIMIT;
+      for (int32_t j = 0; j < batch; ++j) {
+        ++launched;
+        if (stage == 1) {
+          hipLaunchKernelGGL(k_los_eval<1>, gt, bt, 0, s, A, launched, 0);
+          hipLaunchKernelGGL(k_los_apply<1>, gt, bt, 0, s, A, launched);
+        } else {
+          // the first sweep of stage 2 re-evaluates everything: new candidates
+          hipLaunchKernelGGL(k_los_eval<2>, gt, bt, 0, s, A, launched, launched == 1 ? 1 : 0);
+          hipLaunchKernelGGL(k_los_apply<2>, gt, bt, 0, s, A, launched);
+        }
       }
       LSRVT_LAUNCHED();
-      uint32_t alive[kSweepBatch];
-      {
-        const int32_t rc_ = read_words(W.ctl + 2, kSweepBatch, alive, s);
-        if (rc_) return rc_;
-      }
-      int j = 0;
-      while (j < kSweepBatch && alive[j]) ++j;
-      if (j < kSweepBatch) {  // sweep j changed nothing: the stage has converged
-        done += j + 1;
-        break;
-      }
-      done += kSweepBatch;
+      if ((rc = read_words(A.last, 1, &last, s))) return rc;
+      batch = kSweepBatch;
     }
-    if (sweeps) sweeps[stage - 1] = done;
+    took = (int32_t)last + 1;  // the sweep after the last change found none
   }
-  hipLaunchKernelGGL(k_phi_init, dim3(gv), dim3(kLosThreads), 0, s, d_src, g.n, d_phi);
-  LSRVT_LAUNCHED();
-  for (int r = 0;; r += 4) {
+  for (int r = 0;; ++r) {
     if (r >= kPhiRounds) return LSRVT_ELIMIT;
-    if ((rc = fill<uint32_t>(W.ctl + 1, 1, 0u, s))) return rc;
-    for (int j = 0; j < 4; ++j)
-      hipLaunchKernelGGL(k_phi_jump, dim3(gv), dim3(kLosThreads), 0, s, d_src, g.n, d_phi, W.ctl + 1);
+    if (r && (rc = fill<uint32_t>(W.ctl + 1, 1, 0u, s))) return rc;
+    if (r == 0)
+      hipLaunchKernelGGL(k_phi<true>, dim3(gv), dim3(kLosThreads), 0, s, d_src, g.n, d_phi, d_cell, W.ctl + 1);
+    else
+      hipLaunchKernelGGL(k_phi<false>, dim3(gv), dim3(kLosThreads), 0, s, d_src, g.n, d_phi, d_cell, W.ctl + 1);
     LSRVT_LAUNCHED();
     uint32_t f = 0;
-    LSRVT_HIP(hipMemcpyAsync(&f, W.ctl + 1, sizeof(f), hipMemcpyDeviceToHost, s));
-    LSRVT_HIP(hipStreamSynchronize(s));
+    if ((rc = read_words(W.ctl + 1, 1, &f, s))) return rc;
     if (!f) break;
   }
-  hipLaunchKernelGGL(k_phi_cell, dim3(gv), dim3(kLosThreads), 0, s, d_src, d_phi, g.n, d_cell);
-  LSRVT_LAUNCHED();
   return LSRVT_OK;
 }
 
@@ -767,9 +1022,11 @@ extern "C" int32_t lsrvt_los_vt(const uint32_t *d_comp, lsrvt_dims dims, const i
   Geom g;
   LosWork W;
   int32_t rc = los_prepare(dims, n_sites, d_work, work_bytes, g, W);
-  if (rc) return rc;
-  return los_vt(d_comp, g, d_site_q, d_anchor, n_sites, d_dist, d_src, d_phi, d_cell, h_sweeps, W,
-                as_stream(stream));
+  if (rc || (rc = los_nbh(d_comp, g, W, as_stream(stream)))) return rc;
+  int32_t sw[2] = {0, 0};
+  rc = los_vt(d_comp, g, d_site_q, d_anchor, n_sites, d_dist, d_src, d_phi, d_cell, sw, W, as_stream(stream));
+  if (!rc && h_sweeps) { h_sweeps[0] = sw[0]; h_sweeps[1] = sw[1]; }
+  return rc;
 }
 
 extern "C" int32_t lsrvt_los_update(const uint32_t *d_comp, lsrvt_dims dims, const uint16_t *d_weights,
@@ -806,8 +1063,9 @@ extern "C" int32_t lsrvt_los_cvt(const uint32_t *d_comp, lsrvt_dims dims, const 
     LSRVT_LAUNCHED();
     if ((rc = read_err(W.ctl, s))) return rc;
   }
+  if ((rc = los_nbh(d_comp, g, W, s))) return rc;
+  int32_t sw[2] = {0, 0};
   for (int32_t t = 0; t <= iters; ++t) {
-    int32_t sw[2] = {0, 0};
     rc = los_vt(d_comp, g, d_site_q, d_anchor, n_sites, d_dist, d_src, d_phi, d_cell, sw, W, s);
     if (rc) return rc;
     if (h_sweeps) *h_sweeps += sw[0] + sw[1];
