@@ -843,7 +843,6 @@ __global__ __launch_bounds__(256) void k_wake_min(const uint32_t *__restrict__ w
 // has every distance below D and is exact.
 constexpr int kBRThreads = 256;
 constexpr int kBRRow = BX + 1;  // LDS row stride (keys): padding against bank conflicts
-constexpr int kGraphRounds = 8;  // relaxation rounds of a batch per captured graph
 
 struct BRArgs {
   Geom g;
@@ -1010,11 +1009,14 @@ __device__ __forceinline__ void d_br_reset(const uint8_t *__restrict__ moved, BR
   }
 }
 // Sites the last update moved, counted into *out (zeroed before).
-__global__ __launch_bounds__(256) void k_count_moved(const uint8_t *__restrict__ moved, uint32_t S, uint32_t *out) {
+__device__ __forceinline__ void d_count_moved(const uint8_t *__restrict__ moved, uint32_t S, uint32_t *out) {
   uint32_t c = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < S; i += gridDim.x * blockDim.x) c += moved[i] != 0;
   for (int o = kWave / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
   if (lane_id() == 0 && c) atomicAdd(out, c);
+}
+__global__ __launch_bounds__(256) void k_count_moved(const uint8_t *__restrict__ moved, uint32_t S, uint32_t *out) {
+  d_count_moved(moved, S, out);
 }
 
 // Set-up of an incremental pass of lsrvt_cvt: with more than fuse_min
@@ -1022,8 +1024,8 @@ __global__ __launch_bounds__(256) void k_count_moved(const uint8_t *__restrict__
 // is fused into round 1 (ctl[2] set, every brick marked for round 1);
 // otherwise (or always, mode 1) the voxels of moved sites are reset here.
 template <class KT>
-__global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restrict__ moved, BRArgs A,
-                                                          uint32_t fuse_min, int32_t mode) {
+__device__ __forceinline__ void d_br_reset_or_fuse(const uint8_t *__restrict__ moved, const BRArgs &A,
+                                                   uint32_t fuse_min, int32_t mode) {
   if (mode == 2 || (mode == 0 && A.ctl[1] > fuse_min)) {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i0 == 0) {
@@ -1035,7 +1037,11 @@ __global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restr
   }
   d_br_reset<KT>(moved, A);
 }
-
+template <class KT>
+__global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restrict__ moved, BRArgs A,
+                                                          uint32_t fuse_min, int32_t mode) {
+  d_br_reset_or_fuse<KT>(moved, A, fuse_min, mode);
+}
 
 // How the workgroups of a round find its marked bricks.  Up to kDirectBricks
 // bricks there is one workgroup for each, which looks at its brick's mark and
@@ -2194,47 +2200,6 @@ int32_t carve_cvt(void *d_work, size_t bytes, const Geom &g, uint32_t S, int32_t
   return cv.ok ? LSRVT_OK : LSRVT_EWORKSPACE;
 }
 
-// Captures kGraphRounds calls of launch_round(stream, position) into an executable
-// graph (kernel nodes only: nothing is cleared by memset).  The capture runs
-// on a stream of its own (the caller's may be the null stream, which cannot
-// be captured); the graph is then launched on the caller's stream.
-template <class F>
-int32_t capture_rounds(hipGraphExec_t *exec, F launch_round) {
-  hipStream_t cs = nullptr;
-  LSRVT_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-  hipGraph_t graph = nullptr;
-  int32_t rc = LSRVT_OK;
-  if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-    hipStreamDestroy(cs);
-    return LSRVT_EDEVICE;
-  }
-  for (int i = 0; i < kGraphRounds && rc == LSRVT_OK; ++i) rc = launch_round(cs, i);
-  const hipError_t e = hipStreamEndCapture(cs, &graph);
-  hipStreamDestroy(cs);
-  if (rc != LSRVT_OK || e != hipSuccess) {
-    if (graph) hipGraphDestroy(graph);
-    return rc ? rc : LSRVT_EDEVICE;
-  }
-  const hipError_t ei = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
-  hipGraphDestroy(graph);
-  if (ei != hipSuccess) {
-    *exec = nullptr;
-    return LSRVT_EDEVICE;
-  }
-  return LSRVT_OK;
-}
-
-// An executable graph, destroyed with its owner.
-struct RoundGraph {
-  hipGraphExec_t exec = nullptr;
-  RoundGraph() = default;
-  RoundGraph(const RoundGraph &) = delete;
-  RoundGraph &operator=(const RoundGraph &) = delete;
-  ~RoundGraph() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-  }
-};
-
 // Driver state of one Lloyd run: the levels or rounds of the previous
 // passes, which size the first batch of launches of the next one.
 struct VTState {
@@ -2632,6 +2597,29 @@ BRArgs br_args(const Geom &g, CvtWork &W, uint32_t id_bits) {
 // by the previous pass); after each batch the host reads whether any brick
 // is marked.  With narrow keys, a round that stored a key of the largest
 // exact distance sets *far and the pass stops unfinished.
+// Moved sites above which the reset is fused into round 1 (k_br_reset_or_fuse).
+// The separate reset reads every key and lets round 1 work on the bricks
+// that hold reset voxels; the fused one works on every brick in round 1
+// and reads the keys once.  Always fusing takes 108.8 ms for the flame
+// loop (1024 x 512 x 512, 30 updates), never 113.9, and 1.6 ms less than
+// with 1.25 % of the sites as the limit, so the limit lies lower: a cube
+// of the mean cell volume n / S overlaps about (edge / 16 + 1)^3 bricks,
+// the bricks beside them work too, and 32 times that count over 80 % of
+// the bricks is 0.3 % of the sites there.
+uint32_t fuse_limit(const Geom &g, uint32_t S) {
+  const double edge = std::cbrt((double)g.n / std::max<uint32_t>(S, 1u));
+  const double overlap = 32.0 * std::pow(edge / BX + 1.0, 3.0);
+  return (uint32_t)std::min(0.8 * (double)vt_grid(g).nbricks / overlap, 4294967295.0);
+}
+
+// Workgroups of the reset: each thread takes eight slots a step.  A grid that
+// covers the slots once leaves seven of the eight loads idle and costs a fused
+// pass of 379 x 251 x 147 voxels 15 us to start and end instead of 3.4, and the
+// passes of sixteen jobs of 32^3 to 192^3 135 us instead of 21.
+unsigned reset_grid(int64_t nkeys) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((nkeys + 2047) / 2048, 4096));
+}
+
 template <class KT>
 int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell, CvtWork &W, VTState &st,
                  bool inc, hipStream_t s, const Fuse *fz, bool *far) {
@@ -2651,19 +2639,8 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   } else {
     hipLaunchKernelGGL(k_count_moved, dim3(std::min<uint32_t>((S + 255) / 256, 256) + (S == 0)), dim3(256), 0, s,
                        W.moved, S, W.ctl + 1);
-    // The separate reset reads every key and lets round 1 work on the bricks
-    // that hold reset voxels; the fused one works on every brick in round 1
-    // and reads the keys once.  Always fusing takes 108.8 ms for the flame
-    // loop (1024 x 512 x 512, 30 updates), never 113.9, and 1.6 ms less than
-    // with 1.25 % of the sites as the limit, so the limit lies lower: a cube
-    // of the mean cell volume n / S overlaps about (edge / 16 + 1)^3 bricks,
-    // the bricks beside them work too, and 32 times that count over 80 % of
-    // the bricks is 0.3 % of the sites there.
-    const double edge = std::cbrt((double)g.n / std::max<uint32_t>(S, 1u));
-    const double overlap = 32.0 * std::pow(edge / BX + 1.0, 3.0);
-    const uint32_t fuse_min = (uint32_t)std::min(0.8 * (double)bg.nbricks / overlap, 4294967295.0);
-    hipLaunchKernelGGL(k_br_reset_or_fuse<KT>, dim3((unsigned)std::min<int64_t>((nkeys + 255) / 256, 65535)),
-                       dim3(256), 0, s, W.moved, A, fuse_min, tuning(LSRVT_TUNE_RESET));
+    hipLaunchKernelGGL(k_br_reset_or_fuse<KT>, dim3(reset_grid(nkeys)), dim3(256), 0, s, W.moved, A, fuse_limit(g, S),
+                       tuning(LSRVT_TUNE_RESET));
     LSRVT_LAUNCHED();
   }
   if (S) {
@@ -2854,6 +2831,8 @@ struct JobDev {
   double *ds;
   uint8_t *moved;
   uint32_t *fb_list, *fb_cnt;
+  uint32_t first;     // bricks of the jobs before this one
+  uint32_t fuse_min;  // moved sites above which the reset is fused into round 1
 };
 
 __global__ __launch_bounds__(kVTThreads) void kb_br_masks(const JobDev *J) {
@@ -2866,16 +2845,18 @@ __global__ void kb_init_sites(const JobDev *J) {
   d_init_sites(j.seeds, j.S, j.comp, j.g, j.sites, j.site_comp, j.A.ctl + 3);
 }
 
-// Start of pass t: marks and list lengths cleared (of every job: one that has
-// stopped keeps an empty list), and for a full pass (t = 0) every key and
-// packed face unreached.  Block (0, 0) clears the shared round flags and round
-// counter and records the pass (the shared words after the flags: [3] round,
-// [4] pass, read by the graph-replayed round kernels).
+// Start of pass t: marks, list lengths and reset words cleared (of every job:
+// one that has stopped keeps an empty list), and for a full pass (t = 0) every
+// key and packed face unreached.  Block (0, 0) clears the shared words: the
+// round flags and [3], the last round that had work.
 template <class KT>
 __global__ __launch_bounds__(256) void kb_pass_clear(const JobDev *J, int32_t t) {
   const JobDev &j = J[blockIdx.y];
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 5) j.A.alive[threadIdx.x] = threadIdx.x == 4 ? (uint32_t)t : 0u;
-  if (blockIdx.x == 0 && threadIdx.x < 2) j.A.cnt[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 4) j.A.alive[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x < 2) {
+    j.A.cnt[threadIdx.x] = 0u;
+    j.A.ctl[1 + threadIdx.x] = 0u;
+  }
   if (t > j.iters) return;
   const int64_t nb = j.A.bg.nbricks, stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2887,11 +2868,16 @@ __global__ __launch_bounds__(256) void kb_pass_clear(const JobDev *J, int32_t t)
   }
 }
 
+__global__ __launch_bounds__(256) void kb_count_moved(const JobDev *J, int32_t t) {
+  const JobDev &j = J[blockIdx.y];
+  if (t <= j.iters) d_count_moved(j.moved, j.S, j.A.ctl + 1);
+}
+
 template <class KT>
-__global__ __launch_bounds__(256) void kb_reset(const JobDev *J, int32_t t) {
+__global__ __launch_bounds__(256) void kb_reset(const JobDev *J, int32_t t, int32_t mode) {
   const JobDev &j = J[blockIdx.y];
   if (t > j.iters || t == 0) return;
-  d_br_reset<KT>(j.moved, j.A);
+  d_br_reset_or_fuse<KT>(j.moved, j.A, j.fuse_min, mode);
 }
 
 template <class KT>
@@ -2901,25 +2887,49 @@ __global__ void kb_sites(const JobDev *J, int32_t t) {
   d_br_sites<KT>(j.sites, j.S, j.A);
 }
 
-// The shared round advances and every job's marked bricks are listed; the
-// flag that round r + 1 will set and the lengths it will count are emptied by
-// kb_offsets and the first thread of kb_round.
-__global__ __launch_bounds__(256) void kb_list(const JobDev *J) {
-  const JobDev &j = J[blockIdx.y];
-  if ((int32_t)j.A.alive[4] > j.iters) return;
-  d_br_list(j.A, j.A.alive[3] + 1u);
+// The job that holds item i of the jobs' items back to back: the last one that
+// starts at or before it.
+template <class F>
+__device__ __forceinline__ int32_t job_of(int32_t n, uint32_t i, F start) {
+  int32_t lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (start(mid) <= i) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
 }
 
-// The round's work list of the whole batch: the jobs' lists back to back,
-// job j's at off[j] .. off[j + 1] (an exclusive prefix sum of the list
-// lengths, by one workgroup).  A job that has stopped taking part has an empty
-// list.
-__global__ __launch_bounds__(1024) void kb_offsets(const JobDev *J, int32_t n, uint32_t *off) {
+// One relaxation round of the whole batch with a workgroup for every brick of
+// every job (up to kDirectBricks of them, as for one volume): two launches
+// fewer than with lists, 4.4 of 48.9 ms for sixteen jobs of 32^3 to 192^3 with
+// 15 updates, which take 41.3 ms with the fused resets.
+template <class KT>
+__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 5 : 4) void kb_round_all(const JobDev *J, int32_t n,
+                                                                                   uint32_t r, int32_t t) {
+  __shared__ BRLds<KT> L;
+  const int32_t k = job_of(n, blockIdx.x, [&](int32_t i) { return J[i].first; });
+  const BRArgs &A = J[k].A;
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.alive[(r + 2) % 3] = 0u;  // round r + 1 sets it
+  const uint32_t b = blockIdx.x - J[k].first;
+  if (t > J[k].iters || A.mark[(size_t)(r & 1) * A.bg.nbricks + b] != r) return;
+  if (threadIdx.x == 0) A.alive[3] = r;
+  br_process<KT>(A, b, r, L);
+}
+
+// Larger batches: every job's marked bricks are listed, the lists put back to
+// back (job j's at off[j] .. off[j + 1], an exclusive prefix sum of the list
+// lengths by one workgroup; a job that has stopped taking part has an empty
+// one), and the round's workgroups stride over them.
+__global__ __launch_bounds__(256) void kb_list(const JobDev *J, uint32_t r, int32_t t) {
+  const JobDev &j = J[blockIdx.y];
+  if (t <= j.iters) d_br_list(j.A, r);
+}
+
+__global__ __launch_bounds__(1024) void kb_offsets(const JobDev *J, int32_t n, uint32_t *off, uint32_t r) {
   __shared__ uint32_t part[1024];
   const int t = threadIdx.x;
   const int32_t per = (n + 1023) / 1024, a = t * per, e = a + per < n ? a + per : n;
-  uint32_t *alive = J[0].A.alive;
-  const uint32_t r = alive[3] + 1u;
   uint32_t sum = 0;
   for (int32_t i = a; i < e; ++i) {
     sum += J[i].A.cnt[r & 1];
@@ -2939,29 +2949,22 @@ __global__ __launch_bounds__(1024) void kb_offsets(const JobDev *J, int32_t n, u
     run += J[i].A.cnt[r & 1];
   }
   if (t == 1023) {
+    uint32_t *alive = J[0].A.alive;
     off[n] = part[1023];
-    alive[3] = r;
+    if (part[1023]) alive[3] = r;
     alive[(r + 2) % 3] = 0u;
   }
 }
 
-// One relaxation round of the whole batch: the workgroups stride over the
-// concatenated list, each item being a (job, brick) pair found by a binary
-// search of the offsets.
 template <class KT>
-__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 5 : 4) void kb_round(const JobDev *J, int32_t n, const uint32_t *off) {
+__global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 5 : 4) void kb_round(const JobDev *J, int32_t n,
+                                                                               const uint32_t *off, uint32_t r) {
   __shared__ BRLds<KT> L;
   const uint32_t total = off[n];
-  const uint32_t r = J[0].A.alive[3];
   for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
-    int32_t lo = 0, hi = n - 1;  // the last job whose list starts at or before item
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= item) lo = mid;
-      else hi = mid - 1;
-    }
-    const BRArgs &A = J[lo].A;
-    br_process<KT>(A, A.list[item - off[lo]], r, L);
+    const int32_t k = job_of(n, item, [&](int32_t i) { return off[i]; });
+    const BRArgs &A = J[k].A;
+    br_process<KT>(A, A.list[item - off[k]], r, L);
   }
 }
 
@@ -3067,40 +3070,43 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
   const unsigned g_round = cap(c.sum_nb, tuning(LSRVT_TUNE_BR_GRID) > 0 ? tuning(LSRVT_TUNE_BR_GRID) : 8192);
   const unsigned g_fin = cap((c.max_nb + 7) / 8 * 8, 65528);
   const unsigned g_near = cap((c.max_sites + 3) / 4, 512), g_far = cap(c.max_sites, 64);
+  const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
+  const bool direct = tg == 0 && c.sum_nb <= kDirectBricks;
   uint32_t rounds_hint = 0;
-  // kGraphRounds rounds of every job captured once and replayed as one graph launch
-  RoundGraph gs;
-  uint32_t *offs = c.offs;
-  rc = capture_rounds(&gs.exec, [&](hipStream_t cs, int) -> int32_t {
-    hipLaunchKernelGGL(kb_list, dim3(g_list, N), dim3(256), 0, cs, dj);
-    hipLaunchKernelGGL(kb_offsets, dim3(1), dim3(1024), 0, cs, dj, n, offs);
-    hipLaunchKernelGGL(kb_round<KT>, dim3(g_round), dim3(kBRThreads), 0, cs, dj, n, (const uint32_t *)offs);
-    LSRVT_LAUNCHED();
-    return LSRVT_OK;
-  });
-  if (rc) return rc;
   for (int32_t t = 0; t <= c.tmax; ++t) {
     hipLaunchKernelGGL(kb_pass_clear<KT>, dim3(g_clear, N), dim3(256), 0, s, dj, t);
-    if (t > 0) hipLaunchKernelGGL(kb_reset<KT>, dim3(g_clear, N), dim3(256), 0, s, dj, t);
+    if (t > 0) {
+      hipLaunchKernelGGL(kb_count_moved, dim3(cap((c.max_sites + 255) / 256, 256), N), dim3(256), 0, s, dj, t);
+      hipLaunchKernelGGL(kb_reset<KT>, dim3(reset_grid(c.max_keys), N), dim3(256), 0, s, dj, t,
+                         tuning(LSRVT_TUNE_RESET));
+    }
     hipLaunchKernelGGL(kb_sites<KT>, dim3(g_sites, N), dim3(256), 0, s, dj, t);
     LSRVT_LAUNCHED();
     uint32_t r = 0;
-    int batch = rounds_hint ? (int)rounds_hint : kGraphRounds;
-    uint32_t w[3];
+    int batch = rounds_hint ? (int)rounds_hint + 1 : 12;
+    uint32_t w[4];
     const bool timed = timer().on;
     while (true) {
       std::pair<hipEvent_t, hipEvent_t> ev;
-      const int graphs = (batch + kGraphRounds - 1) / kGraphRounds;
       if (timed && (rc = timed_begin(s, ev))) return rc;
-      for (int k = 0; k < graphs; ++k) LSRVT_HIP(hipGraphLaunch(gs.exec, s));
-      r += (uint32_t)(graphs * kGraphRounds);
-      if (timed && (rc = timed_end(s, ev, (uint64_t)graphs * kGraphRounds))) return rc;
-      if ((rc = read_words(c.alive, 3, w, s))) return rc;
+      for (int k = 0; k < batch; ++k) {
+        ++r;
+        if (direct) {
+          hipLaunchKernelGGL(kb_round_all<KT>, dim3((unsigned)c.sum_nb), dim3(kBRThreads), 0, s, dj, n, r, t);
+        } else {
+          hipLaunchKernelGGL(kb_list, dim3(g_list, N), dim3(256), 0, s, dj, r, t);
+          hipLaunchKernelGGL(kb_offsets, dim3(1), dim3(1024), 0, s, dj, n, c.offs, r);
+          hipLaunchKernelGGL(kb_round<KT>, dim3(g_round), dim3(kBRThreads), 0, s, dj, n, (const uint32_t *)c.offs, r);
+        }
+      }
+      LSRVT_LAUNCHED();
+      if (timed && (rc = timed_end(s, ev, (uint64_t)batch))) return rc;
+      if ((rc = read_words(c.alive, 4, w, s))) return rc;
       if (w[(r + 1) % 3] == 0) break;
       if (r > (uint32_t)(1u << 30)) return LSRVT_EDEVICE;
-      batch = kGraphRounds;
+      batch = 4;
     }
-    rounds_hint = r;
+    rounds_hint = w[3];
     if (t < c.tmax) hipLaunchKernelGGL(kb_update_clear, dim3(g_sites, N), dim3(256), 0, s, dj, t);
     hipLaunchKernelGGL(kb_finish<KT>, dim3(g_fin, N), dim3(kVTThreads), 0, s, dj, t);
     if (t < c.tmax) {
@@ -3182,6 +3188,10 @@ int32_t cvt_batch(const CvtBatchJob *jobs, int32_t n, void *work, size_t bytes, 
     j.S = b.n_sites;
     j.iters = b.iters;
     const size_t S = b.n_sites;
+    j.first = (uint32_t)c.sum_nb;
+    j.fuse_min = fuse_limit(g, b.n_sites);
+    j.A.moved = W.moved;
+    j.A.fsites = b.sites;
     j.sums = Sums{W.sums};
     j.ds = W.ds;
     j.moved = W.moved;

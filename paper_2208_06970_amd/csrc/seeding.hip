@@ -335,7 +335,7 @@ __global__ void k_seed_sorted(const uint32_t *idx, int64_t P, const uint32_t *pa
 // list and number).  The walk over the pairs is a chain of loads for every
 // step of the search: with a wave for each component the largest one's 30000
 // pairs took 0.92 ms of a 501 x 333 x 187 volume (0.05 now) and
-// 3.1 ms at 1024 x 512 x 512 (0.1 now).
+// 3.1 ms at 1024 x 512 x 512 (0.19 now).
 constexpr int kNarrowPer = 4;
 constexpr uint32_t kNarrow = kNarrowPer * kWave;
 constexpr int kWideThreads = 1024;
