@@ -1801,26 +1801,38 @@ __device__ __forceinline__ double move_len(uint32_t a, uint32_t b, Geom g) {
 template <class View>
 __device__ __forceinline__ void d_snap(const View &cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds,
                                        uint8_t *moved, uint32_t *fb_list, uint32_t *fb_cnt) {
-  uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S) return;
-  const unsigned long long *sm = sums.p + 4 * (size_t)s;
-  const uint64_t M = sm[0];
-  uint32_t old = sites[s];
-  moved[s] = 0;
-  if (M == 0) {
-    if (ds) ds[s] = 0.0;
-    return;
+  __shared__ uint32_t cnt_s, base_s;
+  const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+  bool out = false;  // the rounded centroid lies outside the site's cell
+  if (s < S) {
+    const unsigned long long *sm = sums.p + 4 * (size_t)s;
+    const uint64_t M = sm[0];
+    uint32_t old = sites[s];
+    moved[s] = 0;
+    if (M == 0) {
+      if (ds) ds[s] = 0.0;
+    } else {
+      const uint64_t qx = round_half_down(sm[1], M), qy = round_half_down(sm[2], M), qz = round_half_down(sm[3], M);
+      const uint32_t q = (uint32_t)(qx + (uint64_t)g.nx * (qy + (uint64_t)g.ny * qz));
+      out = cell.id((int32_t)qx, (int32_t)qy, (int32_t)qz) != s;
+      if (!out) {
+        sites[s] = q;
+        moved[s] = q != old;
+        if (ds) ds[s] = move_len(old, q, g);
+      }
+    }
   }
-  const uint64_t qx = round_half_down(sm[1], M), qy = round_half_down(sm[2], M), qz = round_half_down(sm[3], M);
-  const uint32_t q = (uint32_t)(qx + (uint64_t)g.nx * (qy + (uint64_t)g.ny * qz));
-  if (cell.id((int32_t)qx, (int32_t)qy, (int32_t)qz) == s) {
-    sites[s] = q;
-    moved[s] = q != old;
-    if (ds) ds[s] = move_len(old, q, g);
-  } else {
-    uint32_t pos = atomicAdd(fb_cnt, 1u);
-    fb_list[pos] = s;
-  }
+  // one atomic on the list's length for each workgroup: they queue up (27 ns each)
+  if (threadIdx.x == 0) cnt_s = 0u;
+  __syncthreads();
+  const uint64_t m = __ballot(out);
+  uint32_t pos = 0;
+  if (m && lane_id() == 0) pos = atomicAdd(&cnt_s, (uint32_t)__popcll(m));
+  pos = __shfl(pos, 0, kWave) + (uint32_t)__popcll(m & lanemask_lt());
+  __syncthreads();
+  if (threadIdx.x == 0 && cnt_s) base_s = atomicAdd(fb_cnt, cnt_s);
+  __syncthreads();
+  if (out) fb_list[base_s + pos] = s;
 }
 template <class View>
 __global__ void k_snap(View cell, Geom g, uint32_t S, Sums sums, uint32_t *sites, double *ds, uint8_t *moved,
