@@ -623,6 +623,7 @@ struct FinArgs {
   uint32_t *kmin_c, *kmax_c, *hist_c;
 };
 
+constexpr int kHistAhead = 4;
 __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
   extern __shared__ uint8_t smem[];
   const int m = A.m, lane = lane_id();
@@ -631,6 +632,19 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
   for (uint32_t s = blockIdx.x * kAggWaves + w; s < A.S; s += gridDim.x * kAggWaves) {
     const uint64_t n = A.cnt[s];
     const uint32_t i0 = A.item_off[A.rank[s]], i1 = A.item_off[A.rank[s] + 1];
+    const uint32_t c = A.site_comp[s];
+    const uint32_t site = A.sites[s];
+    // what does not hang on the items is loaded beside them: the first
+    // variable and kHistAhead bins of every lane (123000 cells of 4 variables
+    // with 32 bins: 100 us, 124 with one load after the other; several cells a
+    // wave, their first loads a lane each, 155)
+    const bool has = lane < m;
+    const uint32_t lo0 = has ? A.kmin[(int64_t)s * m + lane] : 0u, hi0 = has ? A.kmax[(int64_t)s * m + lane] : 0u;
+    const float at0 = has && n ? A.vars[(int64_t)lane * A.n + site] : 0.0f;
+    uint32_t h0[kHistAhead];
+#pragma unroll
+    for (int k = 0; k < kHistAhead; ++k)
+      h0[k] = A.hist && lane + kWave * k < m * A.B ? A.hist[(int64_t)s * m * A.B + lane + kWave * k] : 0u;
     const uint32_t step = i1 - i0 > (uint32_t)kFold ? kFold : 1;
     for (int u = lane; u < A.U; u += kWave) {
       double v = 0.0;
@@ -641,15 +655,17 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
     }
     wave_sync();
     if (lane == 0) A.out_n[s] = n;
-    const uint32_t c = A.site_comp[s];
     if (n && c < A.n_comp) {
       if (lane == 0) atomicAdd(&A.cnt_c[c], (unsigned long long)n);
       for (int j = lane; j < m; j += kWave) {
-        atomicMin(&A.kmin_c[(int64_t)c * m + j], A.kmin[(int64_t)s * m + j]);
-        atomicMax(&A.kmax_c[(int64_t)c * m + j], A.kmax[(int64_t)s * m + j]);
+        atomicMin(&A.kmin_c[(int64_t)c * m + j], j < kWave ? lo0 : A.kmin[(int64_t)s * m + j]);
+        atomicMax(&A.kmax_c[(int64_t)c * m + j], j < kWave ? hi0 : A.kmax[(int64_t)s * m + j]);
       }
+#pragma unroll
+      for (int k = 0; k < kHistAhead; ++k)
+        if (h0[k]) atomicAdd(&A.hist_c[(int64_t)c * m * A.B + lane + kWave * k], h0[k]);
       if (A.hist)
-        for (int i = lane; i < m * A.B; i += kWave) {
+        for (int i = lane + kWave * kHistAhead; i < m * A.B; i += kWave) {
           uint32_t h = A.hist[(int64_t)s * m * A.B + i];
           if (h) atomicAdd(&A.hist_c[(int64_t)c * m * A.B + i], h);
         }
@@ -659,13 +675,13 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
       float mean = 0.0f;
       double mean64 = 0.0;
       if (n) {
-        mean64 = (double)A.vars[(int64_t)j * A.n + A.sites[s]] + th[j] / dn;
+        mean64 = (double)(j < kWave ? at0 : A.vars[(int64_t)j * A.n + site]) + th[j] / dn;
         mean = (float)mean64;
       }
       A.mean32[(int64_t)s * m + j] = mean;
       A.mean64[(int64_t)s * m + j] = mean64;
-      A.vmin[(int64_t)s * m + j] = n ? key2f(A.kmin[(int64_t)s * m + j]) : __builtin_inff();
-      A.vmax[(int64_t)s * m + j] = n ? key2f(A.kmax[(int64_t)s * m + j]) : -__builtin_inff();
+      A.vmin[(int64_t)s * m + j] = n ? key2f(j < kWave ? lo0 : A.kmin[(int64_t)s * m + j]) : __builtin_inff();
+      A.vmax[(int64_t)s * m + j] = n ? key2f(j < kWave ? hi0 : A.kmax[(int64_t)s * m + j]) : -__builtin_inff();
     }
     for (int p = lane; p < A.P; p += kWave) {
       const int j = A.pairs.j[p], k = A.pairs.k[p];
@@ -687,10 +703,13 @@ __global__ __launch_bounds__(kAggThreads) void k_agg_finalize(FinArgs A) {
 }
 
 // 5a. exact band statistics from the components: one workgroup per run of at
-// most 256 components in band order; each lane owns columns (count, minima,
+// most kBandRun components in band order; each lane owns columns (count, minima,
 // maxima, histogram bins) and flushes one atomic per column whenever the band
-// changes.  Runs are short enough for about 2048 workgroups: a lane walks its
-// run one load after another, which is what the time goes to.
+// changes.  What the time goes to is a lane's walk along its run, kAhead loads
+// at a time, and the workgroups' atomics on one band's columns, 27 ns each, so
+// there are about 1024 workgroups (123000 components, 4 variables of 32 bins:
+// 41 us; 94 with 2048 workgroups whose loads waited for each other).
+constexpr int kBandRun = 1024;
 struct BandIntArgs {
   uint32_t n_comp, run;
   int m, B;
@@ -710,15 +729,15 @@ __global__ __launch_bounds__(256) void k_band_int(BandIntArgs A) {
   const int nq = (int)(q1 - q0);
   // the run's components and their bands, staged once (the order -> band
   // chain of loads would otherwise repeat for every column)
-  __shared__ uint32_t cs[256];
-  __shared__ int bs[256];
-  if ((int)threadIdx.x < nq) {
-    const uint32_t c = A.order[q0 + threadIdx.x];
-    cs[threadIdx.x] = c;
-    bs[threadIdx.x] = A.comp_band[c];
+  __shared__ uint32_t cs[kBandRun];
+  __shared__ uint8_t bs[kBandRun];
+  for (int i = threadIdx.x; i < nq; i += 256) {
+    const uint32_t c = A.order[q0 + i];
+    cs[i] = c;
+    bs[i] = A.comp_band[c];
   }
   __syncthreads();
-  constexpr int kAhead = 8;  // loads issued together per column
+  constexpr int kAhead = 16;  // loads issued together per column
   for (int64_t col = threadIdx.x; col < cols; col += 256) {
     const int kind = col == 0 ? 0 : col <= m ? 1 : col <= 2 * m ? 2 : 3;
     const int64_t sub = kind == 1 ? col - 1 : kind == 2 ? col - 1 - m : col - 1 - 2 * m;
@@ -736,18 +755,17 @@ __global__ __launch_bounds__(256) void k_band_int(BandIntArgs A) {
         if (acc) atomicAdd(&A.hist_b[(int64_t)band * m * B + sub], (uint32_t)acc);
       }
     };
+    // one address for all kinds: with a branch for each the loads of a step wait
+    // for each other (a component has fewer than 2^31 voxels: the low word)
+    const uint32_t *src = kind == 0   ? reinterpret_cast<const uint32_t *>(A.cnt_c)
+                          : kind == 1 ? A.kmin_c + sub
+                          : kind == 2 ? A.kmax_c + sub
+                                      : A.hist_c + sub;
+    const int64_t stride = kind == 0 ? 2 : kind < 3 ? m : (int64_t)m * B;
     for (int q = 0; q < nq; q += kAhead) {
-      uint64_t v[kAhead];
+      uint32_t v[kAhead];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) {
-        v[k] = 0;
-        if (q + k >= nq) continue;
-        const uint32_t c = cs[q + k];
-        v[k] = kind == 0 ? (uint64_t)A.cnt_c[c]
-             : kind == 1 ? (uint64_t)A.kmin_c[(int64_t)c * m + sub]
-             : kind == 2 ? (uint64_t)A.kmax_c[(int64_t)c * m + sub]
-                         : (uint64_t)A.hist_c[(int64_t)c * m * B + sub];
-      }
+      for (int k = 0; k < kAhead; ++k) v[k] = src[stride * cs[q + k < nq ? q + k : q]];
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
         if (q + k >= nq) break;
@@ -783,10 +801,14 @@ __global__ void k_decode_minmax(const uint32_t *kmin, const uint32_t *kmax, cons
 // 5b. Chan pairwise merge in float64.  Members of group g are
 // order[off[g] .. off[g+1]) in that order.  Groups of at most kSmallGroup
 // members: one thread per (group, pair unit) merges them one after another.
-// Larger groups: one workgroup per (group, pair unit); lane t merges its
-// contiguous share of the members in order, then the 256 lane states merge
-// pairwise in a fixed tree (t with t + 128, ..., t with t + 1).
+// Larger groups: one workgroup per (group, pair unit); lane t merges members t,
+// t + 256, ... in order, then the 256 lane states merge pairwise in a fixed tree
+// (t with t + 128, ..., t with t + 1).  Neighbouring lanes take neighbouring
+// members, because the members' values are a few doubles each and what bounds
+// the merge is the lines they lie in: with a contiguous share for each lane the
+// bands of 123000 components and 4 variables take 125 us, now 71.
 constexpr uint32_t kSmallGroup = 32;
+constexpr int kChanAhead = 8;  // members of a lane whose values are loaded together
 
 struct MergeArgs {
   uint32_t n_groups;
@@ -865,14 +887,21 @@ __global__ __launch_bounds__(256) void k_chan_big(MergeArgs A) {
     const int p = (int)(w % A.P);
     const int j = A.pairs.j[p], k = A.pairs.k[p];
     const uint32_t q0 = A.off[gidx], q1 = A.off[gidx + 1];
-    const uint32_t len = q1 - q0, share = (len + 255) / 256;
-    const uint32_t a0 = q0 + t * share;
-    const uint32_t a1 = a0 + share < q1 ? a0 + share : q1;
     ChanState st{0.0, 0.0, 0.0, 0.0};
-    for (uint32_t q = a0; q < a1; ++q) {
-      const uint32_t mem = A.order[q];
-      chan_add(st, (double)A.in_cnt[mem], A.in_mean[(int64_t)mem * A.m + j], A.in_mean[(int64_t)mem * A.m + k],
-               A.in_c[(int64_t)mem * A.P + p]);
+    for (uint32_t q = q0 + t; q < q1; q += 256 * kChanAhead) {
+      double n[kChanAhead], vj[kChanAhead], vk[kChanAhead], vc[kChanAhead];
+      uint32_t mem[kChanAhead];
+#pragma unroll
+      for (int i = 0; i < kChanAhead; ++i) mem[i] = A.order[q + 256 * i < q1 ? q + 256 * i : q];
+#pragma unroll
+      for (int i = 0; i < kChanAhead; ++i) {
+        n[i] = q + 256 * i < q1 ? (double)A.in_cnt[mem[i]] : 0.0;  // (an empty member adds nothing)
+        vj[i] = A.in_mean[(int64_t)mem[i] * A.m + j];
+        vk[i] = A.in_mean[(int64_t)mem[i] * A.m + k];
+        vc[i] = A.in_c[(int64_t)mem[i] * A.P + p];
+      }
+#pragma unroll
+      for (int i = 0; i < kChanAhead; ++i) chan_add(st, n[i], vj[i], vk[i], vc[i]);
     }
     sn[t] = st.n;
     sj[t] = st.mj;
@@ -1257,7 +1286,7 @@ extern "C" int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, cons
     LSRVT_LAUNCHED();
     BandIntArgs BI;
     BI.n_comp = C;
-    BI.run = std::min<uint32_t>(256, std::max<uint32_t>(8, C / 2048));
+    BI.run = std::min<uint32_t>(kBandRun, std::max<uint32_t>(8, C / 1024));
     BI.m = m;
     BI.B = B;
     BI.order = W.val_b;
