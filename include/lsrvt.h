@@ -541,10 +541,10 @@ int32_t lsrvt_set_vt_engine(int32_t engine);
  *                           the same results.
  *   LSRVT_TUNE_RESET        how an incremental relaxation pass of lsrvt_cvt
  *                           starts: 0 = the reset of moved sites' voxels is
- *                           fused into the first round (which then works on
+ *                           fused into the first rounds (which then work on
  *                           every brick) when the moved sites' cells cover
  *                           most bricks, else done by its own kernel (which
- *                           reads every key but lets the first round work
+ *                           reads every key but lets the first rounds work
  *                           only on bricks with reset voxels); 1 = always
  *                           its own kernel; 2 = always fused.
  * Returns the previous value, or -1 (and changes nothing) for an unknown

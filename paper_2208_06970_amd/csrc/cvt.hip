@@ -818,17 +818,15 @@ __global__ __launch_bounds__(256) void k_wake_min(const uint32_t *__restrict__ w
 // fixed point by line sweeps along x, y and z (forward and backward, with the
 // same-band edge masks) until a sweep round changes nothing, stores the keys
 // that changed, and marks for the next round each face neighbour whose shared
-// face changed.  A brick reads its neighbours' keys while they may be
-// written in the same round: every value it can see is a real path length,
-// and a neighbour that lowers a face key after the read marks it again, so
-// the rounds end exactly at the fixed point.  An incremental pass starts from
-// the previous keys with the voxels of moved sites set to unreached.  That
-// reset is done either by its own kernel (which marks the bricks that hold
-// such voxels), or fused into the first round, which then works on every
-// brick: each key it reads (the brick's own and the neighbours' faces) is
-// taken as unreached when its site moved, unless it is the site's own new
-// voxel, and it stores the whole brick.  Keys seen in the first round are
-// thus always the reset ones, whichever bricks have been stored already.
+// face changed.  Neighbours never work in the same round (br_first), and a
+// neighbour that lowers a face key after the read marks the brick again, so the
+// rounds end exactly at the fixed point.  An incremental pass starts from the
+// previous keys with the voxels of moved sites set to unreached.  That reset is
+// done either by its own kernel (which marks the bricks that hold such voxels),
+// or fused into the bricks' first rounds, in which every brick works: each key
+// that is not yet reset (the brick's own; in round 1 the neighbours' faces too)
+// is taken as unreached when its site moved, unless it is the site's own new
+// voxel, and the whole brick is stored.
 //
 // Keys come in two widths.  Wide keys are 64 bits, distance << 32 | id.
 // Narrow keys are 32 bits, distance << b | id with b the bits the site ids
@@ -856,7 +854,7 @@ struct BRArgs {
   uint32_t *mark;                  // [2][nbricks]: mark[r & 1][b] == r when brick b works in round r
   uint32_t *list;                  // [nbricks] bricks of the current round (large volumes)
   uint32_t *cnt;                   // [2] length of round r's list at r & 1
-  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into round 1, [3] error bits, [13] last round
+  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into the first rounds, [3] error bits, [13] last round
   const uint8_t *moved;            // the sites the last update moved (fused reset)
   const uint32_t *fsites;          // the sites' voxels (fused reset)
   uint32_t *alive;                 // [3] round alive flags (by r % 3); shared by the jobs of a batch
@@ -923,10 +921,34 @@ __device__ __forceinline__ void br_mark(const BRArgs &A, int bx, int by, int bz,
     A.mark[(size_t)(r & 1) * A.bg.nbricks + (size_t)(qx + A.bg.nbx * (qy + A.bg.nby * qz))] = r;
 }
 
+__device__ __forceinline__ void br_coords(const BRArgs &A, int64_t b, int &bx, int &by, int &bz) {
+  const uint32_t row = (uint32_t)b / (uint32_t)A.bg.nbx;
+  bx = (int)((uint32_t)b - row * (uint32_t)A.bg.nbx);
+  by = (int)(row % (uint32_t)A.bg.nby);
+  bz = (int)(row / (uint32_t)A.bg.nby);
+}
+
+// The round in which a brick works first: the bricks of even coordinate sum work
+// in odd rounds and the others in even ones (a brick marks its face neighbours,
+// which are of the other kind, for the next round, so this holds by itself
+// once the first marks are set so).  No two neighbours work in one round, and
+// the second kind already sees what the first found: 114.6 ms for the flame step
+// (1024 x 512 x 512, 30 updates) and 122.3 with all kinds in every round, 14.6
+// and 16.0 for 379 x 251 x 147 with 20 updates, 37.0 and 38.5 for sixteen jobs of
+// 32^3 to 192^3, the same for one pass of 192 x 96 x 96.
+__device__ __forceinline__ uint32_t br_first(int bx, int by, int bz) { return 1u + (uint32_t)((bx + by + bz) & 1); }
+
+// Marks neighbour k of a brick (0: itself) for its first round.
+__device__ __forceinline__ void br_mark_first(const BRArgs &A, int bx, int by, int bz, int k) {
+  const uint32_t r = br_first(bx, by, bz);
+  br_mark(A, bx, by, bz, k, k ? 3u - r : r);
+  A.alive[k ? 3u - r : r] = 1u;
+}
+
 // Site keys of a pass: (0, s) wherever it is smaller than the stored key
 // (every voxel of a full pass is unreached); a site voxel that changes
-// marks its brick, and the face neighbours whose face it lies on, for round
-// 1 (its packed x-face copy follows).
+// marks its brick, and the face neighbours whose face it lies on, for their
+// first rounds (its packed x-face copy follows).
 template <class KT>
 __device__ __forceinline__ void d_br_sites(const uint32_t *__restrict__ sites, uint32_t S, BRArgs A) {
   KT *key = static_cast<KT *>(A.key), *xface = static_cast<KT *>(A.xface);
@@ -958,15 +980,14 @@ __device__ __forceinline__ void d_br_sites(const uint32_t *__restrict__ sites, u
   const bool on[7] = {true, lx == 0, lx == BX - 1, ly == 0, ly == BY - 1, lz == 0, lz == BZ - 1};
 #pragma unroll
   for (int q = 0; q < 7; ++q)
-    if (on[q]) br_mark(A, bx, by, bz, q, 1u);
-  A.alive[1] = 1u;
+    if (on[q]) br_mark_first(A, bx, by, bz, q);
 }
 template <class KT>
 __global__ void k_br_sites(const uint32_t *__restrict__ sites, uint32_t S, BRArgs A) { d_br_sites<KT>(sites, S, A); }
 
 
 // Incremental pass set-up: voxels whose site moved become unreached (keys
-// and packed faces), and their bricks are marked for round 1.  One thread
+// and packed faces), and their bricks are marked for their first rounds.  One thread
 // per voxel slot (the slot index is the brick-major index).
 template <class KT>
 __device__ __forceinline__ void d_br_reset(const uint8_t *__restrict__ moved, BRArgs A) {
@@ -1002,8 +1023,9 @@ __device__ __forceinline__ void d_br_reset(const uint8_t *__restrict__ moved, BR
       }
       const uint64_t any = __ballot(mv[j] != 0);
       if (any && lane == __builtin_ctzll(any)) {
-        A.mark[(size_t)1 * A.bg.nbricks + i / (kRows * BX)] = 1u;  // round 1 has parity 1
-        A.alive[1] = 1u;
+        int bx, by, bz;
+        br_coords(A, i / (kRows * BX), bx, by, bz);
+        br_mark_first(A, bx, by, bz, 0);
       }
     }
   }
@@ -1021,18 +1043,19 @@ __global__ __launch_bounds__(256) void k_count_moved(const uint8_t *__restrict__
 
 // Set-up of an incremental pass of lsrvt_cvt: with more than fuse_min
 // sites moved (the count in ctl[1]; mode 0), or always (mode 2), the reset
-// is fused into round 1 (ctl[2] set, every brick marked for round 1);
+// is fused into the first rounds (ctl[2] set, every brick marked for its own);
 // otherwise (or always, mode 1) the voxels of moved sites are reset here.
 template <class KT>
 __device__ __forceinline__ void d_br_reset_or_fuse(const uint8_t *__restrict__ moved, const BRArgs &A,
                                                    uint32_t fuse_min, int32_t mode) {
   if (mode == 2 || (mode == 0 && A.ctl[1] > fuse_min)) {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i0 == 0) {
-      A.ctl[2] = 1u;
-      A.alive[1] = 1u;
+    if (i0 == 0) A.ctl[2] = 1u;
+    for (int64_t b = i0; b < A.bg.nbricks; b += (int64_t)gridDim.x * blockDim.x) {
+      int bx, by, bz;
+      br_coords(A, b, bx, by, bz);
+      br_mark_first(A, bx, by, bz, 0);
     }
-    for (int64_t b = i0; b < A.bg.nbricks; b += (int64_t)gridDim.x * blockDim.x) A.mark[A.bg.nbricks + b] = 1u;
     return;
   }
   d_br_reset<KT>(moved, A);
@@ -1216,8 +1239,9 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
     KT fyp = key[(size_t)(hyp ? b + bsy : b) * kB + lo4 + 256 * hi4];
     KT fzm = key[(size_t)(hzm ? b - bsz : b) * kB + lo4 + 16 * hi4 + 256 * 15];
     KT fzp = key[(size_t)(hzp ? b + bsz : b) * kB + lo4 + 16 * hi4];
-    // first round of an incremental pass with the reset fused in
-    const bool fuse = r == 1 && A.ctl[2] != 0u;
+    // the brick's first round in an incremental pass with the reset fused in;
+    // in round 2 its neighbours are through with theirs
+    const bool fuse = r <= 2 && A.ctl[2] != 0u;
     if (fuse) {
       const uint32_t nx = (uint32_t)A.g.nx, nxy = (uint32_t)A.g.nx * (uint32_t)A.g.ny;
       const uint32_t x0 = (uint32_t)bx * BX, y0 = (uint32_t)by * BY, z0 = (uint32_t)bz * BZ;
@@ -1226,12 +1250,14 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
 #pragma unroll
       for (int i = 0; i < 16; ++i) kv[i] = br_filter<KT>(A, kv[i], hop, v0 + nxy * (uint32_t)i);
       // the face voxels' own coordinates (unused where the neighbour is missing)
-      fxm = br_filter<KT>(A, fxm, hop, x0 - 1 + nx * (y0 + lo4) + nxy * (z0 + hi4));
-      fxp = br_filter<KT>(A, fxp, hop, x0 + BX + nx * (y0 + lo4) + nxy * (z0 + hi4));
-      fym = br_filter<KT>(A, fym, hop, x0 + lo4 + nx * (y0 - 1) + nxy * (z0 + hi4));
-      fyp = br_filter<KT>(A, fyp, hop, x0 + lo4 + nx * (y0 + BY) + nxy * (z0 + hi4));
-      fzm = br_filter<KT>(A, fzm, hop, x0 + lo4 + nx * (y0 + hi4) + nxy * (z0 - 1));
-      fzp = br_filter<KT>(A, fzp, hop, x0 + lo4 + nx * (y0 + hi4) + nxy * (z0 + BZ));
+      if (r == 1) {
+        fxm = br_filter<KT>(A, fxm, hop, x0 - 1 + nx * (y0 + lo4) + nxy * (z0 + hi4));
+        fxp = br_filter<KT>(A, fxp, hop, x0 + BX + nx * (y0 + lo4) + nxy * (z0 + hi4));
+        fym = br_filter<KT>(A, fym, hop, x0 + lo4 + nx * (y0 - 1) + nxy * (z0 + hi4));
+        fyp = br_filter<KT>(A, fyp, hop, x0 + lo4 + nx * (y0 + BY) + nxy * (z0 + hi4));
+        fzm = br_filter<KT>(A, fzm, hop, x0 + lo4 + nx * (y0 + hi4) + nxy * (z0 - 1));
+        fzp = br_filter<KT>(A, fzp, hop, x0 + lo4 + nx * (y0 + hi4) + nxy * (z0 + BZ));
+      }
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -1262,7 +1288,7 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
       offer(hzp, (mz >> 16) & 1u, fzp, lo4, hi4 + 16 * 15);
     }
     __syncthreads();
-    // The brick's own fixed point: line sweeps along x, y and z.  In round 1
+    // The brick's own fixed point: line sweeps along x, y and z.  In its first round
     // every line is swept (sites were set, keys reset or the pass starts from
     // nothing).  Later a brick's keys are a fixed point of its own relaxation
     // (its last processing ended at one, or the previous pass's result is
@@ -1273,7 +1299,7 @@ __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t 
     // the same iteration, a y sweep's along z.  (`more` is written in the y and
     // z stages only, and read before the x stage's barrier.)
     for (uint32_t it = 1;; ++it) {
-      const bool all = r == 1 && it == 1;
+      const bool all = r <= 2 && it == 1;  // (the brick's first round)
       {  // row t = (ly, lz)
         const uint32_t pd = L.pend[t];
         if (all || pd) {
@@ -2609,10 +2635,11 @@ BRArgs br_args(const Geom &g, CvtWork &W, uint32_t id_bits) {
 // by the previous pass); after each batch the host reads whether any brick
 // is marked.  With narrow keys, a round that stored a key of the largest
 // exact distance sets *far and the pass stops unfinished.
-// Moved sites above which the reset is fused into round 1 (k_br_reset_or_fuse).
-// The separate reset reads every key and lets round 1 work on the bricks
-// that hold reset voxels; the fused one works on every brick in round 1
-// and reads the keys once.  Always fusing takes 108.8 ms for the flame
+// Moved sites above which the reset is fused into the first rounds
+// (k_br_reset_or_fuse).
+// The separate reset reads every key and lets only the bricks that hold reset
+// voxels work first; the fused one works on every brick and reads the keys
+// once.  Always fusing takes 108.8 ms for the flame
 // loop (1024 x 512 x 512, 30 updates), never 113.9, and 1.6 ms less than
 // with 1.25 % of the sites as the limit, so the limit lies lower: a cube
 // of the mean cell volume n / S overlaps about (edge / 16 + 1)^3 bricks,
@@ -2844,7 +2871,7 @@ struct JobDev {
   uint8_t *moved;
   uint32_t *fb_list, *fb_cnt;
   uint32_t first;     // bricks of the jobs before this one
-  uint32_t fuse_min;  // moved sites above which the reset is fused into round 1
+  uint32_t fuse_min;  // moved sites above which the reset is fused into the first rounds
 };
 
 __global__ __launch_bounds__(kVTThreads) void kb_br_masks(const JobDev *J) {
