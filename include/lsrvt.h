@@ -525,7 +525,9 @@ int32_t lsrvt_set_vt_engine(int32_t engine);
  * other two are for tests and experiments):
  *   LSRVT_TUNE_BR_GRID      workgroups of each brick-relaxation round
  *                           (each walks the round's bricks with that stride):
- *                           256 .. 16384, 0 = the library's choice (8192)
+ *                           256 .. 16384, 0 = the library's choice (a
+ *                           workgroup for every brick of the volume up to
+ *                           16384 bricks, 8192 beyond)
  *   LSRVT_TUNE_STATS_TILE   voxels staged in LDS per thread and round by the
  *                           statistics' cell kernel (its tile is this times
  *                           its workgroup size): 1, 2 or 4 (while it fits

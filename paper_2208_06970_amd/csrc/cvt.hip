@@ -1078,7 +1078,13 @@ __global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restr
 // (Rounds that list the next round's bricks themselves, one counter atomic a
 // brick, take 542 us instead of 204 for 16000 bricks: the atomics on one word
 // queue up.)
+// A set round grid (LSRVT_TUNE_BR_GRID) below the number of bricks asks for
+// striding workgroups; one that covers them is a workgroup for every brick.
 constexpr int64_t kDirectBricks = 16384;
+bool direct_rounds(int64_t bricks) {
+  const int64_t tg = tuning(LSRVT_TUNE_BR_GRID);
+  return bricks <= (tg > 0 ? std::min(tg, kDirectBricks) : kDirectBricks);
+}
 
 // The bricks marked for round r, listed (one counter atomic per block).
 __device__ __forceinline__ void d_br_list(const BRArgs &A, uint32_t r) {
@@ -2688,7 +2694,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   }
   const unsigned lgrid = (unsigned)std::min<int64_t>((bg.nbricks + 255) / 256, 4096);
   const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
-  const bool direct = tg == 0 && !A.dbg && bg.nbricks <= kDirectBricks;
+  const bool direct = !A.dbg && direct_rounds(bg.nbricks);
   const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 8192);
   uint32_t r = 0;
   // Rounds are launched as plain kernels, one each (a captured graph of eight
@@ -3109,8 +3115,7 @@ int32_t batch_loop(const BatchCtx &c, int32_t *status, bool *far, hipStream_t s)
   const unsigned g_round = cap(c.sum_nb, tuning(LSRVT_TUNE_BR_GRID) > 0 ? tuning(LSRVT_TUNE_BR_GRID) : 8192);
   const unsigned g_fin = cap((c.max_nb + 7) / 8 * 8, 65528);
   const unsigned g_near = cap((c.max_sites + 3) / 4, 512), g_far = cap(c.max_sites, 64);
-  const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
-  const bool direct = tg == 0 && c.sum_nb <= kDirectBricks;
+  const bool direct = direct_rounds(c.sum_nb);
   uint32_t rounds_hint = 0;
   for (int32_t t = 0; t <= c.tmax; ++t) {
     hipLaunchKernelGGL(kb_pass_clear<KT>, dim3(g_clear, N), dim3(256), 0, s, dj, t);

@@ -1025,7 +1025,8 @@ extern "C" int32_t lsrvt_los_vt(const uint32_t *d_comp, lsrvt_dims dims, const i
   if (rc || (rc = los_nbh(d_comp, g, W, as_stream(stream)))) return rc;
   int32_t sw[2] = {0, 0};
   rc = los_vt(d_comp, g, d_site_q, d_anchor, n_sites, d_dist, d_src, d_phi, d_cell, sw, W, as_stream(stream));
-  if (!rc && h_sweeps) { h_sweeps[0] = sw[0]; h_sweeps[1] = sw[1]; }
+  for (int k = 0; k < 2; ++k)
+    if (h_sweeps && sw[k]) h_sweeps[k] = sw[k];  // of every stage that ended
   return rc;
 }
 

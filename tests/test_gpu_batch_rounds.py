@@ -14,10 +14,10 @@ from tests.gpu_util import banner, dev, host
 pytestmark = pytest.mark.gpu
 
 SPECS = [((16, 16, 16), 1, 2, 3, 64.0), ((17, 33, 31), 2, 4, 5, 20.0), ((5, 40, 18), 3, 3, 0, 30.0),
-         ((48, 31, 33), 4, 3, 1, 400.0)]
+         ((48, 31, 33), 4, 3, 1, 400.0), ((2, 18, 2200), 5, 3, 2, 60.0)]
 
 
-@pytest.mark.parametrize("grid", [0, 256])
+@pytest.mark.parametrize("grid", [0, 256])  # 256: below the 313 bricks of all jobs, so they are listed
 @pytest.mark.parametrize("reset", [0, 1, 2])
 @pytest.mark.parametrize("bits", [0, 64])
 def test_batch_rounds_match_oracle(grid, reset, bits):

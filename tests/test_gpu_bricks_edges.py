@@ -13,10 +13,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 1), (1, 16, 17), (15, 16, 17), (16, 16, 16), (17, 33, 1), (31, 15, 48),
-                                   (33, 17, 34)])
+                                   (33, 17, 34), (17, 20, 2100)])
 @pytest.mark.parametrize("n_bands", [1, 2, 5])
 @pytest.mark.parametrize("bits", [0, 64])
-@pytest.mark.parametrize("grid", [0, 1024])  # a workgroup for every brick; the marked bricks listed
+@pytest.mark.parametrize("grid", [0, 256])  # 256: the 528 bricks of the last shape are listed
 def test_bricks_at_brick_edges(shape, n_bands, bits, grid):
     rng = np.random.default_rng(sum(shape) + n_bands)
     n = int(np.prod(shape))
