@@ -581,8 +581,8 @@ def bench_los(L, cc, sd, w, n, iters):
     return {"ms": round(ms, 3), "iters": iters, "ms_per_pass": round(ms / (iters + 1), 3),
             "gvox_per_iter_s": round(n * iters / (ms / 1e3) / 1e9, 4), "sweeps": int(r.vt.sweeps[0]),
             "sweeps_first_pass": int(one_pass_sweeps), "dtype": "f64 lengths, exact integer update",
-            "includes": "host synchronisation every 8 sweeps",
-            "roofline": {"bound": "hbm", "kernel": "line-of-sight pass (k_los_mark, k_los_eval, k_los_apply) and update",
+            "includes": "host synchronisations (a batch of sweeps each)",
+            "roofline": {"bound": "hbm", "kernel": "line-of-sight pass (k_los_eval, k_los_apply) and update",
                          "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None,
                          "alg_bytes_per_voxel_pass": LOS_BYTES_PER_VOXEL, "passes": iters + 1}}

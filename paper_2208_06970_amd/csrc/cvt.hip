@@ -1071,7 +1071,7 @@ __global__ __launch_bounds__(256) void k_br_reset_or_fuse(const uint8_t *__restr
 // ends if it is not set.  Larger volumes have the marks listed by a launch
 // before the round (k_br_list) and the round's workgroups stride over the
 // list, so that a round with few bricks does not start a workgroup for every
-// brick.  Loops listed and direct: 256 x 128 x 128 voxels (1024 bricks) with
+// brick.  Loops listed and direct (all kinds of bricks in every round): 256 x 128 x 128 voxels (1024 bricks) with
 // 20 updates 10.1 and 9.3 ms, 256^3 (4096) with 20 updates 16.9 and 16.3,
 // 512 x 256 x 256 (8192) with 10 updates 8.59 and 8.45, 512 x 512 x 256
 // (16384) with 10 updates 12.45 and 12.41, 512^3 (32768) 19.6 and 20.7.
@@ -1204,12 +1204,13 @@ __device__ __forceinline__ void br_spread(uint32_t c, uint32_t *pend, uint32_t *
 //
 // Bound by the sweeps' vector operations and, in the rounds of few bricks, by
 // the chain of LDS accesses and barriers between the axes.  Flame loop
-// (1024 x 512 x 512, 30 updates): 110 ms, the rounds 2.6 ms a pass.  142 ms and
-// 3.3 ms with a changed-voxel loop per lane, edge masks transposed from rows
-// per processing, changes counted at every step of a sweep and 2048
-// workgroups a round.  Six waves a SIMD: 48.9 ms for 10 updates, 49.7 with
-// five, 52.2 with seven and 59.7 with eight (spills); 8192 workgroups (48.9)
-// because the bricks' work is uneven: 53.3 with 2048.
+// (1024 x 512 x 512, 30 updates): 78 ms, the rounds 1.9 ms a pass; 110 ms and
+// 2.6 ms before neighbours took turns and the site update was cut, and 142 ms
+// and 3.3 ms with a changed-voxel loop per lane, edge masks transposed from
+// rows per processing, changes counted at every step of a sweep and 2048
+// workgroups a round.  At the 110 ms form, 10 updates: six waves a SIMD 48.9 ms,
+// 49.7 with five, 52.2 with seven and 59.7 with eight (spills); 2048 workgroups
+// 53.3 instead of 48.9 with 8192, because the bricks' work is uneven.
 template <class KT>
 __device__ __forceinline__ void br_process(const BRArgs &A, int64_t b, uint32_t r, BRLds<KT> &L) {
   using KO = BRKey<KT>;

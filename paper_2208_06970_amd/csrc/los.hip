@@ -331,7 +331,12 @@ __global__ __launch_bounds__(kLosThreads) void k_los_nbh(const uint32_t *__restr
 
 // The wave's tile: blocks b, b + 8, ... run on one XCD, so each gets a run of
 // neighbouring tiles, which share their halos in its L2.
-__device__ __forceinline__ uint32_t my_tile() { return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
+// (the grid's y counts runs of kTileRun tiles: a launch has fewer than 2^32
+// threads along x)
+constexpr uint32_t kTileRun = 1u << 22;
+__device__ __forceinline__ uint32_t my_tile() {
+  return blockIdx.y * kTileRun + (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+}
 
 struct Tile {
   int32_t tx, y0, z0;
@@ -915,7 +920,7 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
   LosArgs A{d_comp, g, d_q, d_anchor, S, d_dist, d_src, W.pd, W.ps, W.nbh, W.blk, W.chg, W.flag, W.ctl + 2,
             W.ctl,
             make_div((uint32_t)g.nx), make_div((uint32_t)g.ny), tx, tx, ty, ntiles};
-  const dim3 gt((ntiles + 7) / 8 * 8), bt(kWave);
+  const dim3 gt(std::min((ntiles + 7) / 8 * 8, kTileRun), (ntiles + kTileRun - 1) / kTileRun), bt(kWave);
   if ((rc = fill<uint32_t>(W.ctl, 2, 0u, s))) return rc;
   if (S) {
     hipLaunchKernelGGL(k_los_check, dim3(gs), dim3(256), 0, s, d_comp, g, d_q, d_anchor, S, W.ctl);
