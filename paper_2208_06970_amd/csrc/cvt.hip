@@ -1875,7 +1875,7 @@ __global__ void k_snap(View cell, Geom g, uint32_t S, Sums sums, uint32_t *sites
 
 // Exact nearest in-cell voxel by growing cubes around the centroid: half-widths
 // up to kSnapNear by one wave (W = 1), from 2 kSnapNear on by a team of W waves.
-// The site's own voxel, which lies in the cell, is a first candidate, and a
+// The site's own voxel, if it lies in the cell, is a first candidate, and a
 // voxel farther from the centroid than the best one so far is left out without
 // being read, in float64 with a margin far above its rounding.  What is read is
 // compared exactly, so the answer is that of the whole search.  The team's waves
@@ -1911,7 +1911,7 @@ __device__ __forceinline__ bool snap_search(const View &cell, Geom g, const unsi
       bestv = v;
     }
   };
-  {
+  if ((int64_t)old < g.n) {  // (lsrvt_update takes any value as a site to be moved)
     const int32_t ox = (int32_t)(old % (uint32_t)g.nx), oy = (int32_t)(old / (uint32_t)g.nx % (uint32_t)g.ny),
                   oz = (int32_t)(old / (uint32_t)g.nx / (uint32_t)g.ny);
     if (cell.id(ox, oy, oz) == s) take(dist(ox, oy, oz), old);
