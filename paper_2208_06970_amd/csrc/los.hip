@@ -20,7 +20,7 @@
 // then takes the preferred candidate within 2^-40 of that shortest one (the
 // site itself first, by id, else the lowest voxel index).
 #include <algorithm>
-#include <vector>
+#include <type_traits>
 
 #include "common.h"
 
@@ -38,8 +38,8 @@ constexpr int kPhiHops = 32;
 constexpr int kRadius = 31;  // the largest cube radius (plus one) kept per voxel (5 bits)
 constexpr int kSpec = 4;     // crossings of a ray looked at together
 
-// A tile of a sweep: 32 x 4 x 4 voxels, one wave, one word of each bit plane
-// per row.  Tiles of 512 voxels give a 3 Mvoxel volume about six waves for
+// A tile of a sweep: 32 x 4 x 4 voxels (along the axes of the bit planes,
+// los_plane), one wave, one word of each bit plane per row.  Tiles of 512 voxels give a 3 Mvoxel volume about six waves for
 // every SIMD, which its chains of dependent loads need.
 constexpr int kTX = 32, kTY = 4, kTZ = 4;
 constexpr int kTWords = kTY * kTZ;
@@ -75,10 +75,32 @@ struct LosArgs {
   uint32_t *last;         // the last sweep of the stage that changed a voxel (1-based)
   uint32_t *err;
   Div dx, dy;             // division by g.nx, g.ny
+  int32_t axis;           // the axis along the words of the bit planes (0: x)
+  int32_t pa, pb, pc;     // extents along it and the other two (in the order x, y, z)
   int32_t pw;             // words of a row of a bit plane
-  int32_t tx, ty;         // tiles along x, y
+  int32_t ty;             // tiles along the second
   uint32_t ntiles;
 };
+
+// Plane coordinates of (x, y, z), and the coordinates of (a, b, c).
+template <bool Turned>
+__device__ __forceinline__ void to_plane(const LosArgs &A, int32_t x, int32_t y, int32_t z, int32_t &a, int32_t &b,
+                                         int32_t &c) {
+  a = !Turned || A.axis == 0 ? x : A.axis == 1 ? y : z;
+  b = !Turned || A.axis == 0 ? y : x;
+  c = !Turned || A.axis != 2 ? z : y;
+}
+template <bool Turned>
+__device__ __forceinline__ void from_plane(const LosArgs &A, int32_t a, int32_t b, int32_t c, int32_t &x, int32_t &y,
+                                           int32_t &z) {
+  x = !Turned || A.axis == 0 ? a : b;
+  y = !Turned || A.axis == 0 ? b : A.axis == 1 ? a : c;
+  z = !Turned || A.axis != 2 ? c : a;
+}
+// The word of row (b, c) that holds place 32 i.
+__device__ __forceinline__ int64_t plane_word(const LosArgs &A, int32_t i, int32_t b, int32_t c) {
+  return i + (int64_t)A.pw * (b + (int64_t)A.pb * c);
+}
 
 __device__ __forceinline__ void xyz(uint32_t u, const LosArgs &A, int32_t &x, int32_t &y, int32_t &z) {
   const uint32_t row = quot(u, A.dx);
@@ -264,7 +286,9 @@ __global__ void k_anchor_set(LosArgs A) {
   // the anchors' neighbourhoods are evaluated in the first sweep
   int32_t x, y, z;
   xyz(a, A, x, y, z);
-  atomicOr(&A.flag[x / 32 + A.pw * (y + A.g.ny * z)], 1u << (x & 31));
+  int32_t pa, pb, pc;
+  to_plane<true>(A, x, y, z, pa, pb, pc);
+  atomicOr(&A.flag[plane_word(A, pa / 32, pb, pc)], 1u << (pa & 31));
 }
 
 // ---------------------------------------------------------------- cube radii
@@ -339,11 +363,11 @@ __device__ __forceinline__ uint32_t my_tile() {
 }
 
 struct Tile {
-  int32_t tx, y0, z0;
+  int32_t tx, y0, z0;  // word along the planes' rows, first row along the other two axes
 };
 __device__ __forceinline__ Tile tile_at(const LosArgs &A, uint32_t t) {
-  const uint32_t q = t / (uint32_t)A.tx;
-  return Tile{(int32_t)(t - q * (uint32_t)A.tx), (int32_t)(q % (uint32_t)A.ty) * kTY, (int32_t)(q / (uint32_t)A.ty) * kTZ};
+  const uint32_t q = t / (uint32_t)A.pw;
+  return Tile{(int32_t)(t - q * (uint32_t)A.pw), (int32_t)(q % (uint32_t)A.ty) * kTY, (int32_t)(q / (uint32_t)A.ty) * kTZ};
 }
 
 // The set bits of the tile's words as a list of (word << 5 | bit), in order;
@@ -538,7 +562,7 @@ __device__ __forceinline__ bool los_eval(const LosArgs &A, int32_t x, int32_t y,
 // remembered, 22.3 with each lane's own candidates, 19.0 with packed rays over
 // neighbourhood words, 17.4 with fewer waits by the host.  (Tiles of 256 voxels
 // instead of 512 cost 20.3 instead of 19.0, five waves a SIMD 19.5.)
-template <int Stage>
+template <int Stage, bool Turned>
 __global__ __launch_bounds__(kWave, 4) void k_los_eval(LosArgs A, uint32_t sweep, int all_dirty) {
   __shared__ uint16_t list[kTWords * 32];
   __shared__ uint32_t chg[kTWords];
@@ -550,22 +574,24 @@ __global__ __launch_bounds__(kWave, 4) void k_los_eval(LosArgs A, uint32_t sweep
   const int lane = lane_id();
   const Tile T = tile_at(A, t);
   const int row = lane / kLanes, y = T.y0 + row % kTY, z = T.z0 + row / kTY;
-  const bool in = y < A.g.ny && z < A.g.nz;
-  const int64_t at = T.tx + (int64_t)A.pw * (y + (int64_t)A.g.ny * z);
+  const bool in = y < A.pb && z < A.pc;
+  const int64_t at = plane_word(A, T.tx, y, z);
   uint32_t w = 0;
   if (in) {
     const uint32_t *F = A.flag + at;
-    const int64_t py = A.pw, pz = (int64_t)A.pw * A.g.ny;
-    const int left = A.g.nx - T.tx * kTX;
+    const int64_t py = A.pw, pz = (int64_t)A.pw * A.pb;
+    const int left = A.pa - T.tx * kTX;
     const uint32_t valid = left >= 32 ? ~0u : (1u << left) - 1u;
     const uint32_t m = F[0], xl = T.tx > 0 ? F[-1] : 0u, xr = T.tx < A.pw - 1 ? F[1] : 0u;
-    const uint32_t f[6] = {m << 1 | xl >> 31,           m >> 1 | xr << 31,          y > 0 ? F[-py] : 0u,
-                           y < A.g.ny - 1 ? F[py] : 0u, z > 0 ? F[-pz] : 0u, z < A.g.nz - 1 ? F[pz] : 0u};
+    const uint32_t f[6] = {m << 1 | xl >> 31,        m >> 1 | xr << 31,       y > 0 ? F[-py] : 0u,
+                           y < A.pb - 1 ? F[py] : 0u, z > 0 ? F[-pz] : 0u, z < A.pc - 1 ? F[pz] : 0u};
+    // the axes of the plane in the volume, whose face neighbours are numbered x-, x+, y-, y+, z-, z+
+    const int ax[3] = {Turned ? A.axis : 0, Turned && A.axis ? 0 : 1, Turned && A.axis == 2 ? 1 : 2};
     w = m;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
       w |= f[i];
-      if (lane % kLanes == 0) nbf[i][row] = f[i];
+      if (lane % kLanes == 0) nbf[2 * ax[i / 2] + i % 2][row] = f[i];
     }
     w = (all_dirty ? ~0u : w) & valid;
   }
@@ -578,21 +604,24 @@ __global__ __launch_bounds__(kWave, 4) void k_los_eval(LosArgs A, uint32_t sweep
     for (int k = 0; k < 6; ++k) f |= (nbf[k][e >> 5] >> (e & 31) & 1u) << k;
     return f;
   };
+  auto eval = [&](uint32_t e, auto probe) {
+    const uint32_t r = e >> 5;
+    int32_t vx, vy, vz;
+    from_plane<Turned>(A, T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY), T.z0 + (int)(r / kTY), vx, vy, vz);
+    return los_eval<Stage, decltype(probe)::value>(A, vx, vy, vz, fresh(e), cds, code, aim);
+  };
   uint32_t some = 0;  // listed voxels that have a candidate, moved to the front
   for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
-    const uint32_t e = i0 + lane < n ? list[i0 + lane] : 0u, r = e >> 5;
-    const bool yes = i0 + lane < n && los_eval<Stage, true>(A, T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY),
-                                                            T.z0 + (int)(r / kTY), fresh(e), cds, code, aim);
+    const uint32_t e = i0 + lane < n ? list[i0 + lane] : 0u;
+    const bool yes = i0 + lane < n && eval(e, std::true_type{});
     const uint64_t bal = __ballot(yes);
     if (yes) list[some + (uint32_t)__popcll(bal & lanemask_lt())] = (uint16_t)e;
     some += (uint32_t)__popcll(bal);
   }
   __syncthreads();
   for (uint32_t i = lane; i < some; i += kWave) {
-    const uint32_t e = list[i], r = e >> 5;
-    if (los_eval<Stage, false>(A, T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY), T.z0 + (int)(r / kTY), fresh(e),
-                               cds, code, aim))
-      atomicOr(&chg[r], 1u << (e & 31));
+    const uint32_t e = list[i];
+    if (eval(e, std::false_type{})) atomicOr(&chg[e >> 5], 1u << (e & 31));
   }
   __syncthreads();
   const uint32_t out = chg[row];
@@ -603,7 +632,7 @@ __global__ __launch_bounds__(kWave, 4) void k_los_eval(LosArgs A, uint32_t sweep
 // Installs the proposals of a tile and writes its words of the flag plane.  In
 // stage 1 no voxel has another voxel as its source, so only the changed ones
 // are touched; stage 2 reads the source of every voxel and its change bit.
-template <int Stage>
+template <int Stage, bool Turned>
 __global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) {
   __shared__ uint16_t list[kTWords * 32];
   const uint32_t t = my_tile();
@@ -611,17 +640,21 @@ __global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) 
   const int lane = lane_id();
   const Tile T = tile_at(A, t);
   const int row = lane / kLanes, yy = T.y0 + row % kTY, zz = T.z0 + row / kTY;
-  const bool in = yy < A.g.ny && zz < A.g.nz;
-  const int64_t at = T.tx + (int64_t)A.pw * (yy + (int64_t)A.g.ny * zz);
+  const bool in = yy < A.pb && zz < A.pc;
+  const int64_t at = plane_word(A, T.tx, yy, zz);
   const uint32_t w = in ? A.chg[at] : 0u;
-  const int64_t sy = A.g.nx, sz = (int64_t)A.g.nx * A.g.ny;
+  auto voxel = [&](int32_t a, int32_t b, int32_t c) {
+    int32_t x, y, z;
+    from_plane<Turned>(A, a, b, c, x, y, z);
+    return x + (int64_t)A.g.nx * (y + (int64_t)A.g.ny * z);
+  };
   if (Stage == 1) {
     if (in && lane % kLanes == 0) A.flag[at] = w;
     const uint32_t n = tile_list(w, list);
     __syncthreads();
     for (uint32_t i = lane; i < n; i += kWave) {
       const uint32_t e = list[i], r = e >> 5;
-      const int64_t v = T.tx * kTX + (int)(e & 31) + sy * (T.y0 + (int)(r % kTY)) + sz * (T.z0 + (int)(r / kTY));
+      const int64_t v = voxel(T.tx * kTX + (int)(e & 31), T.y0 + (int)(r % kTY), T.z0 + (int)(r / kTY));
       A.d[v] = A.pd[v];
       A.src[v] = A.ps[v];
     }
@@ -632,8 +665,8 @@ __global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) 
 #pragma unroll
   for (int k = 0; k < kTWords / 2; ++k) {
     const int r = 2 * k + half, y = T.y0 + r % kTY, z = T.z0 + r / kTY;
-    const bool ok = x < A.g.nx && y < A.g.ny && z < A.g.nz;
-    const int64_t v = x + sy * y + sz * z;
+    const bool ok = x < A.pa && y < A.pb && z < A.pc;
+    const int64_t v = voxel(x, y, z);
     const bool ch = (__shfl(w, kLanes * r, kWave) >> (lane & 31)) & 1u;
     s[k] = !ok ? kNone : ch ? A.ps[v] : A.src[v];
     if (ch) {
@@ -646,9 +679,10 @@ __global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) 
   for (int k = 0; k < kTWords / 2; ++k) {
     sc[k] = 0u;
     if (s[k] != kNone && !(s[k] & kSite)) {
-      int32_t ux, uy, uz;
+      int32_t ux, uy, uz, ua, ub, uc;
       xyz(s[k], A, ux, uy, uz);
-      sc[k] = A.chg[ux / 32 + (int64_t)A.pw * (uy + (int64_t)A.g.ny * uz)] >> (ux & 31);
+      to_plane<Turned>(A, ux, uy, uz, ua, ub, uc);
+      sc[k] = A.chg[plane_word(A, ua / 32, ub, uc)] >> (ua & 31);
     }
   }
 #pragma unroll
@@ -656,7 +690,7 @@ __global__ __launch_bounds__(kWave) void k_los_apply(LosArgs A, uint32_t sweep) 
     const int r = 2 * k + half, y = T.y0 + r % kTY, z = T.z0 + r / kTY;
     const uint64_t bal = __ballot((sc[k] & 1u) != 0u);
     const uint32_t f = (uint32_t)(bal >> (32 * half)) | __shfl(w, kLanes * r, kWave);
-    if ((lane & 31) == 0 && y < A.g.ny && z < A.g.nz) A.flag[T.tx + (int64_t)A.pw * (y + (int64_t)A.g.ny * z)] = f;
+    if ((lane & 31) == 0 && y < A.pb && z < A.pc) A.flag[plane_word(A, T.tx, y, z)] = f;
   }
 }
 
@@ -870,13 +904,36 @@ struct LosWork {
   unsigned long long *acc;
 };
 
+// The bit planes and their tiles: words along x, or, when x is too short to
+// fill them, along the longer of the other two axes if that is longer.  A tile
+// is a wave, so in a volume of one voxel along x words along x leave 16 voxels
+// to each of 32 times as many waves.  One update with words along x and along
+// the longer axis: 1 x 1024 x 1024 voxels 63.3 and 25.7 ms, 2 x 1024 x 1024
+// 44.6 and 19.6, 4 x 512 x 512 14.0 and 10.7, 6 x 512 x 512 11.3 and 9.2;
+// 8 x 400 x 300 6.1 and 6.0, 16 x 256 x 300 6.4 and 6.9, 24 x 256 x 200 6.2 and
+// 6.8 (neighbours along the words lie nx apart in memory): from 8 on, x.
+struct LosPlane {
+  int32_t axis, pa, pb, pc, pw, ty, tz;
+};
+constexpr int32_t kTurn = 8;
+LosPlane los_plane(const Geom &g) {
+  LosPlane P{0, g.nx, g.ny, g.nz, 0, 0, 0};
+  if (g.nx < kTurn && std::max(g.ny, g.nz) > g.nx)
+    P = g.ny >= g.nz ? LosPlane{1, g.ny, g.nx, g.nz, 0, 0, 0} : LosPlane{2, g.nz, g.nx, g.ny, 0, 0, 0};
+  P.pw = (P.pa + kTX - 1) / kTX;
+  P.ty = (P.pb + kTY - 1) / kTY;
+  P.tz = (P.pc + kTZ - 1) / kTZ;
+  return P;
+}
+
 template <class C>
 void los_layout(C &cv, const Geom &g, uint32_t S, LosWork *W) {
   double *pd = cv.template take<double>((size_t)g.n);
   uint32_t *ps = cv.template take<uint32_t>((size_t)g.n);
   uint32_t *nbh = cv.template take<uint32_t>((size_t)g.n);
   uint8_t *blk = cv.template take<uint8_t>((size_t)g.n);
-  const size_t words = (size_t)((g.nx + 31) / 32) * g.ny * g.nz;
+  const LosPlane P = los_plane(g);
+  const size_t words = (size_t)P.pw * P.pb * P.pc;
   uint32_t *chg = cv.template take<uint32_t>(words);
   uint32_t *flag = cv.template take<uint32_t>(words);
   uint32_t *ctl = cv.template take<uint32_t>(64);
@@ -915,11 +972,11 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
   int32_t rc;
   const unsigned gs = grid_for(S, 256, 1 << 20);
   const unsigned gv = (unsigned)((g.n + kLosThreads - 1) / kLosThreads);
-  const int32_t tx = (g.nx + kTX - 1) / kTX, ty = (g.ny + kTY - 1) / kTY, tz = (g.nz + kTZ - 1) / kTZ;
-  const uint32_t ntiles = (uint32_t)tx * (uint32_t)ty * (uint32_t)tz;
+  const LosPlane P = los_plane(g);
+  const uint32_t ntiles = (uint32_t)P.pw * (uint32_t)P.ty * (uint32_t)P.tz;
   LosArgs A{d_comp, g, d_q, d_anchor, S, d_dist, d_src, W.pd, W.ps, W.nbh, W.blk, W.chg, W.flag, W.ctl + 2,
             W.ctl,
-            make_div((uint32_t)g.nx), make_div((uint32_t)g.ny), tx, tx, ty, ntiles};
+            make_div((uint32_t)g.nx), make_div((uint32_t)g.ny), P.axis, P.pa, P.pb, P.pc, P.pw, P.ty, ntiles};
   const dim3 gt(std::min((ntiles + 7) / 8 * 8, kTileRun), (ntiles + kTileRun - 1) / kTileRun), bt(kWave);
   if ((rc = fill<uint32_t>(W.ctl, 2, 0u, s))) return rc;
   if (S) {
@@ -930,7 +987,7 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
   if ((rc = fill<double>(d_dist, g.n, __builtin_inf(), s))) return rc;
   if ((rc = fill<uint32_t>(d_src, g.n, kNone, s))) return rc;
   if ((rc = fill<uint8_t>(W.blk, g.n, 0, s))) return rc;
-  if ((rc = fill<uint32_t>(W.flag, (int64_t)tx * g.ny * g.nz, 0u, s))) return rc;
+  if ((rc = fill<uint32_t>(W.flag, (int64_t)P.pw * P.pb * P.pc, 0u, s))) return rc;
   if (S) {
     hipLaunchKernelGGL(k_anchor_reset, dim3(gs), dim3(256), 0, s, A);
     hipLaunchKernelGGL(k_anchor_len, dim3(gs), dim3(256), 0, s, A);
@@ -948,14 +1005,14 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
       if (launched >= (uint32_t)kMaxSweeps) return LSRVT_ELIMIT;
       for (int32_t j = 0; j < batch; ++j) {
         ++launched;
-        if (stage == 1) {
-          hipLaunchKernelGGL(k_los_eval<1>, gt, bt, 0, s, A, launched, 0);
-          hipLaunchKernelGGL(k_los_apply<1>, gt, bt, 0, s, A, launched);
-        } else {
-          // the first sweep of stage 2 re-evaluates everything: new candidates
-          hipLaunchKernelGGL(k_los_eval<2>, gt, bt, 0, s, A, launched, launched == 1 ? 1 : 0);
-          hipLaunchKernelGGL(k_los_apply<2>, gt, bt, 0, s, A, launched);
-        }
+        // the first sweep of stage 2 re-evaluates everything: new candidates
+        const int all = stage == 2 && launched == 1;
+        hipLaunchKernelGGL((stage == 1 ? P.axis ? k_los_eval<1, true> : k_los_eval<1, false>
+                                       : P.axis ? k_los_eval<2, true> : k_los_eval<2, false>),
+                           gt, bt, 0, s, A, launched, all);
+        hipLaunchKernelGGL((stage == 1 ? P.axis ? k_los_apply<1, true> : k_los_apply<1, false>
+                                       : P.axis ? k_los_apply<2, true> : k_los_apply<2, false>),
+                           gt, bt, 0, s, A, launched);
       }
       LSRVT_LAUNCHED();
       if ((rc = read_words(A.last, 1, &last, s))) return rc;
