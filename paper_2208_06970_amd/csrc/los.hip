@@ -1003,7 +1003,7 @@ int32_t los_vt(const uint32_t *d_comp, const Geom &g, const int32_t *d_q, const 
     if ((rc = fill<uint32_t>(A.last, 1, 0u, s))) return rc;
     while (launched == last) {
       if (launched >= (uint32_t)kMaxSweeps) return LSRVT_ELIMIT;
-      for (int32_t j = 0; j < batch; ++j) {
+      for (int32_t j = 0; j < batch && launched < (uint32_t)kMaxSweeps; ++j) {
         ++launched;
         // the first sweep of stage 2 re-evaluates everything: new candidates
         const int all = stage == 2 && launched == 1;
