@@ -16,8 +16,9 @@ changes what is computed):
   tuned per job class by timing a short Lloyd loop (or one Voronoi pass)
   or one statistics call.
 
-A job class is (GPU name, log2 of the voxel count, log2 of voxels per site,
-band count bucket).  Results are kept in a JSON file (``LSRVT_AUTOTUNE_CACHE``,
+A job class is (GPU name, build of the library, log2 of the voxel count, log2
+of voxels per site, band count bucket): another build has other kernels, so
+what it measured says nothing about this one.  Results are kept in a JSON file (``LSRVT_AUTOTUNE_CACHE``,
 by default ``~/.cache/lsrvt/autotune.json``), read once per process and
 rewritten atomically (write to a temporary file, then rename) under a lock
 file, so concurrent processes share it safely.  Nothing here changes what is
@@ -25,6 +26,7 @@ computed: every candidate gives bit-identical results.
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import math
 import os
@@ -34,11 +36,12 @@ import time
 
 import numpy as np
 
-from . import (TUNE_BR_GRID, TUNE_STATS_TILE, VT_BRICKS, VT_LEVELS, lsrvt_set_tuning, lsrvt_set_vt_engine,
-               lsrvt_vt)
+from . import (LIB_PATH, TUNE_BR_GRID, TUNE_STATS_TILE, VT_BRICKS, VT_LEVELS, lsrvt_set_tuning,
+               lsrvt_set_vt_engine, lsrvt_vt)
 
 _LOCK = threading.Lock()
 _CACHE = None
+_BUILD = None
 
 
 def cache_path() -> str:
@@ -52,6 +55,18 @@ def _device_name() -> str:
         return torch.cuda.get_device_properties(torch.cuda.current_device()).name.replace(" ", "_")
     except Exception:  # pragma: no cover
         return "unknown"
+
+
+def _build_tag() -> str:
+    """Eight hex digits that change with the built library."""
+    global _BUILD
+    if _BUILD is None:
+        try:
+            with open(LIB_PATH, "rb") as fh:
+                _BUILD = hashlib.sha256(fh.read()).hexdigest()[:8]
+        except OSError:
+            _BUILD = "none"
+    return _BUILD
 
 
 def _load() -> dict:
@@ -94,7 +109,7 @@ def _store(key: str, value) -> None:
 def job_class(shape, n_sites: int, n_bands: int) -> str:
     n = int(np.prod(shape))
     vps = n / max(int(n_sites), 1)
-    return (f"vt:{_device_name()}:n2^{int(round(math.log2(max(n, 1))))}:"
+    return (f"vt:{_device_name()}:lib{_build_tag()}:n2^{int(round(math.log2(max(n, 1))))}:"
             f"vps2^{int(round(math.log2(max(vps, 1.0))))}:bands{min(int(n_bands), 16)}")
 
 
@@ -157,8 +172,9 @@ def batch_streams(make_jobs, candidates=(2, 4, 8), key: str | None = None, ws=No
     import torch
     from . import lsrvt_batch_run
     if key is not None:
+        key = f"batch:{_device_name()}:lib{_build_tag()}:{key}"
         with _LOCK:
-            hit = _load().get(f"batch:{_device_name()}:{key}")
+            hit = _load().get(key)
         if hit is not None:
             return int(hit["streams"])
     times = {}
@@ -172,8 +188,7 @@ def batch_streams(make_jobs, candidates=(2, 4, 8), key: str | None = None, ws=No
     best = min(times, key=times.get)
     if key is not None:
         with _LOCK:
-            _store(f"batch:{_device_name()}:{key}", {"streams": best,
-                                                     "ms": {str(k): round(v * 1e3, 3) for k, v in times.items()}})
+            _store(key, {"streams": best, "ms": {str(k): round(v * 1e3, 3) for k, v in times.items()}})
     return best
 
 
