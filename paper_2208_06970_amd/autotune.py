@@ -208,10 +208,16 @@ def _time(fn, reps: int = 2) -> float:
     return (time.perf_counter() - t0) / reps
 
 
-def br_grid(band, sites, n_bands: int, candidates=(1024, 2048, 4096, 8192), tune: bool = True, comp=None,
+_GRIDS = (1024, 2048, 4096, 8192)
+_DIRECT_BRICKS = 16384  # the largest volume whose rounds may start a workgroup for every brick
+
+
+def br_grid(band, sites, n_bands: int, candidates=_GRIDS, tune: bool = True, comp=None,
             weights=None, iters: int = 2) -> int | None:
     """Workgroups per relaxation round for this job class: cached, or
-    measured now with each candidate by brick relaxation — a short Lloyd
+    measured now with each candidate (and, of the default ones, with a
+    workgroup for every brick where only a larger grid gives that, as the
+    library does by itself) by brick relaxation — a short Lloyd
     loop (`iters` updates: one full pass, then incremental ones, which
     dominate a long loop) when the components `comp` are given, else one
     Voronoi pass."""
@@ -222,6 +228,9 @@ def br_grid(band, sites, n_bands: int, candidates=(1024, 2048, 4096, 8192), tune
     if not tune:
         return None
     from . import lsrvt_cvt
+    bricks = math.prod(-(-int(n) // 16) for n in band.shape)
+    if candidates is _GRIDS and max(_GRIDS) < bricks <= _DIRECT_BRICKS:
+        candidates += (_DIRECT_BRICKS,)
     if comp is not None:
         def run():
             lsrvt_cvt(band, comp, sites, weights, iters, want_mean_ds=False)

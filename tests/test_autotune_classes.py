@@ -1,6 +1,7 @@
 """Which cached choices and which candidates the autotuner takes (host logic,
 no GPU): an entry that another build of the library wrote is not taken, since a
-change of kernels changes what is fastest."""
+change of kernels changes what is fastest, and a class of more bricks than the
+usual relaxation grids hold also tries the one that covers them."""
 import json
 import types
 
@@ -43,3 +44,16 @@ def test_entries_of_another_library_are_ignored(cache, monkeypatch):
     monkeypatch.setattr(at, "_BUILD", None)
     assert at.job_class((64, 64, 64), 512, 5) != key
     assert at.vt_engine(band, sites, 5, tune=False) is None
+
+
+@pytest.mark.parametrize("shape,most", [((64, 64, 64), 8192), ((512, 256, 256), 8192), ((512, 512, 160), 16384),
+                                        ((512, 512, 256), 16384), ((512, 512, 257), 8192), ((512, 512, 1024), 8192)])
+def test_grids_that_cover_the_bricks_are_tried(cache, monkeypatch, shape, most):
+    grids = []
+    monkeypatch.setattr(at, "lsrvt_set_tuning", lambda knob, v: grids.append(v) or 0)
+    monkeypatch.setattr(at, "lsrvt_set_vt_engine", lambda e: 0)
+    monkeypatch.setattr(at, "_time", lambda fn, reps=2: -float(grids[-1]))  # the largest grid is the fastest
+    band, sites = _job(shape, 4096)
+    assert at.br_grid(band, sites, 5) == most
+    assert {1024, 2048, 4096, 8192} <= set(grids)
+    assert at.br_grid(band, sites, 5, tune=False) == most
