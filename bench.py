@@ -245,9 +245,10 @@ def bench_flame(args):
     _log("flame: tuning launch shapes")
     grid = autotune.br_grid(band, sd, wl.n_bands, comp=cc.comp, weights=w)
     r1 = L.lsrvt_cvt(band, cc.comp, sd, w, 1, want_mean_ds=False)
+    # (four voxels a thread of 18 variables and their 32-bin histograms do not fit in LDS)
     tile = autotune.stats_tile(tuple(band.shape), len(seeds), wl.n_bands, int(x.shape[0]),
                                lambda: L.lsrvt_aggregate(r1.cell, r1.sites, r1.site_comp, cc.comp_band, cc.n_comp,
-                                                         wl.n_bands, x, e, cov=True))
+                                                         wl.n_bands, x, e, cov=True), candidates=(1, 2))
     del r1
     _log(f"flame: relaxation grid {grid}, statistics tile {tile} voxels per thread")
     with autotune.shapes(br_grid=grid, stats_tile=tile):
