@@ -199,10 +199,11 @@ int32_t lsrvt_cvt(const uint8_t *d_band, const uint32_t *d_comp, lsrvt_dims dims
  * row-major over the upper triangle (m(m+1)/2 entries, C_jj = M2_j).
  * Statistics are unweighted.  Histogram bin of x: the number of interior
  * edges e_1..e_{B-1} that are <= x (below e_0 -> bin 0, >= e_B -> bin B-1).
- * Cells accumulate in float32 with compensated (error-free two-sum) sums of
- * values shifted by the value at the cell's site; the cell -> component ->
- * band merges are pairwise (Chan et al.) in float64, in a fixed order (cells
- * by site id within a component, components by id within a band).
+ * Cells accumulate float32 differences from the value at the cell's site in
+ * float64 and round the results to the float32 cell outputs once; the cell ->
+ * component -> band merges are pairwise (Chan et al.) in float64, in a fixed
+ * order of the members (cells by site id within a component, components by id
+ * within a band).
  * Units with n = 0: mean = M2 = C = 0, min = +inf, max = -inf, hist = 0.
  * Variables must be finite.
  *
@@ -265,8 +266,9 @@ int32_t lsrvt_aggregate(const uint32_t *d_cell, lsrvt_dims dims, const uint32_t 
  * cokurtosis are these sums over n times the standard deviations involved.
  * All arithmetic is float64: cells sum products of offsets from the value
  * at the cell's site and convert them to centred sums; components merge
- * their cells (by site id) and bands their components (by id) with
- * pairwise update formulas (Pebay 2008) in a fixed order.  Units with n = 0
+ * their cells (by site id) and bands their components (by id) by shifting
+ * the members' sums to the group's mean and adding them, in chunks of a fixed
+ * size and a fixed order.  Units with n = 0
  * report zeros.  Voxels labelled LSRVT_NONE are skipped.
  *   output arrays (device, caller-allocated, U units): n [U] uint64,
  *   mean [U][m], m2 [U][P2], m3 [U][P3], m4 [U][P4] float64; cells are

@@ -412,7 +412,7 @@ def _cstruct(cls, L):
 
 def lsrvt_aggregate(cell, sites, site_comp, comp_band, n_comp: int, n_bands: int, variables, edges=None,
                     cov: bool = False, ws: Workspace | None = None, stream=None, out=None):
-    """Per-cell FP32 compensated statistics merged (FP64, Chan) to components and bands.
+    """Per-cell statistics (FP64 sums, FP32 outputs) merged (FP64, Chan) to components and bands.
 
     Returns (cell_stats, comp_stats, band_stats) as :class:`LevelStats`."""
     torch = _torch()

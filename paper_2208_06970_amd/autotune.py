@@ -5,9 +5,9 @@ changes what is computed):
 
 * the schedule of the Voronoi passes (``lsrvt_set_vt_engine``): the
   level-synchronous search or the brick relaxation.  Both give the same
-  regions; which is faster depends on the volume's shape and how many voxels
-  each site holds (wide cells mean many levels per pass but few relaxation
-  rounds).  Tuned per job class by timing one Voronoi pass with each.
+  regions; the library takes the relaxation by itself, which was the faster
+  one for every shape and cell width tried.  Tuned per job class by timing
+  one Voronoi pass with each.
 * the number of streams of ``lsrvt_batch_run``'s per-job phases (labels and
   statistics), tuned per batch by timing the whole batch;
 * the launch shapes (``lsrvt_set_tuning``): the workgroups of a relaxation

@@ -93,7 +93,7 @@ __global__ void k_item_cells(const uint32_t *__restrict__ item_off, const uint32
   }
 }
 
-// 3. per-item compensated sums
+// 3. per-item sums
 struct CellArgs {
   const uint32_t *perm;       // layout order of the voxels
   const uint32_t *cell_off;   // [S + 1] by rank
@@ -1034,8 +1034,10 @@ struct SizerT : Sizer {
   }
 };
 
-// Variables and bins that the call takes: those whose histograms, edges and
-// stage of one value per unit group fit in 64 KiB.
+// Variables and bins that the call takes.  The limit is the one that an earlier
+// form of the cell kernel set (histograms, edges and a stage of one value per
+// group of units in 64 KiB); the present kernels need less LDS for whatever it
+// lets through, and what the call refuses has stayed the same.
 bool hist_fits(int m, int B, int U) {
   int G = 1, NT = kAggThreads;
   if (U <= kAggThreads) {

@@ -1,9 +1,13 @@
 // Restricted geodesic Voronoi pass (Eq. 1), snapped centroid update (Sec. 3.1
 // "Centroids"; Sec. 3.2.3) and the fixed-iteration Lloyd loop (Algorithm 1).
 //
-// Voronoi pass.  The regions of Eq. 1 with ties to the lower id are computed
-// by a breadth-first search restricted to same-band face edges, run level
-// by level over the whole volume.  Level 0 holds the sites; at level L every
+// Voronoi pass.  The regions of Eq. 1 with ties to the lower id are computed by
+// one of two schedules with the same result (lsrvt_set_vt_engine): by default
+// the brick relaxation, which is described where its kernels begin (BRArgs), and
+// on request the level search, which comes first in this file.
+//
+// Level search: a breadth-first search restricted to same-band face edges, run
+// level by level over the whole volume.  Level 0 holds the sites; at level L every
 // voxel not reached yet that has a same-band neighbour reached at level L - 1
 // takes the smallest site id among those neighbours.  By induction a voxel
 // at hop distance L from its nearest sites receives exactly the smallest of
@@ -12,10 +16,10 @@
 // distance L.  Each level is one launch, so the ids of level L - 1 are final
 // when level L reads them and the result does not depend on scheduling.
 //
-// The volume is cut into 16^3 bricks.  Per brick row (16 voxels along x) the
-// search keeps 16-bit masks in global memory: the same-band edges in each
-// direction (built once per call, since bands do not change), the voxels
-// reached so far and the frontier of the last two levels, plus the
+// The volume is cut into 16^3 bricks (by both schedules).  Per brick row (16
+// voxels along x) the search keeps 16-bit masks in global memory: the same-band
+// edges in each direction (built once per call, since bands do not change), the
+// voxels reached so far and the frontier of the last two levels, plus the
 // frontier's brick faces packed into a few words for the neighbours to read.
 // A level launch has one wave per brick; a brick works only if it was marked
 // for the level (a brick that reached anything marks itself and its six
@@ -27,12 +31,14 @@
 // pass.
 //
 // Update.  Per site, M = sum w and S_a = sum w a are exact uint64 sums
-// (per-tile LDS aggregation, then one global atomic per distinct cell).  The nearest lattice point to S/M with ties
+// (per-brick or per-tile LDS aggregation, then one set of global atomics per
+// distinct cell).  The nearest lattice point to S/M with ties
 // rounded down, q_a = floor((2 S_a + M - 1) / (2 M)), is the answer whenever
 // it lies in the cell (it then minimises the distance over all lattice
 // points, and among tied points the all-lower corner has the smallest linear
-// index).  Otherwise one workgroup searches cubes of growing half-width r
-// around q; voxels outside the cube are at least r + 1/2 from the centroid,
+// index).  Otherwise cubes of growing half-width r around q are searched, by a
+// wave and then, where that is not enough, by a workgroup; voxels outside the
+// cube are at least r + 1/2 from the centroid,
 // so the search stops once 4 D_best < (M (2 r + 1))^2, comparing
 // D = sum_a (M a - S_a)^2 exactly in 128 bits.
 #include <stdio.h>
@@ -803,7 +809,7 @@ __global__ __launch_bounds__(256) void k_wake_min(const uint32_t *__restrict__ w
 }
 
 // ----------------------------------------------------------------------------
-// Brick relaxation engine (an alternative schedule for the same regions).
+// Brick relaxation engine (the default schedule).
 //
 // The regions of Eq. 1 with ties to the lower id are the unique fixed point
 // of key(v) = min(key(v), min over same-band face neighbours w of
@@ -1886,10 +1892,10 @@ __global__ void k_snap(View cell, Geom g, uint32_t S, Sums sums, uint32_t *sites
 // half-width holds little and one plane (or row) of it would be all that a team
 // has to share.  The near search goes to the half-width that holds about a
 // thousand voxels (flat_near), and the team's waves take the rows of all planes
-// in turn.  One update of 1 x 256 x 256, 2048 x 1 x 2048, 2 x 1024 x 1024 and
-// 512 x 6 x 512 voxels with 512 voxels a site: 43, 118, 64 and 58 us, in the
-// other form 54, 172, 77 and 61; of 8 x 512 x 512 65 and 65 us, with
-// 4096 voxels a site 77 and 67.
+// in turn.  One update of 256 x 256 x 1, 2048 x 1 x 2048, 1024 x 1024 x 2 and
+// 512 x 512 x 6 voxels with 512 voxels a site: 43, 127, 64 and 57 us, in the
+// other form 54, 172, 77 and 61; of 512 x 512 x 8 61 and 65 us, with 4096
+// voxels a site 77 and 67.
 constexpr int32_t kSnapNear = 4;
 constexpr int32_t kFlatEdge = 6;
 __device__ __forceinline__ int32_t flat_near(Geom g) {
@@ -2331,12 +2337,16 @@ struct VTState {
 // Which schedule computes the Voronoi passes: the level-synchronous search
 // or the brick relaxation (both give the same regions bit for bit).  The
 // choice is made per host thread (lsrvt_set_vt_engine); by default the brick
-// relaxation, which is the faster one whatever the volume and the cells.
+// relaxation, which was the faster one for every volume and cell width tried.
 // Levels against bricks: 8^3 with a site for every voxel or two, 10 updates,
 // 1.52 and 1.18 ms; 25^3 with a site a voxel, one pass, 0.165 and 0.138; 64^3,
 // 1.6 voxels a site, 10 updates, 1.80 and 1.41; one pass of 192 x 96 x 96 1.6
 // and 0.67; 379 x 251 x 147 with 20 updates 27.3 and 12.3; 512 x 256 x 256
-// flame block with 10 updates 52.9 and 8.4.
+// flame block with 10 updates 52.9 and 8.4.  Thin volumes too, although their
+// bricks are mostly empty (10 updates, 64 voxels a site): 2048 x 2048 x 1 in each
+// of its three orientations 14.4 to 18.2 and 6.4 to 8.5, 2 x 1448 x 1448 8.1 and
+// 6.0 (the closest of 19 shapes of one to 16 voxels along an axis, with 64, 512 and
+// 4096 voxels a site: 1.3 to 6.3 times), 32767 x 1 x 1 2.4 and 1.4.
 enum class VTEngine { Auto = 0, Levels = 1, Bricks = 2 };
 
 thread_local VTEngine t_engine = VTEngine::Auto;
@@ -2444,7 +2454,7 @@ unsigned finish_grid(const VTGrid &bg) {
 }
 
 // The schedule of the call's passes, and the edge masks of the bands in its form.
-int32_t vt_prepare(const uint8_t *band, const Geom &g, uint32_t S, CvtWork &W, VTState &st, hipStream_t s) {
+int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, VTState &st, hipStream_t s) {
   VTGrid bg = vt_grid(g);
   st.bricks = vt_engine() == VTEngine::Bricks;
   if (st.bricks) {
@@ -3372,7 +3382,7 @@ extern "C" int32_t lsrvt_vt(const uint8_t *d_band, lsrvt_dims dims, const uint32
   hipStream_t s = as_stream(stream);
   if ((rc = begin(W, g, s))) return rc;
   VTState st;
-  if ((rc = vt_prepare(d_band, g, n_sites, W, st, s))) return rc;
+  if ((rc = vt_prepare(d_band, g, W, st, s))) return rc;
   if ((rc = vt_pass(g, d_sites, n_sites, d_cell, W, st, false, s))) return rc;
   return vt_errors(W, s);
 }
@@ -3409,7 +3419,7 @@ extern "C" int32_t lsrvt_cvt(const uint8_t *d_band, const uint32_t *d_comp, lsrv
     LSRVT_LAUNCHED();
   }
   VTState st;
-  if ((rc = vt_prepare(d_band, g, n_sites, W, st, s))) return rc;
+  if ((rc = vt_prepare(d_band, g, W, st, s))) return rc;
   const Fuse fz{d_weights, n_sites, Sums{W.sums}};
   for (int32_t t = 0; t <= iters; ++t) {
     // the first pass covers every voxel; later ones only what the moved sites change.  A pass
