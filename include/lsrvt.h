@@ -532,9 +532,9 @@ int32_t lsrvt_set_vt_engine(int32_t engine);
  *                           16384 bricks, 8192 beyond)
  *   LSRVT_TUNE_STATS_TILE   voxels staged in LDS per thread and round by the
  *                           statistics' cell kernel (its tile is this times
- *                           its workgroup size): 1, 2 or 4 (the largest of
- *                           these up to the value that fits in 64 KiB of
- *                           LDS), 0 = 1
+ *                           its workgroup size): 1, 2 or 4 (a round that
+ *                           does not fit in 64 KiB of LDS is the library's
+ *                           choice), 0 = the library's choice (1)
  *   LSRVT_TUNE_KEY_BITS     key width of the brick relaxation: 0 = narrow
  *                           32-bit keys (distance and site id) when the site
  *                           ids fit in 24 bits, wide 64-bit keys otherwise;

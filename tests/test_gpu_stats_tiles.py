@@ -1,6 +1,6 @@
-"""Staging rounds of the statistics that fit in LDS, that fit only in half the
-asked size and that do not fit at all: the sums' order does not depend on the
-round, so every output is that of the library's own choice, bit for bit."""
+"""Staging rounds of the statistics that fit in LDS and that do not: the sums'
+order does not depend on the round, so every output is that of the library's
+own choice, bit for bit."""
 import numpy as np
 import pytest
 
