@@ -1897,11 +1897,14 @@ __global__ void k_snap(View cell, Geom g, uint32_t S, Sums sums, uint32_t *sites
 // Flat: volumes of at most kFlatEdge voxels along an axis, where a cube of that
 // half-width holds little and one plane (or row) of it would be all that a team
 // has to share.  The near search goes to the half-width that holds about a
-// thousand voxels (flat_near), and the team's waves take the rows of all planes
-// in turn.  One update of 256 x 256 x 1, 2048 x 1 x 2048, 1024 x 1024 x 2 and
-// 512 x 512 x 6 voxels with 512 voxels a site: 43, 127, 64 and 57 us, in the
-// other form 54, 172, 77 and 61; of 512 x 512 x 8 61 and 65 us, with 4096
-// voxels a site 77 and 67.
+// thousand voxels (flat_near), and the team's lanes take the voxels of the box
+// one after the other.  One update in this and the other form (nx x ny x nz):
+// 1 x 256 x 256 with 512 voxels a site 71 and 83 us, 256 x 256 x 1 with 4096 47
+// and 53; cells of 400 consecutive voxels, of which many are broken at a row's
+// end: 2048 x 1 x 2048 12.1 and 21.0 ms, 1024 x 1024 x 2 2.9 and 15.6,
+// 512 x 512 x 6 1.48 and 1.81, 512 x 8 x 512 0.56 and 0.37.  (Rows of the box
+// over the lanes instead of its voxels leave most lanes idle where x is short:
+// 8.5 ms for 1 x 1024 x 1024 and such cells of 209 voxels, now 1.7.)
 constexpr int32_t kSnapNear = 4;
 constexpr int32_t kFlatEdge = 6;
 __device__ __forceinline__ int32_t flat_near(Geom g) {
@@ -2037,29 +2040,28 @@ __device__ __forceinline__ bool snap_search(const View &cell, Geom g, const unsi
     const double rho2 = reach();
     const uint32_t before = bestv;
     const int32_t width = hi[0] - lo[0] + 1;
-    const int32_t XL = Flat && width <= 4 ? 4 : width <= 16 ? 16 : width <= 32 ? 32 : kWave;  // lanes of a row
+    const int32_t XL = width <= 16 ? 16 : width <= 32 ? 32 : kWave;  // lanes of a row
     const int32_t per = kWave / XL;
     if constexpr (Flat) {
-      constexpr int kFlatAhead = 3;
-      const uint32_t ny = (uint32_t)(hi[1] - lo[1] + 1), rows = ny * (uint32_t)(hi[2] - lo[2] + 1);
-      for (uint32_t q0 = 0; q0 < rows; q0 += (uint32_t)(W * kFlatAhead * per))
-        for (int32_t xc = lo[0]; xc <= hi[0]; xc += XL) {
-          const int32_t x = xc + lane % XL;
-          uint32_t id[kFlatAhead];
-          int32_t y[kFlatAhead], z[kFlatAhead];
+      constexpr int kFlatAhead = 4;
+      const uint32_t nx = (uint32_t)width, ny = (uint32_t)(hi[1] - lo[1] + 1);
+      const uint32_t all = nx * ny * (uint32_t)(hi[2] - lo[2] + 1);
+      for (uint32_t i0 = (uint32_t)(w * kWave); i0 < all; i0 += (uint32_t)(W * kFlatAhead * kWave)) {
+        uint32_t id[kFlatAhead];
+        int32_t x[kFlatAhead], y[kFlatAhead], z[kFlatAhead];
 #pragma unroll
-          for (int u = 0; u < kFlatAhead; ++u) {
-            const uint32_t row = q0 + (uint32_t)((u * W + w) * per + lane / XL);
-            y[u] = lo[1] + (int32_t)(row % ny);
-            z[u] = lo[2] + (int32_t)(row / ny);
-            const double ex = x - cx, ey = y[u] - cy, ez = z[u] - cz;
-            id[u] = x <= hi[0] && row < rows && ex * ex + ey * ey + ez * ez <= rho2 ? cell.id(x, y[u], z[u]) : kNone;
-          }
-#pragma unroll
-          for (int u = 0; u < kFlatAhead; ++u)
-            if (id[u] == s)
-              take(dist(x, y[u], z[u]), (uint32_t)(x + (int64_t)g.nx * (y[u] + (int64_t)g.ny * z[u])));
+        for (int u = 0; u < kFlatAhead; ++u) {
+          const uint32_t i = i0 + (uint32_t)(u * W * kWave + lane), row = i / nx;
+          x[u] = lo[0] + (int32_t)(i - row * nx);
+          y[u] = lo[1] + (int32_t)(row % ny);
+          z[u] = lo[2] + (int32_t)(row / ny);
+          const double ex = x[u] - cx, ey = y[u] - cy, ez = z[u] - cz;
+          id[u] = i < all && ex * ex + ey * ey + ez * ez <= rho2 ? cell.id(x[u], y[u], z[u]) : kNone;
         }
+#pragma unroll
+        for (int u = 0; u < kFlatAhead; ++u)
+          if (id[u] == s) take(dist(x[u], y[u], z[u]), (uint32_t)(x[u] + (int64_t)g.nx * (y[u] + (int64_t)g.ny * z[u])));
+      }
     } else {
       for (int32_t z = lo[2] + w; z <= hi[2]; z += W) {
         const double ez2 = (z - cz) * (z - cz);
