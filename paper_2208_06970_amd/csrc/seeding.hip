@@ -126,56 +126,47 @@ __device__ __forceinline__ uint64_t div_small(u128 num, u128 den, uint32_t *err)
 }
 
 // ---------------------------------------------------------------------------
-// Components and masses of the block's voxels 16 t .. 16 t + 15; returns the
-// mask of those inside the volume.  With the largest block edge (Row) these are
-// a row, read in four (two for the weights) wide loads; it has kernels of its
-// own because the addresses of the general case take twice the registers.
+// Components and masses of row t of the block (its voxels B t .. B t + B - 1);
+// returns the mask of those inside the volume.  Sixteen voxels are read in four
+// (two for the weights) wide loads, whatever the edge: what lies past the row is
+// not used, and only where it would lie past the volume's last voxel are they
+// read one by one.  (The call on 501 x 333 x 187 voxels in 6 isobands with weights and
+// edge 15 takes 0.58 ms so, 2.16 reading a row voxel by voxel, 1.55 with
+// sixteen voxels a thread across the rows and 1.50 with neighbouring lanes on
+// neighbouring voxels.)
 constexpr int kPer = kBlockCap / kSeedThreads;
-template <bool Row>
-__device__ __forceinline__ uint32_t load_run(const uint32_t *__restrict__ comp, const SeedGeom &G, const MassIn &mi,
+__device__ __forceinline__ uint32_t load_row(const uint32_t *__restrict__ comp, const SeedGeom &G, const MassIn &mi,
                                              int64_t b, int t, uint32_t vc[kPer], uint32_t vm[kPer]) {
   static_assert(kPer == kMaxBlockEdge, "a thread's voxels are a row of the largest block");
-  const int nv = G.B * G.B * G.B;
-  if (Row) {
-    const int64_t v = block_voxel(G, b, t * kPer);
-    if (v < 0) return 0u;
-    const int left = G.g.nx - (int)(b % G.nbx) * kPer;
-    if (left >= kPer) {
-      uint16_t w[kPer];
-      __builtin_memcpy(vc, comp + v, sizeof(uint32_t) * kPer);
-      if (mi.w) __builtin_memcpy(w, mi.w + v, sizeof(w));
+  if (t >= G.B * G.B) return 0u;
+  const int64_t v = block_voxel(G, b, t * G.B);
+  if (v < 0) return 0u;
+  const int left = min(G.B, G.g.nx - (int)(b % G.nbx) * G.B);
+  if (v + kPer <= G.g.n) {
+    uint16_t w[kPer];
+    __builtin_memcpy(vc, comp + v, sizeof(uint32_t) * kPer);
+    if (mi.w) __builtin_memcpy(w, mi.w + v, sizeof(w));
 #pragma unroll
-      for (int j = 0; j < kPer; ++j) vm[j] = !mi.w ? 1u : mi.lut ? mi.lut[w[j]] : (uint32_t)w[j];
-      return (1u << kPer) - 1u;
-    }
+    for (int j = 0; j < kPer; ++j) vm[j] = !mi.w ? 1u : mi.lut ? mi.lut[w[j]] : (uint32_t)w[j];
+  } else {
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
       if (j < left) {
         vc[j] = comp[v + j];
         vm[j] = voxel_mass(mi, v + j);
       }
-    return (1u << left) - 1u;
   }
-  uint32_t in = 0;
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int k = t * kPer + j;
-    const int64_t v = k < nv ? block_voxel(G, b, k) : -1;
-    if (v >= 0) {
-      vc[j] = comp[v];
-      vm[j] = voxel_mass(mi, v);
-      in |= 1u << j;
-    }
-  }
-  return in;
+  return (1u << left) - 1u;
 }
 
 // per block: distinct components (pass 0 counts them and sums the block's
 // mass; pass 1 writes the pairs: component, block, mass, in any order).  A
 // block of one component needs no table; in the others each thread adds the
-// runs of its 16 voxels (501 x 333 x 187 voxels with 5 isobands and a table of
+// runs of its row (501 x 333 x 187 voxels with 5 isobands and a table of
 // masses: the two passes took 0.34 ms with an atomic for each voxel, now 0.28).
-template <int Pass, bool Row>
+// Edge: the block edge where it is known to the compiler (the usual 16: 2 to 4 % of the
+// call on labels of many small components), else 0.
+template <int Pass, int Edge>
 __global__ __launch_bounds__(kSeedThreads) void k_seed_blocks(const uint32_t *__restrict__ comp, SeedGeom G,
                                                               uint32_t n_comp, MassIn mi, uint32_t *pcnt,
                                                               unsigned long long *bmass, const uint32_t *poff,
@@ -185,11 +176,12 @@ __global__ __launch_bounds__(kSeedThreads) void k_seed_blocks(const uint32_t *__
   __shared__ unsigned long long msum[Pass ? kBlockCap : 1];
   __shared__ uint32_t wsum[kSeedThreads / kWave];
   __shared__ unsigned long long red[kSeedThreads / kWave];
+  if (Edge) G.B = Edge;
   const int t = threadIdx.x, lane = lane_id(), wid = t / kWave;
   for (int64_t b = blockIdx.x; b < G.nblocks; b += gridDim.x) {
     const uint32_t c0 = comp[block_voxel(G, b, 0)];  // a block's first voxel is inside the volume
     uint32_t vc[kPer], vm[kPer];
-    uint32_t in = load_run<Row>(comp, G, mi, b, t, vc, vm);
+    uint32_t in = load_row(comp, G, mi, b, t, vc, vm);
     bool one = true;
     unsigned long long mine = 0;
 #pragma unroll
@@ -543,12 +535,12 @@ __global__ void k_seed_unsort(const uint32_t *idx, int64_t P, const uint32_t *sn
 
 // Per block, each pair with sites: prefix sums of the pair's mass over the
 // block's voxels in linear order, then the systematic points.  The block's
-// components and masses are read once into registers (thread t holds voxels
-// 16 t .. 16 t + 15); per pair the prefix sums are a wave scan of the
+// components and masses are read once into registers (thread t holds row t);
+// per pair the prefix sums are a wave scan of the
 // per-thread sums plus the four wave totals.  They lie in LDS with one place
 // unused after every 16, so that the threads' stores meet different banks
 // (501 x 333 x 187 voxels: 0.45 ms before, 0.22 now).
-template <bool Row>
+template <int Edge>
 __global__ __launch_bounds__(kSeedThreads) void k_seed_place(const uint32_t *__restrict__ comp, SeedGeom G,
                                                              MassIn mi, const uint32_t *poff,
                                                              const uint32_t *pair_comp,
@@ -558,6 +550,7 @@ __global__ __launch_bounds__(kSeedThreads) void k_seed_place(const uint32_t *__r
                                                              uint32_t key_hi, uint32_t *sites, uint32_t cap) {
   __shared__ unsigned long long cum[kBlockCap + kBlockCap / kPer];
   __shared__ unsigned long long wtot[kSeedThreads / kWave];
+  if (Edge) G.B = Edge;
   const int t = threadIdx.x, lane = lane_id(), wid = t / kWave;
   for (int64_t b = blockIdx.x; b < G.nblocks; b += gridDim.x) {
     const uint32_t k0 = poff[b], k1 = poff[b + 1];
@@ -565,7 +558,7 @@ __global__ __launch_bounds__(kSeedThreads) void k_seed_place(const uint32_t *__r
     for (uint32_t k = k0 + t; k < k1; k += kSeedThreads) any |= nb_pair[k];
     if (!__syncthreads_or(any != 0u)) continue;  // no site in this block
     uint32_t vc[kPer], vm[kPer];
-    const uint32_t in = load_run<Row>(comp, G, mi, b, t, vc, vm);
+    const uint32_t in = load_row(comp, G, mi, b, t, vc, vm);
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
       if (!(in >> j & 1u)) {
@@ -621,7 +614,7 @@ __global__ __launch_bounds__(kSeedThreads) void k_seed_place(const uint32_t *__r
           else
             lo = mid + 1;
         }
-        const int64_t v = block_voxel(G, b, lo);
+        const int64_t v = block_voxel(G, b, lo / kPer * G.B) + lo % kPer;  // place lo: voxel lo % 16 of row lo / 16
         if (so + j < cap) sites[so + j] = (uint32_t)v;
       }
       __syncthreads();
@@ -737,8 +730,8 @@ extern "C" int32_t lsrvt_seed(const uint32_t *d_comp, const uint32_t *d_comp_fir
   const unsigned gb = (unsigned)std::min<int64_t>(G.nblocks, 65535);
   if ((rc = fill<uint32_t>(W.err, 2, 0u, s))) return rc;
   // pairs per block, block masses, total mass
-  const bool row = block == kPer;
-  hipLaunchKernelGGL((row ? k_seed_blocks<0, true> : k_seed_blocks<0, false>), dim3(gb), dim3(kSeedThreads), 0, s,
+  const bool usual = block == kMaxBlockEdge;
+  hipLaunchKernelGGL((usual ? k_seed_blocks<0, kMaxBlockEdge> : k_seed_blocks<0, 0>), dim3(gb), dim3(kSeedThreads), 0, s,
                      d_comp, G, n_comp, mi, W.pcnt, W.bmass, nullptr, nullptr, nullptr, nullptr, W.err);
   hipLaunchKernelGGL(k_seed_total, dim3(1), dim3(kSeedThreads), 0, s, W.bmass, G.nblocks, W.total);
   LSRVT_LAUNCHED();
@@ -751,7 +744,7 @@ extern "C" int32_t lsrvt_seed(const uint32_t *d_comp, const uint32_t *d_comp_fir
   const uint32_t P = hdr[0];
   if (h_n_pairs) *h_n_pairs = P;
   if (P > cap_pairs) return LSRVT_ECAPACITY;
-  hipLaunchKernelGGL((row ? k_seed_blocks<1, true> : k_seed_blocks<1, false>), dim3(gb), dim3(kSeedThreads), 0, s,
+  hipLaunchKernelGGL((usual ? k_seed_blocks<1, kMaxBlockEdge> : k_seed_blocks<1, 0>), dim3(gb), dim3(kSeedThreads), 0, s,
                      d_comp, G, n_comp, mi, W.pcnt, W.bmass, W.poff, W.pair_comp, W.pair_block, W.pair_mass, W.err);
   // stable radix sort of the pairs by component (block order is kept)
   hipLaunchKernelGGL(k_seed_iota, dim3(blocks_for_n(P)), dim3(256), 0, s, W.val_a, (int64_t)P);
@@ -789,8 +782,8 @@ extern "C" int32_t lsrvt_seed(const uint32_t *d_comp, const uint32_t *d_comp_fir
   if (S > cap_sites) return LSRVT_ECAPACITY;
   hipLaunchKernelGGL(k_seed_unsort, dim3(blocks_for_n(P)), dim3(256), 0, s, cur, (int64_t)P, W.snb, W.ssoff,
                      W.nb_pair, W.soff_pair);
-  hipLaunchKernelGGL((row ? k_seed_place<true> : k_seed_place<false>), dim3(gb), dim3(kSeedThreads), 0, s, d_comp, G, mi, W.poff, W.pair_comp,
-                     W.pair_mass, d_comp_first, W.nb_pair, W.soff_pair, (uint32_t)seed, (uint32_t)(seed >> 32),
+  hipLaunchKernelGGL((usual ? k_seed_place<kMaxBlockEdge> : k_seed_place<0>), dim3(gb), dim3(kSeedThreads), 0, s, d_comp,
+                     G, mi, W.poff, W.pair_comp, W.pair_mass, d_comp_first, W.nb_pair, W.soff_pair, (uint32_t)seed, (uint32_t)(seed >> 32),
                      d_sites, cap_sites);
   LSRVT_LAUNCHED();
   return LSRVT_OK;
