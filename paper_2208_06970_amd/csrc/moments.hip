@@ -440,7 +440,9 @@ struct MomGroups {
   uint32_t J;
 };
 
-// Counts and first sums about the mean of the group's first member: of every
+// Counts and first sums about the mean of the group's first member (about zero
+// where that is not finite, so that what an infinite mean gives does not hang on
+// which member has it): of every
 // chunk (job = true: rows of `sum`, [m + 1] each) or of every group, whose
 // mean is formed.
 template <bool job>
@@ -451,7 +453,8 @@ __global__ __launch_bounds__(kWave) void k_mom_mean(MomGroups Q, MergeIn in, Mom
     const uint32_t lo = job ? Q.job_lo[b] : Q.off[g], hi = job ? Q.job_hi[b] : Q.off[g + 1];
     if (j > m) continue;  // lane m: the counts
     const uint32_t f = Q.off[g];
-    const double first = j < m && hi > lo ? in.mean[(int64_t)(in.map ? in.map[f] : f) * m + j] : 0.0;
+    const double mean0 = j < m && hi > lo ? in.mean[(int64_t)(in.map ? in.map[f] : f) * m + j] : 0.0;
+    const double first = __builtin_isfinite(mean0) ? mean0 : 0.0;
     const bool split = !job && hi - lo > (uint32_t)kMergeChunk;
     double s = 0.0;
     if (split) {
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(kWave) void k_mom_mean(MomGroups Q, MergeIn in, Mom
       if (j == m)
         out.n[g] = (uint64_t)s;
       else
-        out.mean[(int64_t)g * m + j] = n > 0.0 ? (hi - lo == 1 ? first : first + s / n) : 0.0;
+        out.mean[(int64_t)g * m + j] = n > 0.0 ? (hi - lo == 1 ? mean0 : first + s / n) : 0.0;
     }
   }
 }
