@@ -905,20 +905,26 @@ struct LosWork {
 };
 
 // The bit planes and their tiles: words along x, or, when x is too short to
-// fill them, along the longer of the other two axes if that is longer.  A tile
-// is a wave, so in a volume of one voxel along x words along x leave 16 voxels
-// to each of 32 times as many waves.  One update with words along x and along
-// the longer axis: 1 x 1024 x 1024 voxels 63.3 and 25.7 ms, 2 x 1024 x 1024
-// 44.6 and 19.6, 4 x 512 x 512 14.0 and 10.7, 6 x 512 x 512 11.3 and 9.2;
-// 8 x 400 x 300 6.1 and 6.0, 16 x 256 x 300 6.4 and 6.9, 24 x 256 x 200 6.2 and
-// 6.8 (neighbours along the words lie nx apart in memory): from 8 on, x.
+// fill them and the volume is large, along the longer of the other two axes if
+// that is longer.  A tile is a wave, so in a volume of one voxel along x words
+// along x leave 16 voxels to each of 32 times as many waves; those run side by
+// side until the card is full (4096 of these waves), and neighbours along the
+// words lie nx apart in memory when turned, so a few waves of 16 voxels are
+// better than fewer full ones.  One update with turned words over one without,
+// e x e voxels across nx along x, 4 bands, 64 voxels a site: nx = 1 1.01 (e =
+// 200), 0.94 (300), 0.86 (360), 0.70 (512), 0.55 (724); nx = 4 1.14, 1.05,
+// 0.99, 0.81, 0.65; nx = 7 1.12, 1.06, 0.99, 0.86, 0.75.  The line is drawn
+// between 300 and 360, at kTurnTiles tiles along x.  From 8 voxels on, x:
+// 8 x 400 x 300 voxels 6.1 ms and 6.0 turned, 16 x 256 x 300 6.4 and 6.9.
 struct LosPlane {
   int32_t axis, pa, pb, pc, pw, ty, tz;
 };
 constexpr int32_t kTurn = 8;
+constexpr int64_t kTurnTiles = 6000;
 LosPlane los_plane(const Geom &g) {
   LosPlane P{0, g.nx, g.ny, g.nz, 0, 0, 0};
-  if (g.nx < kTurn && std::max(g.ny, g.nz) > g.nx)
+  const int64_t tiles = (int64_t)((g.ny + kTY - 1) / kTY) * ((g.nz + kTZ - 1) / kTZ);  // of one word along x
+  if (g.nx < kTurn && tiles > kTurnTiles && std::max(g.ny, g.nz) > g.nx)
     P = g.ny >= g.nz ? LosPlane{1, g.ny, g.nx, g.nz, 0, 0, 0} : LosPlane{2, g.nz, g.nx, g.ny, 0, 0, 0};
   P.pw = (P.pa + kTX - 1) / kTX;
   P.ty = (P.pb + kTY - 1) / kTY;

@@ -1,7 +1,7 @@
-"""Line-of-sight passes on volumes that are short along x, whose bit planes
-and tiles lie along y or z instead: the shortest and the longest x of that
-rule and one past it, words and tiles one voxel short of, at and past their
-ends, bit for bit against the oracle."""
+"""Line-of-sight passes on small volumes that are short along x (whose bit
+planes lie along x like the others'; the large ones' lie along y or z): words
+and tiles one voxel short of, at and past their ends, bit for bit against the
+oracle."""
 import numpy as np
 import pytest
 
