@@ -505,7 +505,9 @@ int32_t lsrvt_los_cvt(const uint32_t *d_comp, lsrvt_dims dims, const uint32_t *d
 /* ------------------------------------------------------------------------
  * Schedule of the Voronoi passes of lsrvt_vt and lsrvt_cvt (Eq. 1): both
  * compute the same regions bit for bit.
- *   LSRVT_VT_AUTO     the library's choice (the brick relaxation)
+ *   LSRVT_VT_AUTO     the library's choice (the brick relaxation; the level
+ *                     search for the rest of a call of very many sites with
+ *                     long winding paths among them)
  *   LSRVT_VT_LEVELS   level-synchronous breadth-first search, one launch per
  *                     level, over 16^3 bricks of bit masks
  *   LSRVT_VT_BRICKS   brick relaxation: rounds of launches over marked 16^3

@@ -6,7 +6,7 @@ changes what is computed):
 * the schedule of the Voronoi passes (``lsrvt_set_vt_engine``): the
   level-synchronous search or the brick relaxation.  Both give the same
   regions; the library takes the relaxation by itself, which was the faster
-  one for every shape and cell width tried.  Tuned per job class by timing
+  one for every shape and cell width tried with sites from ``lsrvt_seed``.  Tuned per job class by timing
   one Voronoi pass with each.
 * the number of streams of ``lsrvt_batch_run``'s per-job phases (labels and
   statistics), tuned per batch by timing the whole batch;

@@ -860,7 +860,7 @@ struct BRArgs {
   uint32_t *mark;                  // [2][nbricks]: mark[r & 1][b] == r when brick b works in round r
   uint32_t *list;                  // [nbricks] bricks of the current round (large volumes)
   uint32_t *cnt;                   // [2] length of round r's list at r & 1
-  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into the first rounds, [3] error bits, [13] last round
+  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into the first rounds, [3] error bits, [12] bricks worked on, [13] last round
   const uint8_t *moved;            // the sites the last update moved (fused reset)
   const uint32_t *fsites;          // the sites' voxels (fused reset)
   uint32_t *alive;                 // [3] round alive flags (by r % 3); shared by the jobs of a batch
@@ -1407,6 +1407,7 @@ __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_roun
     A.cnt[(r + 1) & 1] = 0u;    // the list of round r + 1 counts in it
     A.hist[r % kHistLen] = count;
     if (count) A.ctl[13] = r;   // the last round that had work
+    A.ctl[12] += count;
   }
   for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) br_process<KT>(A, A.list[item], r, L);
 }
@@ -1417,7 +1418,11 @@ __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_roun
   __shared__ BRLds<KT> L;
   if (blockIdx.x == 0 && threadIdx.x == 0) A.alive[(r + 2) % 3] = 0u;  // round r + 1 sets it
   if (A.mark[(size_t)(r & 1) * A.bg.nbricks + blockIdx.x] != r) return;
-  if (threadIdx.x == 0) A.ctl[13] = r;  // the last round that had work
+  if (threadIdx.x == 0) {
+    A.ctl[13] = r;  // the last round that had work
+    // bricks that worked, from every 32nd of them (one counter for all would queue up)
+    if ((blockIdx.x * 2654435761u) >> 27 == 0u) atomicAdd(&A.ctl[12], 32u);
+  }
   br_process<KT>(A, blockIdx.x, r, L);
 }
 
@@ -2340,12 +2345,15 @@ struct VTState {
   bool bricks = false;      // passes by brick relaxation (else by level search)
   bool keys_set = false;    // the key width of the brick relaxation is chosen at its first pass
   uint32_t id_bits = 0;     // narrow keys: the id field's bits; 0: wide keys
+  uint32_t br_work = 0;     // bricks relaxed by a pass that outgrew its narrow keys
+  const uint8_t *band = nullptr;  // the bands of the call
 };
 
 // Which schedule computes the Voronoi passes: the level-synchronous search
 // or the brick relaxation (both give the same regions bit for bit).  The
 // choice is made per host thread (lsrvt_set_vt_engine); by default the brick
-// relaxation, which was the faster one for every volume and cell width tried.
+// relaxation, which was the faster one for every volume and cell width tried with
+// sites drawn by lsrvt_seed (and see levels_after_narrow).
 // Levels against bricks: 8^3 with a site for every voxel or two, 10 updates,
 // 1.52 and 1.18 ms; 25^3 with a site a voxel, one pass, 0.165 and 0.138; 64^3,
 // 1.6 voxels a site, 10 updates, 1.80 and 1.41; one pass of 192 x 96 x 96 1.6
@@ -2461,20 +2469,46 @@ unsigned finish_grid(const VTGrid &bg) {
   return (unsigned)(g < 65535 ? g : 65535);
 }
 
-// The schedule of the call's passes, and the edge masks of the bands in its form.
-int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, VTState &st, hipStream_t s) {
+// The edge masks of the bands in the form of the call's schedule.
+int32_t vt_masks(const Geom &g, CvtWork &W, const VTState &st, hipStream_t s) {
   VTGrid bg = vt_grid(g);
-  st.bricks = vt_engine() == VTEngine::Bricks;
   if (st.bricks) {
-    hipLaunchKernelGGL(k_br_masks, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, band, g, bg, W.eq);
+    hipLaunchKernelGGL(k_br_masks, dim3(brick_grid(bg)), dim3(kVTThreads), 0, s, st.band, g, bg, W.eq);
     LSRVT_LAUNCHED();
     return LSRVT_OK;
   }
   const int64_t slots = bg.nbricks * kRows * BX;
   const unsigned grid = (unsigned)std::min<int64_t>((slots + kVTThreads - 1) / kVTThreads, 65535);
-  hipLaunchKernelGGL(k_vt_eq, dim3(grid), dim3(kVTThreads), 0, s, band, g, bg, W.eq);
+  hipLaunchKernelGGL(k_vt_eq, dim3(grid), dim3(kVTThreads), 0, s, st.band, g, bg, W.eq);
   LSRVT_LAUNCHED();
   return LSRVT_OK;
+}
+
+// The schedule of the call's passes and its masks.
+int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, VTState &st, hipStream_t s) {
+  st.band = band;
+  st.bricks = vt_engine() == VTEngine::Bricks;
+  return vt_masks(g, W, st, s);
+}
+
+// Whether a call whose narrow keys ran out of distance goes on by levels instead
+// of wide keys (by the library's choice only); work: the bricks relaxed in all
+// rounds until then.  Where sites are many, narrow keys hold few hundred hops, and
+// a pass that needs more has long winding paths among them: noise with a site for
+// every component, near the fraction at which a band's largest component reaches
+// through the volume.  Its bricks are relaxed some twenty times, where a level
+// touches only what it reaches.  By levels and with wide keys, one pass over three
+// random bands: 256^3 voxels (7.4 a site, 6.7 relaxations a brick so far) 12.4 and
+// 19.2 ms, 300^3 17.5 and 38.8, 360^3 (3.1 so far) 24.6 and 57.9.  Long straight
+// paths past many sites relax few bricks: 512 x 512 x 128 (8 a site, 0.9 so far)
+// 12.8 and 1.7 ms.  With fewer than four voxels a site most components are a few voxels:
+// 256^3 in six noisy bands (2.9 a site, 4.1 so far) 9.7 and 7.2.  (Sites drawn by
+// lsrvt_seed stay far from the limit in all of these, and the relaxation takes 0.4
+// to 0.9 of the levels' time.)
+bool levels_after_narrow(const Geom &g, uint32_t S, uint32_t work) {
+  const int64_t per = g.n / (int64_t)std::max<uint32_t>(S, 1u);
+  return t_engine == VTEngine::Auto && tuning(LSRVT_TUNE_KEY_BITS) == 0 && per >= 4 && per < 1024 &&
+         (int64_t)work >= 2 * vt_grid(g).nbricks;
 }
 
 BFSArgs bfs_args(const Geom &g, CvtWork &W) {
@@ -2816,6 +2850,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     if (c[3] & ~4u) return LSRVT_EDEVICE;
     if (c[3] & 4u) {  // a narrow key reached the largest exact distance
       *far = true;
+      st.br_work = c[12];
       return LSRVT_OK;
     }
     if (c[4 + (r + 1) % 3] == 0) break;
@@ -2861,7 +2896,8 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
 
 // One Voronoi pass by brick relaxation, with narrow keys when the sites
 // allow and until a pass outgrows them: that pass is repeated from the sites
-// with wide keys, which the rest of the call keeps.
+// with wide keys (or by levels, levels_after_narrow), which the rest of the call
+// keeps.
 int32_t run_br(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell, CvtWork &W, VTState &st, bool inc,
                hipStream_t s, const Fuse *fz = nullptr) {
   if (!st.keys_set) {
@@ -2875,6 +2911,11 @@ int32_t run_br(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell,
     st.id_bits = 0;
     if ((rc = fill<uint32_t>(W.ctl + 3, 1, 0u, s))) return rc;
     inc = false;
+    if (levels_after_narrow(g, S, st.br_work)) {
+      st.bricks = false;
+      if ((rc = vt_masks(g, W, st, s))) return rc;
+      return run_vt(g, sites, S, cell, W, st, s, fz);
+    }
   }
   return run_br_k<unsigned long long>(g, sites, S, cell, W, st, inc, s, fz, nullptr);
 }
