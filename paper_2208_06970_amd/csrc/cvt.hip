@@ -860,7 +860,7 @@ struct BRArgs {
   uint32_t *mark;                  // [2][nbricks]: mark[r & 1][b] == r when brick b works in round r
   uint32_t *list;                  // [nbricks] bricks of the current round (large volumes)
   uint32_t *cnt;                   // [2] length of round r's list at r & 1
-  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into the first rounds, [3] error bits, [12] bricks worked on, [13] last round
+  uint32_t *ctl;                   // [1] moved sites, [2] reset fused into the first rounds, [3] error bits, [12] bricks worked on (if counted), [13] last round
   const uint8_t *moved;            // the sites the last update moved (fused reset)
   const uint32_t *fsites;          // the sites' voxels (fused reset)
   uint32_t *alive;                 // [3] round alive flags (by r % 3); shared by the jobs of a batch
@@ -1412,17 +1412,16 @@ __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_roun
   for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) br_process<KT>(A, A.list[item], r, L);
 }
 
-// The same round with one workgroup for every brick.
-template <class KT>
+// The same round with one workgroup for every brick.  Tally: the bricks that work
+// are counted, from every 32nd of them (one counter for all would queue up; loops of
+// 1104 bricks take 1 % longer with it).
+template <class KT, bool Tally>
 __global__ __launch_bounds__(kBRThreads, sizeof(KT) == 4 ? 6 : 4) void k_br_round_all(BRArgs A, uint32_t r) {
   __shared__ BRLds<KT> L;
   if (blockIdx.x == 0 && threadIdx.x == 0) A.alive[(r + 2) % 3] = 0u;  // round r + 1 sets it
   if (A.mark[(size_t)(r & 1) * A.bg.nbricks + blockIdx.x] != r) return;
-  if (threadIdx.x == 0) {
-    A.ctl[13] = r;  // the last round that had work
-    // bricks that worked, from every 32nd of them (one counter for all would queue up)
-    if ((blockIdx.x * 2654435761u) >> 27 == 0u) atomicAdd(&A.ctl[12], 32u);
-  }
+  if (threadIdx.x == 0) A.ctl[13] = r;  // the last round that had work
+  if (Tally && threadIdx.x == 0 && (blockIdx.x * 2654435761u) >> 27 == 0u) atomicAdd(&A.ctl[12], 32u);
   br_process<KT>(A, blockIdx.x, r, L);
 }
 
@@ -2820,6 +2819,8 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   const int32_t tg = tuning(LSRVT_TUNE_BR_GRID);
   const bool direct = !A.dbg && direct_rounds(bg.nbricks);
   const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 8192);
+  // (with fewer id bits, only paths of more than 4094 hops outgrow narrow keys)
+  const bool tally = sizeof(KT) == 4 && st.id_bits >= 20;
   uint32_t r = 0;
   // Rounds are launched as plain kernels, one each (a captured graph of eight
   // rounds replayed is slower: 14.0 against 13.4 ms for 379 x 251 x 147 voxels
@@ -2837,7 +2838,8 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     for (int i = 0; i < batch; ++i) {
       ++r;
       if (direct) {
-        hipLaunchKernelGGL(k_br_round_all<KT>, dim3((unsigned)bg.nbricks), dim3(kBRThreads), 0, s, A, r);
+        hipLaunchKernelGGL((tally ? k_br_round_all<KT, sizeof(KT) == 4> : k_br_round_all<KT, false>),
+                           dim3((unsigned)bg.nbricks), dim3(kBRThreads), 0, s, A, r);
       } else {
         hipLaunchKernelGGL(k_br_list, dim3(lgrid), dim3(256), 0, s, A, r);
         hipLaunchKernelGGL(k_br_round<KT>, dim3(rgrid), dim3(kBRThreads), 0, s, A, r);
