@@ -2084,13 +2084,13 @@ __device__ __forceinline__ bool snap_search(const View &cell, Geom g, const unsi
             const int32_t x = xc + lane % XL;
             const double ex2 = (x - cx) * (x - cx) + ez2;
             uint32_t id[kRowsAhead];
-  #pragma unroll
+#pragma unroll
             for (int u = 0; u < kRowsAhead; ++u) {
               const int32_t y = yc + u * per + lane / XL;
               const double ey = y - cy;
               id[u] = x <= x1 && y <= y1 && ex2 + ey * ey <= rho2 ? cell.id(x, y, z) : kNone;
             }
-  #pragma unroll
+#pragma unroll
             for (int u = 0; u < kRowsAhead; ++u) {
               if (id[u] != s) continue;
               const int32_t y = yc + u * per + lane / XL;
@@ -2344,7 +2344,7 @@ struct VTState {
   bool bricks = false;      // passes by brick relaxation (else by level search)
   bool keys_set = false;    // the key width of the brick relaxation is chosen at its first pass
   uint32_t id_bits = 0;     // narrow keys: the id field's bits; 0: wide keys
-  uint32_t br_work = 0;     // bricks relaxed by a pass that outgrew its narrow keys
+  uint32_t br_work = 0;     // bricks relaxed by a pass that outgrew its narrow keys (0: not counted)
   const uint8_t *band = nullptr;  // the bands of the call
 };
 
@@ -2492,7 +2492,7 @@ int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, VTState &st, 
 
 // Whether a call whose narrow keys ran out of distance goes on by levels instead
 // of wide keys (by the library's choice only); work: the bricks relaxed in all
-// rounds until then.  Where sites are many, narrow keys hold few hundred hops, and
+// rounds until then.  Where sites are many, narrow keys hold a few hundred hops, and
 // a pass that needs more has long winding paths among them: noise with a site for
 // every component, near the fraction at which a band's largest component reaches
 // through the volume.  Its bricks are relaxed some twenty times, where a level
@@ -2852,7 +2852,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     if (c[3] & ~4u) return LSRVT_EDEVICE;
     if (c[3] & 4u) {  // a narrow key reached the largest exact distance
       *far = true;
-      st.br_work = c[12];
+      st.br_work = tally ? c[12] : 0u;
       return LSRVT_OK;
     }
     if (c[4 + (r + 1) % 3] == 0) break;
