@@ -2352,7 +2352,7 @@ struct VTState {
 // or the brick relaxation (both give the same regions bit for bit).  The
 // choice is made per host thread (lsrvt_set_vt_engine); by default the brick
 // relaxation, which was the faster one for every volume and cell width tried with
-// sites drawn by lsrvt_seed (and see levels_after_narrow).
+// sites drawn by lsrvt_seed (and see levels_after_bricks).
 // Levels against bricks: 8^3 with a site for every voxel or two, 10 updates,
 // 1.52 and 1.18 ms; 25^3 with a site a voxel, one pass, 0.165 and 0.138; 64^3,
 // 1.6 voxels a site, 10 updates, 1.80 and 1.41; one pass of 192 x 96 x 96 1.6
@@ -2490,21 +2490,23 @@ int32_t vt_prepare(const uint8_t *band, const Geom &g, CvtWork &W, VTState &st, 
   return vt_masks(g, W, st, s);
 }
 
-// Whether a call whose narrow keys ran out of distance goes on by levels instead
-// of wide keys (by the library's choice only); work: the bricks relaxed in all
-// rounds until then.  Where sites are many, narrow keys hold a few hundred hops, and
-// a pass that needs more has long winding paths among them: noise with a site for
-// every component, near the fraction at which a band's largest component reaches
-// through the volume.  Its bricks are relaxed some twenty times, where a level
-// touches only what it reaches.  By levels and with wide keys, one pass over three
-// random bands: 256^3 voxels (7.4 a site, 6.7 relaxations a brick so far) 12.4 and
-// 19.2 ms, 300^3 17.5 and 38.8, 360^3 (3.1 so far) 24.6 and 57.9.  Long straight
-// paths past many sites relax few bricks: 512 x 512 x 128 (8 a site, 0.9 so far)
-// 12.8 and 1.7 ms.  With fewer than four voxels a site most components are a few voxels:
-// 256^3 in six noisy bands (2.9 a site, 4.1 so far) 9.7 and 7.2.  (Sites drawn by
-// lsrvt_seed stay far from the limit in all of these, and the relaxation takes 0.4
-// to 0.9 of the levels' time.)
-bool levels_after_narrow(const Geom &g, uint32_t S, uint32_t work) {
+// Whether a call goes on by levels (by the library's choice only) where its narrow
+// keys ran out of distance, or where its sites outnumber their 24 bits and the first
+// pass has not ended after kLongPass rounds; work: the bricks relaxed in all rounds
+// until then.  Where sites are many, narrow keys hold a few hundred hops, and a pass
+// that needs more has long winding paths among them: noise with a site for every
+// component, near the fraction at which a band's largest component reaches through
+// the volume.  Its bricks are relaxed some twenty times, where a level touches only
+// what it reaches.  By levels and with wide keys, one pass over three random bands:
+// 256^3 voxels (7.4 a site, 6.7 relaxations a brick so far) 12.4 and 19.2 ms, 300^3
+// 17.5 and 38.8, 360^3 (3.1 so far) 24.6 and 57.9, 512^3 59 and 113.  Long straight paths
+// past many sites relax few bricks: 512 x 512 x 128 (8 a site, 0.9 so far) 12.8 and
+// 1.7 ms.  With fewer than four voxels a site most components are a few voxels:
+// 256^3 in six noisy bands (2.9 a site, 4.1 so far) 9.7 and 7.2.  (With sites drawn
+// by lsrvt_seed passes over such volumes end within 20 rounds and far from the limit,
+// and the relaxation takes 0.4 to 0.9 of the levels' time.)
+constexpr uint32_t kLongPass = 24;
+bool levels_after_bricks(const Geom &g, uint32_t S, uint32_t work) {
   const int64_t per = g.n / (int64_t)std::max<uint32_t>(S, 1u);
   return t_engine == VTEngine::Auto && tuning(LSRVT_TUNE_KEY_BITS) == 0 && per >= 4 && per < 1024 &&
          (int64_t)work >= 2 * vt_grid(g).nbricks;
@@ -2763,7 +2765,8 @@ BRArgs br_args(const Geom &g, CvtWork &W, uint32_t id_bits) {
 // update that set W.moved.  Rounds are enqueued in batches (the first sized
 // by the previous pass); after each batch the host reads whether any brick
 // is marked.  With narrow keys, a round that stored a key of the largest
-// exact distance sets *far and the pass stops unfinished.
+// exact distance sets *far and the pass stops unfinished, as with wide keys (where
+// far is given) a long pass does that levels_after_bricks hands to the levels.
 // Moved sites above which the reset is fused into the first rounds
 // (k_br_reset_or_fuse).
 // The separate reset reads every key and lets only the bricks that hold reset
@@ -2820,7 +2823,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
   const bool direct = !A.dbg && direct_rounds(bg.nbricks);
   const unsigned rgrid = (unsigned)std::min<int64_t>(bg.nbricks, tg ? tg : 8192);
   // (with fewer id bits, only paths of more than 4094 hops outgrow narrow keys)
-  const bool tally = sizeof(KT) == 4 && st.id_bits >= 20;
+  const bool tally = S > (1u << 19);
   uint32_t r = 0;
   // Rounds are launched as plain kernels, one each (a captured graph of eight
   // rounds replayed is slower: 14.0 against 13.4 ms for 379 x 251 x 147 voxels
@@ -2838,7 +2841,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     for (int i = 0; i < batch; ++i) {
       ++r;
       if (direct) {
-        hipLaunchKernelGGL((tally ? k_br_round_all<KT, sizeof(KT) == 4> : k_br_round_all<KT, false>),
+        hipLaunchKernelGGL((tally ? k_br_round_all<KT, true> : k_br_round_all<KT, false>),
                            dim3((unsigned)bg.nbricks), dim3(kBRThreads), 0, s, A, r);
       } else {
         hipLaunchKernelGGL(k_br_list, dim3(lgrid), dim3(256), 0, s, A, r);
@@ -2857,6 +2860,13 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
     }
     if (c[4 + (r + 1) % 3] == 0) break;
     if ((int64_t)r > max_rounds) return LSRVT_EDEVICE;
+    if (far && sizeof(KT) == 8 && r >= kLongPass) {
+      st.br_work = c[12];
+      if (levels_after_bricks(g, S, st.br_work)) {
+        *far = true;
+        return LSRVT_OK;
+      }
+    }
     // (a long pass waits for the host a few times, not every four rounds: one
     // along a corridor of 256 x 256 x 32 voxels takes 16.6 ms instead of 21.9)
     batch = std::max(4, (int)(r / 4));
@@ -2898,7 +2908,7 @@ int32_t run_br_k(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cel
 
 // One Voronoi pass by brick relaxation, with narrow keys when the sites
 // allow and until a pass outgrows them: that pass is repeated from the sites
-// with wide keys (or by levels, levels_after_narrow), which the rest of the call
+// with wide keys (or by levels, levels_after_bricks), which the rest of the call
 // keeps.
 int32_t run_br(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell, CvtWork &W, VTState &st, bool inc,
                hipStream_t s, const Fuse *fz = nullptr) {
@@ -2912,14 +2922,18 @@ int32_t run_br(const Geom &g, const uint32_t *sites, uint32_t S, uint32_t *cell,
     if (rc || !far) return rc;
     st.id_bits = 0;
     if ((rc = fill<uint32_t>(W.ctl + 3, 1, 0u, s))) return rc;
-    inc = false;
-    if (levels_after_narrow(g, S, st.br_work)) {
-      st.bricks = false;
-      if ((rc = vt_masks(g, W, st, s))) return rc;
-      return run_vt(g, sites, S, cell, W, st, s, fz);
-    }
+    if (!levels_after_bricks(g, S, st.br_work))
+      return run_br_k<unsigned long long>(g, sites, S, cell, W, st, false, s, fz, nullptr);
+  } else {
+    // (a pass that may still change to levels: the first of more sites than narrow keys hold)
+    bool far = false;
+    int32_t rc = run_br_k<unsigned long long>(g, sites, S, cell, W, st, inc, s, fz,
+                                              !inc && S > (1u << 24) ? &far : nullptr);
+    if (rc || !far) return rc;
   }
-  return run_br_k<unsigned long long>(g, sites, S, cell, W, st, inc, s, fz, nullptr);
+  st.bricks = false;
+  int32_t rc = vt_masks(g, W, st, s);
+  return rc ? rc : run_vt(g, sites, S, cell, W, st, s, fz);
 }
 
 // A Voronoi pass with the selected schedule; with fz, its last kernel also

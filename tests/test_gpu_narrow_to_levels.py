@@ -1,22 +1,25 @@
 """A call whose narrow relaxation keys run out of distance by the library's own
 choice: over noise with a site for every component (long winding paths, bricks
-relaxed many times) it goes on by levels, over a wide band with one site beside
-many it stays with the relaxation.  Same cells, sites and displacements as with
+relaxed many times) it goes on by levels, also where the sites are too many for
+narrow keys, over a wide band with one site beside many it stays with the
+relaxation.  Same cells, sites and displacements as with
 each schedule asked for, whose parity with the oracle other tests check."""
 import numpy as np
 import pytest
 
 import paper_2208_06970_amd as L
-from tests.gpu_util import banner, dev, torch
+from tests.gpu_util import banner, torch
 
 pytestmark = pytest.mark.gpu
 
 
-def _noise():
-    band = np.random.default_rng(3).integers(0, 3, size=(256, 256, 256), dtype=np.uint8)
-    cc = L.lsrvt_components(dev(band), 3, cap_comp=1 << 22)
-    assert 1 << 21 < cc.n_comp <= 1 << 22  # 22 bits for the ids, 1022 hops
-    return dev(band), cc.comp, cc.comp_first.contiguous()
+def _noise(edge, bits):
+    t = torch()
+    g = t.Generator(device="cuda").manual_seed(3)
+    band = t.randint(0, 3, (edge,) * 3, device="cuda", generator=g, dtype=t.uint8)
+    cc = L.lsrvt_components(band, 3, cap_comp=1 << bits)
+    assert 1 << (bits - 1) < cc.n_comp <= 1 << bits
+    return band, cc.comp, cc.comp_first.contiguous()
 
 
 def _one_beside_many():
@@ -31,11 +34,13 @@ def _one_beside_many():
     return band, cc.comp, t.cat([seeds, t.tensor([half], device="cuda", dtype=t.int32)])
 
 
-@pytest.mark.parametrize("case,engines", [("noise", 1), ("one beside many", 2)])
+@pytest.mark.parametrize("case,engines", [("noise", 1), ("noise, wide keys", 1), ("one beside many", 2)])
 def test_after_narrow_keys(case, engines):
     t = torch()
     banner(f"narrow keys run out: {case}")
-    band, comp, seeds = _noise() if case == "noise" else _one_beside_many()
+    # (22 bits for the ids leave 1022 hops, 25 do not fit)
+    band, comp, seeds = {"noise": lambda: _noise(256, 22), "noise, wide keys": lambda: _noise(512, 25),
+                         "one beside many": _one_beside_many}[case]()
     L.lsrvt_timing_enable(True)
     try:
         L.lsrvt_timing_read()
